@@ -18,6 +18,7 @@
 // Each wave loads the counts of its own sub-chunks and scans them with DPP,
 // candidate loads are issued in batches, and every workgroup-wide step is one
 // scan or reduction, so the dependency chain stays short.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -30,9 +31,9 @@ namespace pqhsa {
 
 constexpr int kNW = kSelThreads / kWave;
 constexpr int kRankCap = 128;
-constexpr int kNzSubBits = 10;           // sub-chunk bits of a nonempty-list entry
-static_assert((1 << kNzSubBits) >= kSelMaxSub, "sub-chunk ids");
-static_assert(kSelCap < (1 << (31 - kNzSubBits)), "first-candidate indices");          // boundary-bin keys ranked exactly (O(m^2 / 64) ballots)
+constexpr int kNzSubBits = 13;           // sub-chunk bits of a nonempty-list entry
+constexpr int kSelMaxSubWide = kMaxSeq / kSub;   // sub-chunks per row of the wide select
+static_assert((1 << kNzSubBits) >= kSelMaxSubWide, "sub-chunk ids");
 constexpr float kMassScale = 1099511627776.0f;       // 2^40: fixed-point weights
 constexpr float kMassUnscale = 1.0f / 1099511627776.0f;
 
@@ -126,124 +127,158 @@ __device__ __forceinline__ bool rank_boundary_bin(KeyAt key_at, TokAt tok_at, in
 //   rank_idx [kRankCap] | rank_tok [kRankCap] | chosen bitmap [kCap / 32] |
 //   counter, flags [4] | sub-chunk offsets, or the nonempty sub-chunks, [kSelMaxSub] |
 //   mass (uint64) [n_list]
+// The wide select keeps only the keys in LDS (the candidates' words go to
+// global memory), and its nonempty sub-chunks take the key area until the
+// keys are written.
+constexpr int kSelCapWide = 28672;
 template <int kCap>
 struct SelLayout {
+    static constexpr bool kWide = kCap == kSelCapWide;
     static constexpr int kOffCand = kCap;
-    static constexpr int kOffHist = 2 * kCap;
+    static constexpr int kOffHist = kWide ? kCap : 2 * kCap;
     static constexpr int kOffRKey = kOffHist + kHistBins;
     static constexpr int kOffRIdx = kOffRKey + kRankCap;
     static constexpr int kOffRTok = kOffRIdx + kRankCap;
     static constexpr int kOffBits = kOffRTok + kRankCap;
     static constexpr int kOffCounter = kOffBits + kCap / 32;
-    static constexpr int kOffSub = kOffCounter + 4;
-    static constexpr int kOffMass = (kOffSub + kSelMaxSub + 1) & ~1;   // 8-byte aligned
-    static size_t bytes(int n_list) { return static_cast<size_t>(kOffMass + 2 * n_list) * 4; }
+    static constexpr int kOffSub = kWide ? 0 : kOffCounter + 4;
+    static constexpr int kOffMass = (kOffCounter + 4 + (kWide ? 0 : kSelMaxSub) + 1) & ~1;   // 8-byte aligned
+    static constexpr size_t bytes(int n_list) { return static_cast<size_t>(kOffMass + 2 * n_list) * 4; }
     static_assert(kCap % kSelThreads == 0 && kCap % 32 == 0, "whole copy tiers and bitmap words");
     static_assert(kOffCand % 4 == 0, "16-byte candidate stores");
+    static_assert(!kWide || kCap >= kSelMaxSubWide, "the nonempty sub-chunks fit the key area");
+    static_assert(kCap < (1 << (31 - kNzSubBits)), "first-candidate indices");
 };
-// Two capacities: every row's candidates of a large budget in LDS (one
-// workgroup per CU), or fewer (two workgroups per CU, for grids of more rows
-// than CUs; rows beyond it take the global-memory path).
+// Three capacities (select_cap below picks one per call): every row's
+// candidates in LDS (one workgroup per CU); fewer (two workgroups per CU, for
+// grids of more rows than CUs); and the wide one, keys alone, for rows of more
+// than kSelMaxSub sub-chunks or more candidates than the first holds. Rows
+// beyond the capacity take the global-memory path.
 constexpr int kSelCapSmall = 7168;
+constexpr size_t kLdsPerCu = 160 * 1024;
+static_assert(SelLayout<kSelCapWide>::bytes(kMaxLists) + sizeof(SelectScratch) + sizeof(BlockScratch) <= kLdsPerCu,
+              "the wide select fits a CU at the most lists");
 
-// Copy the row's `total` candidates (1 <= total <= N * kSelThreads) from
-// their sub-chunk slots into LDS in position order (one workgroup per CU): keys at lds[i], words
-// (list << kPosBits | token) at lds[kOffCand + i]. Thread t copies the
-// indices u * kSelThreads + t, so neighbouring lanes read neighbouring
-// slots. Candidate i lives in the sub-chunk sc with pre[sc] <= i < pre[sc + 1]
-// (the last of equal offsets, so empty sub-chunks never match). Every thread
-// searches all of its indices together and issues all loads before using
-// any, so the copy costs one search chain and one memory round trip
-// (indices past the end repeat the last candidate's load). Tracks this
-// thread's min / max key.
-// With fixed bins (hist != nullptr), every candidate is also counted in
-// hist at bin min((key - bkmin) >> bsh, kHistBins - 1).
-template <int N, int kOffCand>
-__device__ __forceinline__ void copy_candidates_search(const uint2* __restrict__ cand, const int* pre,
-                                                int nsub, int total, uint32_t* lds,
-                                                uint32_t& kmin, uint32_t& kmax, int* hist,
-                                                uint32_t bkmin, int bsh) {
+// Read the candidates first + u kSelThreads + tid, u < N, of the row's
+// `total` (>= 1) from their sub-chunk slots (one workgroup per CU):
+// neighbouring lanes read neighbouring slots. Candidate i lives in the
+// sub-chunk sc with pre[sc] <= i < pre[sc + 1] (the last of equal offsets, so
+// empty sub-chunks never match). Every thread searches all of its indices
+// together and issues all loads before using any, so the copy costs one search
+// chain and one memory round trip (indices past the end repeat the last
+// candidate's load).
+template <int N, int kMaxSub>
+__device__ __forceinline__ void read_candidates_search(const uint2* __restrict__ cand, const int* pre,
+                                                       int nsub, int first, int total, uint2 (&rec)[N]) {
     const int tid = threadIdx.x;
     // the N searches advance together, one step at a time, so their LDS
     // reads overlap instead of forming one long dependent chain
     int cs[N], ci[N];
 #pragma unroll
     for (int u = 0; u < N; ++u) {
-        ci[u] = min(u * kSelThreads + tid, total - 1);
+        ci[u] = min(first + u * kSelThreads + tid, total - 1);
         cs[u] = 0;
     }
 #pragma unroll
-    for (int step = kSelMaxSub / 2; step > 0; step >>= 1) {
+    for (int step = kMaxSub / 2; step > 0; step >>= 1) {
         int pv[N];
 #pragma unroll
-        for (int u = 0; u < N; ++u) pv[u] = pre[min(cs[u] + step, kSelMaxSub - 1)];
+        for (int u = 0; u < N; ++u) pv[u] = pre[min(cs[u] + step, nsub - 1)];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const int t = cs[u] + step;
             if (t < nsub && pv[u] <= ci[u]) cs[u] = t;
         }
     }
-    uint2 rec[N];
 #pragma unroll
-    for (int u = 0; u < N; ++u) {
-        const int slot = min(u * kSelThreads + tid, total - 1) - pre[cs[u]];   // in [0, count)
-        rec[u] = cand[static_cast<int64_t>(cs[u]) * kSub + slot];
+    for (int u = 0; u < N; ++u)   // slot in [0, count)
+        rec[u] = cand[static_cast<int64_t>(cs[u]) * kSub + (ci[u] - pre[cs[u]])];
+}
+
+// Read the N consecutive candidates first + N tid + u, u < N. nzl lists the
+// row's n_nz nonempty sub-chunks in position order, each as (index of its
+// first candidate << kNzSubBits | sub-chunk), n_nz <= kMaxNz (a power of two).
+// One binary search over nzl finds the entry of the thread's first index, and
+// since every listed sub-chunk holds at least one candidate, index N tid + u
+// lies at most u entries further, which batches of kWin reads settle. All
+// loads are issued before any is used, so the copy costs one search chain and
+// one memory round trip (indices past the end repeat the last candidate's
+// load).
+template <int N, int kMaxNz>
+__device__ __forceinline__ void read_candidates_runs(const uint2* __restrict__ cand, const int* nzl,
+                                                     int n_nz, int first, int total, uint2 (&rec)[N]) {
+    constexpr int kWin = N % 8 == 0 ? 8 : N % 7 == 0 ? 7 : N % 6 == 0 ? 6 : N;
+    static_assert(N % kWin == 0, "whole windows");
+    const int i0 = min(first + N * static_cast<int>(threadIdx.x), total - 1);
+    int k = 0;   // the last entry whose first index is <= i0
+#pragma unroll
+    for (int step = kMaxNz / 2; step > 0; step >>= 1) {
+        const int t = k + step;
+        if (t < n_nz && (nzl[min(t, n_nz - 1)] >> kNzSubBits) <= i0) k = t;
     }
 #pragma unroll
+    for (int w0 = 0; w0 < N; w0 += kWin) {
+        // entries k .. k + kWin (the last one repeated past the list); k holds
+        // the entry of the index before the window, or of its first
+        constexpr int kEnt = kWin + 1;
+        int ent[kEnt];
+#pragma unroll
+        for (int v = 0; v < kEnt; ++v) ent[v] = nzl[min(k + v, n_nz - 1)];
+        int at = 0;
+#pragma unroll
+        for (int u = 0; u < kWin; ++u) {
+            const int i = min(first + N * static_cast<int>(threadIdx.x) + w0 + u, total - 1);
+            int e = ent[0];
+#pragma unroll
+            for (int v = 1; v <= u + (w0 > 0 ? 1 : 0) && v < kEnt; ++v)
+                if ((ent[v] >> kNzSubBits) <= i) {
+                    e = ent[v];
+                    if (u == kWin - 1) at = v;
+                }
+            const int sc = e & ((1 << kNzSubBits) - 1);
+            rec[w0 + u] = cand[static_cast<int64_t>(sc) * kSub + (i - (e >> kNzSubBits))];
+        }
+        k += at;
+    }
+}
+
+// The copy of all candidates (first = 0) into LDS in position order: keys at
+// lds[i], words (list << kPosBits | token) at lds[kOffCand + i], or for the
+// wide select at words[i] in global memory. Tracks this thread's min / max
+// key; with fixed bins (hist != nullptr), every candidate is also counted in
+// hist at bin min((key - bkmin) >> bsh, kHistBins - 1), one LDS atomic per
+// candidate (their bins are mostly distinct).
+template <int N, int kOffCand>
+__device__ __forceinline__ void copy_candidates_search(const uint2* __restrict__ cand, const int* pre,
+                                                int nsub, int total, uint32_t* lds,
+                                                uint32_t& kmin, uint32_t& kmax, int* hist,
+                                                uint32_t bkmin, int bsh) {
+    uint2 rec[N];
+    read_candidates_search<N, kSelMaxSub>(cand, pre, nsub, 0, total, rec);
+#pragma unroll
     for (int u = 0; u < N; ++u) {
-        const int ci = u * kSelThreads + tid;
+        const int ci = u * kSelThreads + static_cast<int>(threadIdx.x);
         const uint32_t kk = float_key(__uint_as_float(rec[u].x));
         if (ci < total) {
             lds[ci] = kk;
             lds[kOffCand + ci] = rec[u].y;
             kmin = min(kmin, kk);
             kmax = max(kmax, kk);
+            if (hist) atomicAdd(&hist[fixed_bin(kk, bkmin, bsh)], 1);
         }
-        // one LDS atomic per candidate: their bins are mostly distinct
-        if (hist && ci < total) atomicAdd(&hist[fixed_bin(kk, bkmin, bsh)], 1);
     }
 }
 
-// The same copy for two workgroups per CU, where the select's VALU work
-// binds: keys at lds[i], words (list << kPosBits | token) at
-// lds[kOffCand + i]. nzl lists the row's n_nz
-// nonempty sub-chunks in position order, each as (index of its first
-// candidate << kNzSubBits | sub-chunk). Thread t copies the N consecutive
-// indices N t .. N t + N - 1: one binary search over nzl finds the entry of
-// the first, and since every listed sub-chunk holds at least one candidate,
-// index N t + u lies at most u entries further, which one batch of N reads
-// settles. All loads are issued before any is used, so the copy costs one
-// search chain and one memory round trip (indices past the end repeat the
-// last candidate's load). Tracks this thread's min / max key.
-// With fixed bins (hist != nullptr), every candidate is also counted in
-// hist at bin min((key - bkmin) >> bsh, kHistBins - 1).
-template <int N, int kOffCand>
+template <int N, int kCap>
 __device__ __forceinline__ void copy_candidates_runs(const uint2* __restrict__ cand, const int* nzl,
-                                                int n_nz, int total, uint32_t* lds,
+                                                int n_nz, int total, uint32_t* lds, int32_t* words,
                                                 uint32_t& kmin, uint32_t& kmax, int* hist,
                                                 uint32_t bkmin, int bsh) {
+    using L = SelLayout<kCap>;
     const int tid = threadIdx.x;
-    const int i0 = min(N * tid, total - 1);
-    int k = 0;   // the last entry whose first index is <= i0
-#pragma unroll
-    for (int step = kSelMaxSub / 2; step > 0; step >>= 1) {
-        const int t = k + step;
-        if (t < n_nz && (nzl[min(t, n_nz - 1)] >> kNzSubBits) <= i0) k = t;
-    }
-    int ent[N];   // entries k .. k + N - 1 (the last one repeated past the list)
-#pragma unroll
-    for (int v = 0; v < N; ++v) ent[v] = nzl[min(k + v, n_nz - 1)];
     uint2 rec[N];
-#pragma unroll
-    for (int u = 0; u < N; ++u) {
-        const int i = min(N * tid + u, total - 1);
-        int e = ent[0];
-#pragma unroll
-        for (int v = 1; v <= u && v < N; ++v)
-            if ((ent[v] >> kNzSubBits) <= i) e = ent[v];
-        const int sc = e & ((1 << kNzSubBits) - 1);
-        rec[u] = cand[static_cast<int64_t>(sc) * kSub + (i - (e >> kNzSubBits))];
-    }
+    read_candidates_runs<N, L::kWide ? kSelMaxSubWide : kSelMaxSub>(cand, nzl, n_nz, 0, total, rec);
+    if constexpr (L::kWide) __syncthreads();   // nzl sits in the key area: read by every wave
     uint32_t kk[N], cw[N];
 #pragma unroll
     for (int u = 0; u < N; ++u) {
@@ -256,22 +291,23 @@ __device__ __forceinline__ void copy_candidates_runs(const uint2* __restrict__ c
 #pragma unroll
         for (int u = 0; u < N; u += 4) {
             *reinterpret_cast<uint4*>(lds + N * tid + u) = make_uint4(kk[u], kk[u + 1], kk[u + 2], kk[u + 3]);
-            *reinterpret_cast<uint4*>(lds + kOffCand + N * tid + u) =
-                make_uint4(cw[u], cw[u + 1], cw[u + 2], cw[u + 3]);
+            if constexpr (!L::kWide)
+                *reinterpret_cast<uint4*>(lds + L::kOffCand + N * tid + u) =
+                    make_uint4(cw[u], cw[u + 1], cw[u + 2], cw[u + 3]);
         }
     } else {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             lds[N * tid + u] = kk[u];
-            lds[kOffCand + N * tid + u] = cw[u];
+            if constexpr (!L::kWide) lds[L::kOffCand + N * tid + u] = cw[u];
         }
     }
 #pragma unroll
     for (int u = 0; u < N; ++u) {
         if (N * tid + u < total) {
+            if constexpr (L::kWide) words[N * tid + u] = static_cast<int32_t>(cw[u]);
             kmin = min(kmin, kk[u]);
             kmax = max(kmax, kk[u]);
-            // one LDS atomic per candidate: their bins are mostly distinct
             if (hist) atomicAdd(&hist[fixed_bin(kk[u], bkmin, bsh)], 1);
         }
     }
@@ -304,7 +340,10 @@ struct BxRow {
     float* bx_wsel;               // [max_topk] W of the list of each entry of T
 };
 
-template <bool kBx, bool kBxPre, typename KeyAt, typename CandAt, typename IsSel>
+// kBatch candidates' keys and words are read at once: 1 where both sit in LDS,
+// 4 where they come from global memory (each read then waits for a round trip
+// of its own, which the stores between them keep the compiler from overlapping).
+template <bool kBx, bool kBxPre, int kBatch, typename KeyAt, typename CandAt, typename IsSel>
 __device__ __forceinline__ void emit_selection(KeyAt key_at, CandAt cand_at, IsSel is_sel,
                                                int total, int k, int n_list,
                                                float shift, unsigned long long* mass,
@@ -314,16 +353,28 @@ __device__ __forceinline__ void emit_selection(KeyAt key_at, CandAt cand_at, IsS
     const int eper = (total + kSelThreads - 1) / kSelThreads;
     const int e0 = min(tid * eper, total);
     const int e1 = min(e0 + eper, total);
+    // every candidate of the thread in order, kBatch read ahead
+    auto each = [&](auto&& f) {
+        for (int i0 = e0; i0 < e1; i0 += kBatch) {
+            uint32_t kb[kBatch], cb[kBatch];
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u) {
+                kb[u] = key_at(min(i0 + u, e1 - 1));
+                cb[u] = cand_at(min(i0 + u, e1 - 1));
+            }
+#pragma unroll
+            for (int u = 0; u < kBatch; ++u)
+                if (kBatch == 1 || i0 + u < e1) f(i0 + u, kb[u], cb[u]);
+        }
+    };
     int nsel = 0;
-    for (int i = e0; i < e1; ++i) nsel += is_sel(i, key_at(i), cand_at(i)) ? 1 : 0;
+    each([&](int i, uint32_t key, uint32_t cand) { nsel += is_sel(i, key, cand) ? 1 : 0; });
     int tot = 0;
     int o = block_excl_scan<kSelThreads, false>(nsel, tot, ss);   // ss is not written before the barrier below
     const int o_first = o;
     int run_list = -1;
     unsigned long long run = 0ull;
-    for (int i = e0; i < e1; ++i) {
-        const uint32_t key = key_at(i);
-        const uint32_t cand = cand_at(i);
+    each([&](int i, uint32_t key, uint32_t cand) {
         const int lst = static_cast<int>(cand >> kPosBits);
         if (lst != run_list) {
             if (run) atomicAdd(&mass[run_list], run);
@@ -336,7 +387,7 @@ __device__ __forceinline__ void emit_selection(KeyAt key_at, CandAt cand_at, IsS
         } else {
             run += static_cast<unsigned long long>(__expf(key_float(key) - shift) * kMassScale);
         }
-    }
+    });
     if (run) atomicAdd(&mass[run_list], run);
     __syncthreads();
     if constexpr (!kBx) {
@@ -374,13 +425,12 @@ __device__ __forceinline__ void emit_selection(KeyAt key_at, CandAt cand_at, IsS
         for (int j = tid; j < n_list; j += kSelThreads) cnt[j] = 0;
         __syncthreads();
         o = o_first;
-        for (int i = e0; i < e1; ++i) {
-            const uint32_t cand = cand_at(i);
-            if (is_sel(i, key_at(i), cand)) {
+        each([&](int i, uint32_t key, uint32_t cand) {
+            if (is_sel(i, key, cand)) {
                 if (o < k) atomicAdd(&cnt[cand >> kPosBits], 1);
                 ++o;
             }
-        }
+        });
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < kBxPer; ++u) {
@@ -394,13 +444,12 @@ __device__ __forceinline__ void emit_selection(KeyAt key_at, CandAt cand_at, IsS
         }
         __syncthreads();
         o = o_first;
-        for (int i = e0; i < e1; ++i) {
-            const uint32_t cand = cand_at(i);
-            if (is_sel(i, key_at(i), cand)) {
+        each([&](int i, uint32_t key, uint32_t cand) {
+            if (is_sel(i, key, cand)) {
                 if (o < k) bx.bx_wsel[o] = wl[cand >> kPosBits];
                 ++o;
             }
-        }
+        });
     }
 }
 
@@ -443,7 +492,11 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
     // faster at 512 rows), by a search of every index over the sub-chunk
     // offsets with one workgroup per CU (0.4 us faster at 32 rows: its loads
     // of neighbouring lanes touch neighbouring slots)
-    constexpr bool kRunsCopy = kCap == kSelCapSmall;
+    // (and for the wide rows, whose search would be a step per doubling longer
+    // for every index)
+    constexpr bool kWide = L::kWide;
+    constexpr bool kRunsCopy = kCap == kSelCapSmall || kWide;
+    constexpr int kMaxSub = kWide ? kSelMaxSubWide : kSelMaxSub;
     int* subl = reinterpret_cast<int*>(lds + L::kOffSub);
     __shared__ SelectScratch ss;
     __shared__ BlockScratch bs;
@@ -470,7 +523,7 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
     for (int i = tid; i < kCap / 32; i += kSelThreads) chosen[i] = 0u;
     if (tid < 4) counter[tid] = 0;   // counter[1] is the equal-key flag of the rank
     BxRow bx{};
-    constexpr bool kBxPre = kCap != kSelCapSmall;
+    constexpr bool kBxPre = kCap == kSelCap;
     if constexpr (kBx) {
         bx.loff = ix.loff + static_cast<int64_t>(bg) * (D.n_list + 1);
         if constexpr (kBxPre) {
@@ -488,21 +541,36 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
         bx.bx_wsel = w.bx_wsel + static_cast<int64_t>(row) * D.max_topk;
     }
 
-    // 1) candidate counts: wave w owns sub-chunks [w * spw, (w + 1) * spw)
-    const bool small_nsub = nsub <= kSelMaxSub;
-    const int spw = small_nsub ? (nsub + kNW - 1) / kNW : 0;
+    // 1) candidate counts: wave w owns sub-chunks [w * spw, (w + 1) * spw), a
+    //    64 of them per step of its lanes. (launch_select sends no row of more
+    //    than kMaxSub sub-chunks here; one would be re-scanned.)
+    constexpr int kCntPer = kMaxSub / kSelThreads;
+    static_assert(kCntPer * kSelThreads == kMaxSub, "sub-chunks per lane");
+    const bool fits_sub = nsub <= kMaxSub;
+    const int spw = fits_sub ? (nsub + kNW - 1) / kNW : 0;
     const int32_t* cnt = w.cand_cnt + static_cast<int64_t>(row) * D.nsub_cap;
-    int c_l = 0, incl = 0;
     int total = 0;
     int n_nz = 0;   // nonempty sub-chunks of the row
-    if (small_nsub) {
-        const int sc = wave * spw + lane;
-        c_l = (lane < spw && sc < nsub) ? cnt[sc] : 0;
-        incl = wave_incl_scan_i32(c_l);
-        const uint64_t nzm = kRunsCopy ? __builtin_amdgcn_ballot_w64(c_l > 0) : 0ull;
+    if (fits_sub) {
+        int c_l[kCntPer], incl[kCntPer];
+        uint64_t nzm[kCntPer];
+#pragma unroll
+        for (int u = 0; u < kCntPer; ++u) {
+            const int in = u * kWave + lane;
+            const int sc = wave * spw + in;
+            c_l[u] = (in < spw && sc < nsub) ? cnt[sc] : 0;
+        }
+        int before = 0, nz_before = 0;   // of the wave's earlier steps
+#pragma unroll
+        for (int u = 0; u < kCntPer; ++u) {
+            incl[u] = wave_incl_scan_i32(c_l[u]) + before;
+            nzm[u] = kRunsCopy ? __builtin_amdgcn_ballot_w64(c_l[u] > 0) : 0ull;
+            if constexpr (kCntPer > 1) before = __builtin_amdgcn_readlane(incl[u], kWave - 1);
+            nz_before += __popcll(nzm[u]);
+        }
         if (lane == kWave - 1) {
-            ss.wave_tot[wave] = incl;
-            ss.wave_aux[wave] = __popcll(nzm);
+            ss.wave_tot[wave] = incl[kCntPer - 1];
+            ss.wave_aux[wave] = nz_before;
         }
         __syncthreads();
         int wbase = 0, nzbase = 0;
@@ -515,28 +583,35 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
             total += t;
             n_nz += z;
         }
-        incl += wbase;   // row-wide inclusive offset of this lane's sub-chunk
-        if constexpr (kRunsCopy) {
-            if (c_l > 0) subl[nzbase + lanes_below(nzm)] = ((incl - c_l) << kNzSubBits) | sc;
-        } else {
-            if (lane < spw && sc < nsub) subl[sc] = incl - c_l;
+#pragma unroll
+        for (int u = 0; u < kCntPer; ++u) {
+            const int in = u * kWave + lane;
+            const int sc = wave * spw + in;
+            const int first = incl[u] + wbase - c_l[u];   // row-wide index of the sub-chunk's first candidate
+            if constexpr (kRunsCopy) {
+                // entries are kept while the indices fit beside the sub-chunk
+                // bits (rows of more candidates take the global-memory path)
+                if (c_l[u] > 0) subl[nzbase + lanes_below(nzm[u])] = (min(first, kCap) << kNzSubBits) | sc;
+                nzbase += __popcll(nzm[u]);
+            } else {
+                if (in < spw && sc < nsub) subl[sc] = first;
+            }
         }
         __syncthreads();
-    } else {
-        int mine = 0;
-        const int per = (nsub + kSelThreads - 1) / kSelThreads;
-        const int sc0 = min(tid * per, nsub), sc1 = min(sc0 + per, nsub);
-        for (int sc = sc0; sc < sc1; ++sc) mine += cnt[sc];
-        block_excl_scan<kSelThreads>(mine, total, ss);
     }
-    const bool fallback = force_fallback || (n_r > 0 && total < (k > 0 ? k : 1));
+    const bool fallback = force_fallback || !fits_sub || (n_r > 0 && total < (k > 0 ? k : 1));
     bx.rescan = fallback;
     float shift = neg_inf;
 
-    if (!fallback && small_nsub && total <= kCap) {
+    if (!fallback && total <= kCap) {
         // ---- fast path: candidates in LDS, position order ----
+        int32_t* words = w.comp_pos + rbase;   // the wide select's candidate words
+        constexpr int kBatch = kWide ? 4 : 1;
         auto KEY = [&](int i) { return lds[i]; };
-        auto CAND = [&](int i) { return lds[kOffCand + i]; };
+        auto CAND = [&](int i) {
+            if constexpr (kWide) return static_cast<uint32_t>(words[i]);
+            else return lds[kOffCand + i];
+        };
         uint32_t kmin = 0xffffffffu, kmax = 0u, kcount = 0u;
         const uint2* cand = w.cand + rbase;
         // Bins fixed in advance from the sampled range [tau_lo, tau_hi] (every
@@ -548,25 +623,26 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
         uint32_t bkmin = fixed ? float_key(tlo) : 0u;
         int bsh = fixed ? bin_shift(bkmin, float_key(thi)) : 0;
         int* fh = fixed ? hist : nullptr;
-        constexpr int kMid = kCap / kSelThreads > 8 ? 8 : kCap / kSelThreads;
+        constexpr int kMid = kWide ? 16 : kCap / kSelThreads > 8 ? 8 : kCap / kSelThreads;
+        constexpr int kLow = kWide ? 8 : 4;
         auto copy = [&](auto tier) {
             constexpr int N = decltype(tier)::value;
             if constexpr (kRunsCopy)
-                copy_candidates_runs<N, kOffCand>(cand, subl, n_nz, total, lds, kmin, kmax, fh, bkmin, bsh);
+                copy_candidates_runs<N, kCap>(cand, subl, n_nz, total, lds, words, kmin, kmax, fh, bkmin, bsh);
             else
                 copy_candidates_search<N, kOffCand>(cand, subl, nsub, total, lds, kmin, kmax, fh, bkmin, bsh);
         };
         if (total > kMid * kSelThreads)
             copy(std::integral_constant<int, kCap / kSelThreads>{});
-        else if (total > 4 * kSelThreads)
+        else if (total > kLow * kSelThreads)
             copy(std::integral_constant<int, kMid>{});
         else if (total > 0)
-            copy(std::integral_constant<int, 4>{});
+            copy(std::integral_constant<int, kLow>{});
         if (!fixed) block_min_max_count<kSelThreads>(kmin, kmax, kcount, bs);
         auto TOK = [&](int i) { return static_cast<int>(CAND(i) & kPosMask); };
         if (k == 0) {
             shift = total > 0 ? key_float(kmax) : neg_inf;
-            emit_selection<kBx, kBxPre>(
+            emit_selection<kBx, kBxPre, kBatch>(
                 KEY, CAND, [](int, uint32_t, uint32_t) { return false; }, total, 0, D.n_list, shift,
                 mass, sel_tok, cand_mass, bx, ss);
         } else {
@@ -598,7 +674,7 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
                                                    counter + 1, chosen, kth, bs);
             if (by_rank) {
                 shift = key_float(kth);   // the k-th largest score
-                emit_selection<kBx, kBxPre>(
+                emit_selection<kBx, kBxPre, kBatch>(
                     KEY, CAND,
                     [&](int i, uint32_t key, uint32_t) {
                         const int bn = static_cast<int>(fixed_bin(key, bkmin, bsh));
@@ -619,7 +695,7 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
                     tok_cut = static_cast<int>(~t.key);
                 }
                 shift = key_float(kk);
-                emit_selection<kBx, kBxPre>(
+                emit_selection<kBx, kBxPre, kBatch>(
                     KEY, CAND,
                     [&](int, uint32_t key, uint32_t cw) {
                         return key > kk || (key == kk && static_cast<int>(cw & kPosMask) <= tok_cut);
@@ -630,19 +706,40 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
     } else {
         // ---- slow path: candidates in global memory (many, or the re-scan) ----
         if (!fallback) {
-            const int per = (nsub + kSelThreads - 1) / kSelThreads;
-            const int sc0 = min(tid * per, nsub), sc1 = min(sc0 + per, nsub);
-            int mine = 0;
-            for (int sc = sc0; sc < sc1; ++sc) mine += cnt[sc];
-            int tot = 0;
-            int o = block_excl_scan<kSelThreads>(mine, tot, ss);
-            for (int sc = sc0; sc < sc1; ++sc) {
-                const int c = cnt[sc];
-                const int64_t src = rbase + static_cast<int64_t>(sc) * kSub;
-                for (int i = 0; i < c; ++i, ++o) {
-                    const uint2 rec = w.cand[src + i];
-                    w.comp_key[rbase + o] = float_key(__uint_as_float(rec.x));
-                    w.comp_pos[rbase + o] = static_cast<int32_t>(rec.y);
+            // the sub-chunks' first indices into the (unused) key area, then a
+            // batch of kSlowBatch candidates per thread and round trip
+            constexpr int kSlowBatch = 8;
+            int* pre = reinterpret_cast<int*>(lds);
+            if constexpr (kRunsCopy) {
+                __syncthreads();   // the nonempty sub-chunks may sit there
+                int at = 0;
+                for (int i = 0; i < wave; ++i) at += ss.wave_tot[i];
+#pragma unroll
+                for (int u = 0; u < kCntPer; ++u) {
+                    const int in = u * kWave + lane;
+                    const int sc = wave * spw + in;
+                    const int c = (in < spw && sc < nsub) ? cnt[sc] : 0;
+                    const int inc = wave_incl_scan_i32(c) + at;
+                    if (in < spw && sc < nsub) pre[sc] = inc - c;
+                    at = __builtin_amdgcn_readlane(inc, kWave - 1);
+                }
+                __syncthreads();
+            } else {
+                pre = subl;   // the offsets of the search copy
+            }
+            const uint2* __restrict__ src = w.cand + rbase;
+            uint32_t* __restrict__ okey = w.comp_key + rbase;
+            int32_t* __restrict__ oword = w.comp_pos + rbase;
+            for (int first = 0; first < total; first += kSlowBatch * kSelThreads) {
+                uint2 rec[kSlowBatch];
+                read_candidates_search<kSlowBatch, kMaxSub>(src, pre, nsub, first, total, rec);
+#pragma unroll
+                for (int u = 0; u < kSlowBatch; ++u) {
+                    const int i = first + u * kSelThreads + tid;
+                    if (i < total) {
+                        okey[i] = float_key(__uint_as_float(rec[u].x));
+                        oword[i] = static_cast<int32_t>(rec[u].y);
+                    }
                 }
             }
         } else {
@@ -660,7 +757,7 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
         auto CAND = [&](int i) { return ccand[i]; };
         if (total == 0) {
             shift = neg_inf;
-            emit_selection<kBx, kBxPre>(KEY, CAND, [](int, uint32_t, uint32_t) { return false; }, 0, 0,
+            emit_selection<kBx, kBxPre, 4>(KEY, CAND, [](int, uint32_t, uint32_t) { return false; }, 0, 0,
                            D.n_list, shift, mass, sel_tok, cand_mass, bx, ss);
         } else {
             const SelectResult r = block_select_desc<kSelThreads>(
@@ -674,7 +771,7 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
                 tok_cut = static_cast<int>(~t.key);
             }
             shift = key_float(r.key);   // k-th largest, or the maximum when k = 0
-            emit_selection<kBx, kBxPre>(
+            emit_selection<kBx, kBxPre, 4>(
                 KEY, CAND,
                 [&](int, uint32_t key, uint32_t cand) {
                     return k > 0 && (key > kth || (key == kth && static_cast<int>(cand & kPosMask) <= tok_cut));
@@ -702,27 +799,69 @@ __global__ __launch_bounds__(kSelThreads) __attribute__((amdgpu_num_sgpr(80))) v
     select_row<kDev, kSelCapSmall, kBx>(D, ba, ix, w, force_fallback);
 }
 
-// The small-capacity select when the rows outnumber the CUs and two of its
-// workgroups fit in one CU's LDS.
-static bool select_small(const Dims& D) {
+template <bool kDev, bool kBx>
+__global__ __launch_bounds__(kSelThreads) void select_wide_kernel(Dims D, BatchArgs ba, Index ix, Work w,
+                                                                  int force_fallback) {
+    select_row<kDev, kSelCapWide, kBx>(D, ba, ix, w, force_fallback);
+}
+
+// Candidates the sampled threshold is likely to leave for a row of n_r tokens
+// and budget k: its rank among the samples (see the prologue) in tokens, and
+// 30% for the sample's spread (over the rows of the 128K workload the counts
+// range over -20% to +15%).
+static int expected_candidates(int n_r, int k) {
+    if (n_r <= 0) return 0;
+    const SampleRuns sr = sample_runs(n_r);
+    const double ns = static_cast<double>(sr.nrun) * sr.run_len;
+    const double c = 2.0 * k * ns / n_r + 8.0;
+    if (c > ns) return n_r;   // no threshold: every token
+    return static_cast<int>(std::min<double>(n_r, 1.3 * c * n_r / ns));
+}
+
+// The capacity of a call's select:
+//  * wide when a row has more sub-chunks or is likely to have more candidates
+//    than the plain one holds: such rows took the global-memory path (one
+//    sequence of 512K tokens, 1%: the call 253 -> 102 us, its select 189 ->
+//    about 40 us);
+//  * small when the rows outnumber the CUs, two of its workgroups fit in one
+//    CU's LDS and the rows' candidates are likely to fit it.
+// Budgets that are device data are unknown here (the context's largest may be
+// far above the step's), so they pick nothing: a row whose candidates don't
+// fit takes the global-memory path.
+static int select_cap(const Dims& D, const BatchArgs& ba, bool dev_args) {
+    int n_max = 0, c_max = 0;
+    for (int b = 0; b < D.B; ++b) {
+        n_max = std::max(n_max, ba.n_r[b]);
+        if (!dev_args) c_max = std::max(c_max, expected_candidates(ba.n_r[b], ba.topk[b]));
+    }
+    if (n_max > kSelMaxSub * kSub || c_max > kSelCap) return kSelCapWide;
     const int n_cu = device_cu_count();
-    constexpr size_t kLdsPerCu = 160 * 1024;
     constexpr size_t kStatic = sizeof(SelectScratch) + sizeof(BlockScratch);
-    return n_cu > 0 && D.B * D.Hq > n_cu &&
-           2 * (SelLayout<kSelCapSmall>::bytes(D.n_list) + kStatic) <= kLdsPerCu;
+    if (n_cu > 0 && D.B * D.Hq > n_cu && c_max <= kSelCapSmall &&
+        2 * (SelLayout<kSelCapSmall>::bytes(D.n_list) + kStatic) <= kLdsPerCu)
+        return kSelCapSmall;
+    return kSelCap;
 }
 
 template <bool kDev, bool kBx>
 static void launch_select_d(const Dims& D, const BatchArgs& ba, const Index& ix, const Work& w,
                             int force_fallback, hipStream_t s, const KTiming& tm) {
-    if (select_small(D))
-        hipExtLaunchKernelGGL((select_small_kernel<kDev, kBx>), dim3(D.B * D.Hq), dim3(kSelThreads),
-                              SelLayout<kSelCapSmall>::bytes(D.n_list), s, tm.start, tm.stop, 0, D, ba,
-                              ix, w, force_fallback);
-    else
-        hipExtLaunchKernelGGL((select_kernel<kDev, kBx>), dim3(D.B * D.Hq), dim3(kSelThreads),
-                              SelLayout<kSelCap>::bytes(D.n_list), s, tm.start, tm.stop, 0, D, ba, ix,
-                              w, force_fallback);
+    const dim3 grid(D.B * D.Hq), block(kSelThreads);
+    switch (select_cap(D, ba, kDev)) {
+        case kSelCapSmall:
+            hipExtLaunchKernelGGL((select_small_kernel<kDev, kBx>), grid, block,
+                                  SelLayout<kSelCapSmall>::bytes(D.n_list), s, tm.start, tm.stop, 0, D, ba,
+                                  ix, w, force_fallback);
+            break;
+        case kSelCapWide:
+            hipExtLaunchKernelGGL((select_wide_kernel<kDev, kBx>), grid, block,
+                                  SelLayout<kSelCapWide>::bytes(D.n_list), s, tm.start, tm.stop, 0, D, ba,
+                                  ix, w, force_fallback);
+            break;
+        default:
+            hipExtLaunchKernelGGL((select_kernel<kDev, kBx>), grid, block, SelLayout<kSelCap>::bytes(D.n_list),
+                                  s, tm.start, tm.stop, 0, D, ba, ix, w, force_fallback);
+    }
 }
 
 hipError_t launch_select(const Dims& D, const BatchArgs& ba, const Index& ix, const Work& w,
@@ -738,21 +877,25 @@ hipError_t launch_select(const Dims& D, const BatchArgs& ba, const Index& ix, co
     return hipGetLastError();
 }
 
+template <bool kDev, bool kBx>
+static hipError_t configure_select_d() {
+    const struct { const void* kernel; size_t bytes; } k[] = {
+        {reinterpret_cast<const void*>(&select_kernel<kDev, kBx>), SelLayout<kSelCap>::bytes(kMaxLists)},
+        {reinterpret_cast<const void*>(&select_small_kernel<kDev, kBx>), SelLayout<kSelCapSmall>::bytes(kMaxLists)},
+        {reinterpret_cast<const void*>(&select_wide_kernel<kDev, kBx>), SelLayout<kSelCapWide>::bytes(kMaxLists)}};
+    for (const auto& e : k) {
+        const hipError_t r = hipFuncSetAttribute(e.kernel, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                                 static_cast<int>(e.bytes));
+        if (r != hipSuccess) return r;
+    }
+    return hipSuccess;
+}
+
 hipError_t configure_select() {
-    const void* k[] = {reinterpret_cast<const void*>(&select_kernel<false, false>),
-                       reinterpret_cast<const void*>(&select_kernel<true, false>),
-                       reinterpret_cast<const void*>(&select_kernel<false, true>),
-                       reinterpret_cast<const void*>(&select_kernel<true, true>),
-                       reinterpret_cast<const void*>(&select_small_kernel<false, false>),
-                       reinterpret_cast<const void*>(&select_small_kernel<true, false>),
-                       reinterpret_cast<const void*>(&select_small_kernel<false, true>),
-                       reinterpret_cast<const void*>(&select_small_kernel<true, true>)};
-    const int big = static_cast<int>(SelLayout<kSelCap>::bytes(kMaxLists));
-    const int small = static_cast<int>(SelLayout<kSelCapSmall>::bytes(kMaxLists));
-    const int bytes[] = {big, big, big, big, small, small, small, small};
-    hipError_t e = hipSuccess;
-    for (int i = 0; i < 8 && e == hipSuccess; ++i)
-        e = hipFuncSetAttribute(k[i], hipFuncAttributeMaxDynamicSharedMemorySize, bytes[i]);
+    hipError_t e = configure_select_d<false, false>();
+    if (e == hipSuccess) e = configure_select_d<true, false>();
+    if (e == hipSuccess) e = configure_select_d<false, true>();
+    if (e == hipSuccess) e = configure_select_d<true, true>();
     return e;
 }
 
