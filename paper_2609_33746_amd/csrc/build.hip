@@ -359,6 +359,22 @@ __global__ __launch_bounds__(kGroupThreads) void reseed_kernel(Dims D, BatchInts
     }
 }
 
+// ||k|| of the token row at p, over 16 lanes of 8 dimensions each: the same
+// sum, in the same order, wherever the build takes a norm. x receives the
+// lane's slice of the row.
+template <typename T>
+__device__ __forceinline__ float row_norm(const T* p, float (&x)[8]) {
+    Load8<T>::run(p, x);
+    float ss = 0.0f;
+#pragma unroll
+    for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
+    return sqrtf(ss);
+}
+
+// The starting coarse centers are taken before any assignment pass has
+// written the norms, so kind 0 takes the norm of its token itself.
 template <typename T>
 __global__ __launch_bounds__(kHeadDim) void init_centers_kernel(Dims D, int kind, KV kv,
                                                                 const int32_t* init,
@@ -370,8 +386,20 @@ __global__ __launch_bounds__(kHeadDim) void init_centers_kernel(Dims D, int kind
     const int p = blockIdx.y;
     const Problem pr = problem_of(D, kind, p);
     const int x = threadIdx.x;
-    if (c >= pr.nkeys || x >= pr.dims) return;
+    if (c >= pr.nkeys) return;
     const int t = init[static_cast<int64_t>(p) * pr.nkeys + c];
+    if (kind == 0) {
+        if (x >= 16) return;
+        const T* row = static_cast<const T*>(kv.k) + (pr.bg / D.Hkv) * kv.sb + (pr.bg % D.Hkv) * kv.sh +
+                       static_cast<int64_t>(t) * kv.sn;
+        float k[8];
+        const float r = row_norm<T>(row + x * 8, k);
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            out[center_index(D, kind, pr, c, x * 8 + e)] = r > 0.0f ? k[e] / r : 0.0f;
+        return;
+    }
+    if (x >= pr.dims) return;
     out[center_index(D, kind, pr, c, x)] =
         token_elem<T>(D, kind, kv, pr.bg, pr.m, pr.dims, t, x, ids_tm, norms_tm, centroids);
 }
@@ -492,6 +520,7 @@ template <typename T>
 __global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts lo, BatchInts hi, KV kv,
                                                              const float* __restrict__ centroids,
                                                              int32_t* __restrict__ ids_tm,
+                                                             float* __restrict__ norms_tm,
                                                              float* __restrict__ dist_c) {
     __shared__ float4 rows4[kAsgTok * kAsgLd / 4];   // token rows, then center chunks
     __shared__ float cn[kAsgCen];                    // ||c||^2 of the chunk's centers
@@ -529,6 +558,7 @@ __global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts l
 #pragma unroll
         for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
         const float r = sqrtf(ss);
+        if (tid % 16 == 0 && tk < nt) norms_tm[static_cast<int64_t>(bg) * D.rcap + t_base + tk] = r;
         float uu = 0.0f;
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
@@ -800,16 +830,16 @@ hipError_t launch_subspace(const Dims& D, const BatchInts& lo, const BatchInts& 
 }
 
 hipError_t launch_assign(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
-                         const KV& kv, const float* centroids, int32_t* ids_tm, float* dist_c,
-                         hipStream_t s) {
+                         const KV& kv, const float* centroids, int32_t* ids_tm, float* norms_tm,
+                         float* dist_c, hipStream_t s) {
     if (max_n <= 0) return hipSuccess;
     const dim3 grid((max_n + kAsgTok - 1) / kAsgTok, D.Hkv, D.B);
     if (kv.bf16)
         hipLaunchKernelGGL(assign_kernel<bf16_t>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv,
-                           centroids, ids_tm, dist_c);
+                           centroids, ids_tm, norms_tm, dist_c);
     else
         hipLaunchKernelGGL(assign_kernel<float>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv,
-                           centroids, ids_tm, dist_c);
+                           centroids, ids_tm, norms_tm, dist_c);
     return hipGetLastError();
 }
 

@@ -275,10 +275,11 @@ hipError_t static_scratch(void** ptr);
 // mean over R_b of variant C
 hipError_t launch_glob_mean(const Dims& D, const Index& ix, float* glob, hipStream_t s);
 // The coarse assignment of the build on the matrix cores: the nearest center
-// of every token of R_b (ids_tm) and its squared distance (dist_c, or null).
+// of every token of R_b (ids_tm), its norm, and its squared distance (dist_c,
+// or null).
 hipError_t launch_assign(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
-                         const KV& kv, const float* centroids, int32_t* ids_tm, float* dist_c,
-                         hipStream_t s);
+                         const KV& kv, const float* centroids, int32_t* ids_tm, float* norms_tm,
+                         float* dist_c, hipStream_t s);
 // The codeword search of the build on the matrix cores, for tokens whose
 // lists are in ids_tm: norms, codes and the chosen distances (dist_f or null).
 hipError_t launch_subspace(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
