@@ -574,7 +574,9 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
         const size_t n_hist = std::max<size_t>(1, nseg * std::max(BG * L, BG * M * Kc));
         if (e == hipSuccess) e = hipMalloc(&bb.seg_hist, n_hist * 4);
     }
+    if (e == hipSuccess) e = hipMalloc(&bb.split, split_center_bytes(D));
     auto release = [&]() {
+        hipFree(bb.split);
         hipFree(bb.order);
         hipFree(bb.offs);
         hipFree(bb.dist_c);
@@ -594,7 +596,7 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
     // without them a build took 16.6 ms in place of 22.3).
     auto assign = [&](float* dist) {
         if (e == hipSuccess)
-            e = launch_assign(D, lo, hi, max_n, kv, C, c->ids_tm, c->norms_tm, dist, stream);
+            e = launch_assign(D, lo, hi, max_n, kv, C, bb.split, c->ids_tm, c->norms_tm, dist, stream);
     };
     auto encode = [&](float* dist) {
         if (e == hipSuccess)

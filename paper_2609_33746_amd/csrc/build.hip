@@ -17,6 +17,8 @@
 //    to the smaller token id; one point per empty center, in center order).
 //  * init_centers_kernel: the starting centers, the direction or residual
 //    slice of caller-drawn tokens.
+#include <type_traits>
+
 #include "device_common.h"
 #include "pqhsa_internal.h"
 
@@ -487,176 +489,323 @@ hipError_t launch_init_centers(const Dims& D, int kind, const KV& kv, const int3
 }
 
 // ---------------------------------------------------------------------------
-// assign_kernel: the coarse assignment of the build on the matrix cores.
-// ||u - c||^2 = ||u||^2 + ||c||^2 - 2 u . c, and the dot products of a tile
-// of tokens with a chunk of centers are one fp32 matrix product: 128 tokens
-// per workgroup (4 waves x 2 tiles of 16), centers in chunks of 64 (4 tiles
-// of 16), K = 128 dimensions as 32 steps of v_mfma_f32_16x16x4f32. In step
-// j, lane group q (lane / 16) contributes dimension 32 q + j, so each lane
-// reads 32 contiguous floats of its row; rows are 132 floats apart in LDS,
-// which puts the 16 rows of a read on distinct 16-byte bank groups. Every
-// lane keeps a running (distance, center) minimum for the 2 token columns
-// it holds, over the 4 centers of each tile it sees; the 4 lane groups are
-// folded at the end, ties going to the smaller center id. The directions,
-// norms and distances are fp32; the distance of the chosen center is
-// written for the re-seeding.
+// The searches of the build run on the bf16 matrix cores at the precision of
+// 32-bit sums. A 32-bit x is the sum of three bf16 parts x1 + x2 + x3 (each
+// part the rounding of what the earlier ones leave, 8 bits apiece), products
+// of bf16 parts are exact in the matrix cores' 32-bit sums, and parts are
+// added smallest first. Against float64 over random unit vectors of 128
+// dimensions the dot products of a bf16 key with a split center are off by
+// 6.2e-9 (rms; 7.0e-8 at most), those of v_mfma_f32_16x16x4f32 on the 32-bit
+// direction by 1.8e-8 (1.7e-7).
+// ---------------------------------------------------------------------------
+typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef float f16_t __attribute__((ext_vector_type(16)));
+
+// The bf16 parts of x, largest first.
+__device__ __forceinline__ void split_bf16(float x, __bf16 (&p)[3]) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i) {
+        p[i] = static_cast<__bf16>(x);
+        x -= static_cast<float>(p[i]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// split_centers_kernel: the centers of each (b, kv head) as the A operands of
+// assign_kernel, tiles of kTileCen centers in operand order: kSplitBlocks
+// blocks of 64 lanes x 8 bf16, lane l of a block holding 8 consecutive
+// dimensions (from 8 (l / 32)) of 16 of center l mod 32. Blocks 0-7 hold the
+// third parts of dimensions 0-15, 16-31, ..., blocks 8-15 the second parts,
+// 16-23 the first, and block 24 the parts of ||c||^2 / 2 in the slots that
+// meet a token's norm parts (norm_slots below). Centers past the last stand
+// farther than any real one.
+// ---------------------------------------------------------------------------
+constexpr int kTileCen = 32;
+constexpr int kDimBlocks = kHeadDim / 16;             // 16-dimension blocks of a row: 8
+constexpr int kSplitBlocks = 3 * kDimBlocks + 1;
+constexpr int kTileBf16 = kSplitBlocks * kWave * 8;   // bf16 per tile: 25 KB
+constexpr float kFarCenter = 1e15f;
+
+static size_t split_center_count(const Dims& D) {
+    const size_t tiles = (static_cast<size_t>(D.n_list) + kTileCen - 1) / kTileCen;
+    return static_cast<size_t>(D.B) * D.Hkv * tiles * kTileBf16;
+}
+size_t split_center_bytes(const Dims& D) { return split_center_count(D) * sizeof(__bf16); }
+
+// one workgroup per (tile, b g): 8 threads per center, 16 dimensions each
+__global__ __launch_bounds__(kTileCen * 8) void split_centers_kernel(Dims D, const float* __restrict__ centroids,
+                                                                     __bf16* __restrict__ split) {
+    const int tile = blockIdx.x, n_tile = gridDim.x, bg = blockIdx.y;
+    const int row = threadIdx.x / 8, kb = threadIdx.x % 8;
+    const int c = tile * kTileCen + row;
+    const bool real = c < D.n_list;
+    const float* src = centroids + (static_cast<int64_t>(bg) * D.n_list + (real ? c : 0)) * kHeadDim + kb * 16;
+    __bf16* out = split + (static_cast<int64_t>(bg) * n_tile + tile) * kTileBf16;
+    double c2 = 0.0;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        float x[8];
+        Load8<float>::run(src + half * 8, x);
+        bf8_t v[3];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            if (!real) x[e] = 0.0f;
+            c2 += static_cast<double>(x[e]) * x[e];
+            __bf16 p[3];
+            split_bf16(x[e], p);
+#pragma unroll
+            for (int i = 0; i < 3; ++i) v[i][e] = p[i];
+        }
+#pragma unroll
+        for (int i = 0; i < 3; ++i)
+            *reinterpret_cast<bf8_t*>(out + (((2 - i) * kDimBlocks + kb) * kWave + half * 32 + row) * 8) = v[i];
+    }
+#pragma unroll
+    for (int off = 1; off < 8; off <<= 1) c2 += __shfl_xor(c2, off);
+    if (kb < 2) {
+        __bf16 p[3];
+        split_bf16(real ? static_cast<float>(0.5 * c2) : kFarCenter, p);
+        bf8_t v = {};
+        if (kb == 0) {   // against norm_slots: -(r3, r1, r2, r1, r2, r1, 0, 0)
+            v[0] = p[0]; v[1] = p[2]; v[2] = p[1]; v[3] = p[1]; v[4] = p[0]; v[5] = p[0];
+        }
+        *reinterpret_cast<bf8_t*>(out + (3 * kDimBlocks * kWave + kb * 32 + row) * 8) = v;
+    }
+}
+
+// The B operand that meets the ||c||^2 / 2 parts: minus the parts of r, paired
+// so that the block adds -r ||c||^2 / 2 to 24 bits (lanes of the second 8 hold
+// zeros).
+__device__ __forceinline__ bf8_t norm_slots(float r, int half) {
+    bf8_t v = {};
+    if (half == 0) {
+        __bf16 p[3];
+        split_bf16(-r, p);
+        v[0] = p[2]; v[1] = p[0]; v[2] = p[1]; v[3] = p[0]; v[4] = p[1]; v[5] = p[0];
+    }
+    return v;
+}
+
+// ---------------------------------------------------------------------------
+// assign_kernel: the nearest center of every direction u = k / r, r = ||k||.
+// Its distance is ||u||^2 - 2 (u . c - ||c||^2 / 2), so per token the largest
+// r (u . c - ||c||^2 / 2) = k . c - r ||c||^2 / 2 decides: one product of the
+// key, which in a bf16 cache is its own only part, with the center's parts,
+// and a last 16-wide block that subtracts the center's half norm. So the
+// accumulator is compared as it is: 3 VALU instructions per (token, center),
+// which the next products hide. A 32-bit cache takes u itself, in three parts
+// (6 products of parts; those left out are below 2^-24 of the terms).
+//
+// A workgroup of 4 waves holds 64 tokens (32 with a 32-bit cache) a wave as B
+// operands in registers and streams the split centers through LDS, a tile of
+// 32 (25 KB) at a time, the next tile's loads under the current one's
+// products. v_mfma_f32_32x32x16_bf16: element i of lane l is center
+// 8 (i / 4) + 4 (l / 32) + i mod 4 against token l mod 32. 128K tokens x 8 KV
+// heads against 1024 lists: 0.71 ms (1.2 PFLOP/s of bf16 products, about what
+// a large library product reaches here) in place of 3.19 ms with
+// v_mfma_f32_16x16x4f32 and a distance and a two-key compare per pair.
 // ---------------------------------------------------------------------------
 constexpr int kAsgThreads = 256;
-constexpr int kAsgTok = 128;                  // tokens per workgroup
-constexpr int kAsgCen = 64;                   // centers per chunk
-constexpr int kAsgLd = kHeadDim + 4;          // LDS row stride (floats)
-static_assert(kAsgTok * kAsgLd >= 2 * kAsgCen * kAsgLd, "the token rows hold a center chunk");
+constexpr int kAsgWaves = kAsgThreads / kWave;
 
-typedef float asg_v4f __attribute__((ext_vector_type(4)));
+template <typename T>
+struct AsgTokens;
+template <>
+struct AsgTokens<bf16_t> {
+    static constexpr int kTiles = 2, kParts = 1;   // token tiles of 32 per wave, bf16 parts per element
+};
+template <>
+struct AsgTokens<float> {
+    static constexpr int kTiles = 1, kParts = 3;
+};
 
 __device__ __forceinline__ void asg_fold(float& d, int& i, float od, int oi) {
-    if (od < d || (od == d && oi < i)) {
+    if (od > d || (od == d && oi < i)) {
         d = od;
         i = oi;
     }
 }
 
+// The operands of a token's row: lane half h holds dimensions 16 kb + 8 h ..
+// + 7 of every block kb. Returns ||k|| (the sum in row_norm's order), in
+// `scale` what the row stands multiplied by (r for the raw key, 1 for the
+// direction), and in `unit2` ||u||^2. A zero row, or one whose norm
+// overflows, is the zero direction; a row with a NaN or an infinity is
+// nearest to nothing and takes center 0 at distance 0.
 template <typename T>
-__global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts lo, BatchInts hi, KV kv,
-                                                             const float* __restrict__ centroids,
-                                                             int32_t* __restrict__ ids_tm,
-                                                             float* __restrict__ norms_tm,
-                                                             float* __restrict__ dist_c) {
-    __shared__ float4 rows4[kAsgTok * kAsgLd / 4];   // token rows, then center chunks
-    __shared__ float cn[kAsgCen];                    // ||c||^2 of the chunk's centers
-    __shared__ float un[kAsgTok];                    // ||u||^2 of the tokens
-    float* rows = reinterpret_cast<float*>(rows4);
-    const int b = blockIdx.z;
-    const int g = blockIdx.y;
-    const int t_base = lo.v[b] + static_cast<int>(blockIdx.x) * kAsgTok;
-    if (t_base >= hi.v[b]) return;
-    const int nt = min(kAsgTok, hi.v[b] - t_base);
-    const int bg = b * D.Hkv + g;
-    const int tid = threadIdx.x;
-    const int wave = tid / kWave;
-    const int lane = lane_id();
-    const int col = lane % 16;   // the lane's token column (B) / center row (A) in a tile
-    const int q = lane / 16;     // its lane group: dimensions 32 q .. 32 q + 31
-
-    // 1) the directions u = k / ||k|| of the workgroup's tokens into LDS:
-    //    16 threads per token, 8 dimensions each
-    const T* kb = static_cast<const T*>(kv.k) + b * kv.sb + g * kv.sh;
+__device__ __forceinline__ float load_token(const T* p, bool present, int half,
+                                            bf8_t (&v)[AsgTokens<T>::kParts][kDimBlocks], float& scale,
+                                            float& unit2) {
+    float ps[kDimBlocks];
+    float x[std::is_same<T, float>::value ? kDimBlocks : 1][8];
+    bool bad = false;
 #pragma unroll
-    for (int it = 0; it < kAsgTok / 16; ++it) {
-        const int tk = it * 16 + tid / 16;
-        const int x0 = (tid % 16) * 8;
-        float x[8];
-        if (tk < nt) {
-            Load8<T>::run(kb + static_cast<int64_t>(t_base + tk) * kv.sn + x0, x);
+    for (int kb = 0; kb < kDimBlocks; ++kb) {
+        float e8[8] = {};
+        if constexpr (std::is_same<T, float>::value) {
+            if (present) Load8<float>::run(p + kb * 16 + half * 8, x[kb]);
+            else
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[kb][e] = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) e8[e] = x[kb][e];
         } else {
+            uint4 w = make_uint4(0u, 0u, 0u, 0u);
+            if (present) w = *reinterpret_cast<const uint4*>(p + kb * 16 + half * 8);
+            v[0][kb] = __builtin_bit_cast(bf8_t, w);
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+            for (int e = 0; e < 8; ++e) e8[e] = static_cast<float>(v[0][kb][e]);
         }
         float ss = 0.0f;
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
-        const float r = sqrtf(ss);
-        if (tid % 16 == 0 && tk < nt) norms_tm[static_cast<int64_t>(bg) * D.rcap + t_base + tk] = r;
-        float uu = 0.0f;
-#pragma unroll
         for (int e = 0; e < 8; ++e) {
-            x[e] = r > 0.0f ? x[e] / r : 0.0f;
-            uu = fmaf(x[e], x[e], uu);
+            ss = fmaf(e8[e], e8[e], ss);
+            bad = bad || !(fabsf(e8[e]) < __builtin_huge_valf());
         }
-#pragma unroll
-        for (int off = 1; off < 16; off <<= 1) uu += __shfl_xor(uu, off);
-        if (tid % 16 == 0) un[tk] = uu;
-        float4* dst = reinterpret_cast<float4*>(rows + tk * kAsgLd + x0);
-        dst[0] = make_float4(x[0], x[1], x[2], x[3]);
-        dst[1] = make_float4(x[4], x[5], x[6], x[7]);
+        ps[kb] = ss + __shfl_xor(ss, 32);
     }
-    __syncthreads();
-    // 2) the B operands: token rows (2 tiles of the wave), 32 dimensions each
-    float bv[2][32];
+    const float ss = ((ps[0] + ps[1]) + (ps[2] + ps[3])) + ((ps[4] + ps[5]) + (ps[6] + ps[7]));
+    const float r = sqrtf(ss);
+    bad = __shfl_xor(static_cast<int>(bad), 32) || bad;
+    const bool live = !bad && r > 0.0f && r < __builtin_huge_valf();
+    scale = bad ? 0.0f : live && !std::is_same<T, float>::value ? r : 1.0f;
+    unit2 = live ? ss / (r * r) : 0.0f;
+    if constexpr (std::is_same<T, float>::value) {
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-        const float4* src = reinterpret_cast<const float4*>(rows + (wave * 32 + tt * 16 + col) * kAsgLd + 32 * q);
+        for (int kb = 0; kb < kDimBlocks; ++kb)
 #pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const float4 f = src[v];
-            bv[tt][4 * v] = f.x; bv[tt][4 * v + 1] = f.y; bv[tt][4 * v + 2] = f.z; bv[tt][4 * v + 3] = f.w;
-        }
-    }
-    float best_d[2] = {__builtin_huge_valf(), __builtin_huge_valf()};
-    int best_i[2] = {0, 0};   // a valid id even if every distance is NaN
-
-    // 3) the centers, a chunk of 64 at a time
-    const float* cen = centroids + static_cast<int64_t>(bg) * D.n_list * kHeadDim;
-    for (int c0 = 0; c0 < D.n_list; c0 += kAsgCen) {
-        __syncthreads();   // the previous chunk (or the token rows) is no longer read
+            for (int e = 0; e < 8; ++e) {
+                __bf16 q[3];
+                split_bf16(live ? x[kb][e] / r : 0.0f, q);
 #pragma unroll
-        for (int it = 0; it < kAsgCen * kHeadDim / 4 / kAsgThreads; ++it) {
-            const int idx = it * kAsgThreads + tid;
-            const int ci = idx / 32;          // 32 float4 per center row
-            const int p = idx % 32;
-            const bool ok = c0 + ci < D.n_list;
-            const float4 v = ok ? reinterpret_cast<const float4*>(cen + static_cast<int64_t>(c0 + ci) * kHeadDim)[p]
-                                : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-            float ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
-#pragma unroll
-            for (int off = 1; off < 32; off <<= 1) ss += __shfl_xor(ss, off);
-            if (p == 0) cn[ci] = ss;
-            reinterpret_cast<float4*>(rows + ci * kAsgLd)[p] = v;
-        }
-        __syncthreads();
-        // dot products: 4 center tiles x 2 token tiles, 8 independent chains
-        asg_v4f acc[4][2];
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-            for (int tt = 0; tt < 2; ++tt) acc[ct][tt] = asg_v4f{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-        for (int j4 = 0; j4 < 8; ++j4) {
-            float4 av[4];
-#pragma unroll
-            for (int ct = 0; ct < 4; ++ct)
-                av[ct] = reinterpret_cast<const float4*>(rows + (ct * 16 + col) * kAsgLd + 32 * q)[j4];
-#pragma unroll
-            for (int jj = 0; jj < 4; ++jj)
-#pragma unroll
-                for (int ct = 0; ct < 4; ++ct) {
-                    const float a = jj == 0 ? av[ct].x : jj == 1 ? av[ct].y : jj == 2 ? av[ct].z : av[ct].w;
-#pragma unroll
-                    for (int tt = 0; tt < 2; ++tt)
-                        acc[ct][tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[tt][4 * j4 + jj],
-                                                                        acc[ct][tt], 0, 0, 0);
-                }
-        }
-        // distances up to ||u||^2: row 4 q + i of tile ct is center c0 + 16 ct + 4 q + i
-#pragma unroll
-        for (int ct = 0; ct < 4; ++ct)
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const int cl = ct * 16 + 4 * q + i;
-                if (c0 + cl < D.n_list) {
-                    const float c2 = cn[cl];
-#pragma unroll
-                    for (int tt = 0; tt < 2; ++tt)
-                        asg_fold(best_d[tt], best_i[tt], fmaf(-2.0f, acc[ct][tt][i], c2), c0 + cl);
-                }
+                for (int i = 0; i < 3; ++i) v[i][kb][e] = q[i];
             }
+    } else if (!live) {
+#pragma unroll
+        for (int kb = 0; kb < kDimBlocks; ++kb) v[0][kb] = bf8_t{};
     }
-    // 4) the 4 lane groups of a token column, then the outputs
+    return r;
+}
+
+template <typename T>
+__global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts lo, BatchInts hi, KV kv,
+                                                             const __bf16* __restrict__ split, int n_tile,
+                                                             int32_t* __restrict__ ids_tm,
+                                                             float* __restrict__ norms_tm,
+                                                             float* __restrict__ dist_c) {
+    constexpr int NT = AsgTokens<T>::kTiles, P = AsgTokens<T>::kParts;
+    constexpr int kWgTok = kAsgWaves * NT * 32;
+    __shared__ bf8_t cen[2][kSplitBlocks * kWave];
+    const int b = blockIdx.z;
+    const int g = blockIdx.y;
+    const int t_base = lo.v[b] + static_cast<int>(blockIdx.x) * kWgTok;
+    if (t_base >= hi.v[b]) return;
+    const int nt = min(kWgTok, hi.v[b] - t_base);
+    const int bg = b * D.Hkv + g;
+    const int wave = threadIdx.x / kWave;
+    const int lane = lane_id();
+    const int col = lane % 32;
+    const int half = lane / 32;
+
+    // the tiles' staging: block wave, wave + 4, ... of a tile by each wave
+    constexpr int kStage = (kSplitBlocks + kAsgWaves - 1) / kAsgWaves;
+    const bf8_t* src = reinterpret_cast<const bf8_t*>(split) + static_cast<int64_t>(bg) * n_tile * kSplitBlocks * kWave;
+    bf8_t st[kStage];
+    auto fetch = [&](int tile) {
 #pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-#pragma unroll
-        for (int off = 16; off < kWave; off <<= 1) {
-            const float od = __shfl_xor(best_d[tt], off);
-            const int oi = __shfl_xor(best_i[tt], off);
-            asg_fold(best_d[tt], best_i[tt], od, oi);
+        for (int i = 0; i < kStage; ++i) {
+            const int blk = min(i * kAsgWaves + wave, kSplitBlocks - 1);
+            st[i] = src[(static_cast<int64_t>(tile) * kSplitBlocks + blk) * kWave + lane];
         }
-        const int tk = wave * 32 + tt * 16 + col;
-        if (q == 0 && tk < nt) {
+    };
+    auto put = [&](int buf) {
+#pragma unroll
+        for (int i = 0; i < kStage; ++i)
+            if (i * kAsgWaves + wave < kSplitBlocks) cen[buf][(i * kAsgWaves + wave) * kWave + lane] = st[i];
+    };
+    fetch(0);
+
+    bf8_t tok[NT][P][kDimBlocks], nrm[NT];
+    float unit2[NT], scale[NT];
+    const T* kb = static_cast<const T*>(kv.k) + b * kv.sb + g * kv.sh;
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+        const int tk = (wave * NT + tt) * 32 + col;
+        const float r = load_token<T>(kb + static_cast<int64_t>(t_base + tk) * kv.sn, tk < nt, half, tok[tt],
+                                      scale[tt], unit2[tt]);
+        nrm[tt] = norm_slots(scale[tt], half);
+        if (half == 0 && tk < nt) norms_tm[static_cast<int64_t>(bg) * D.rcap + t_base + tk] = r;
+    }
+    float best[NT];
+    int best_i[NT];
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+        best[tt] = -__builtin_huge_valf();
+        best_i[tt] = 0;   // a valid id whatever the values
+    }
+    put(0);
+    __syncthreads();
+    for (int tile = 0; tile < n_tile; ++tile) {
+        if (tile + 1 < n_tile) fetch(tile + 1);
+        const bf8_t* a = cen[tile & 1] + lane;
+        f16_t acc[NT];
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) acc[tt] = f16_t{};
+        // products of parts, smallest first: (center part, token part) with
+        // the block of a center part p at (2 - p) kDimBlocks
+        auto block = [&](int cp, int tp, int kd) {
+            const bf8_t av = a[((2 - cp) * kDimBlocks + kd) * kWave];
+#pragma unroll
+            for (int tt = 0; tt < NT; ++tt)
+                acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, tok[tt][tp][kd], acc[tt], 0, 0, 0);
+        };
+#pragma unroll
+        for (int kd = 0; kd < kDimBlocks; ++kd) block(2, 0, kd);
+        if constexpr (P == 3) {
+#pragma unroll
+            for (int kd = 0; kd < kDimBlocks; ++kd) block(1, 1, kd);
+#pragma unroll
+            for (int kd = 0; kd < kDimBlocks; ++kd) block(0, 2, kd);
+        }
+#pragma unroll
+        for (int kd = 0; kd < kDimBlocks; ++kd) block(1, 0, kd);
+        if constexpr (P == 3) {
+#pragma unroll
+            for (int kd = 0; kd < kDimBlocks; ++kd) block(0, 1, kd);
+        }
+#pragma unroll
+        for (int kd = 0; kd < kDimBlocks; ++kd) block(0, 0, kd);
+        const bf8_t av = a[3 * kDimBlocks * kWave];
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt)
+            acc[tt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(av, nrm[tt], acc[tt], 0, 0, 0);
+#pragma unroll
+        for (int tt = 0; tt < NT; ++tt) {
+            // the lane's rows are in increasing center order: the first of
+            // equal values stays (and a NaN, of a center that is one, never wins)
+            float m = -__builtin_huge_valf();
+            int mi = 0;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                mi = acc[tt][i] > m ? i : mi;
+                m = fmaxf(m, acc[tt][i]);
+            }
+            if (m > best[tt]) {
+                best[tt] = m;
+                best_i[tt] = tile * kTileCen + 8 * (mi / 4) + 4 * half + mi % 4;
+            }
+        }
+        if (tile + 1 < n_tile) put((tile + 1) & 1);   // its last readers passed the barrier below
+        __syncthreads();
+    }
+#pragma unroll
+    for (int tt = 0; tt < NT; ++tt) {
+        asg_fold(best[tt], best_i[tt], __shfl_xor(best[tt], 32), __shfl_xor(best_i[tt], 32));
+        const int tk = (wave * NT + tt) * 32 + col;
+        if (half == 0 && tk < nt) {
             const int64_t at = static_cast<int64_t>(bg) * D.rcap + t_base + tk;
-            ids_tm[at] = best_i[tt];
-            if (dist_c) dist_c[at] = fmaxf(best_d[tt] + un[tk], 0.0f);
+            ids_tm[at] = min(best_i[tt], D.n_list - 1);
+            if (dist_c) dist_c[at] = scale[tt] > 0.0f ? fmaxf(unit2[tt] - 2.0f * best[tt] / scale[tt], 0.0f) : 0.0f;
         }
     }
 }
@@ -671,6 +820,17 @@ __global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts l
 // and the chosen squared distances (dist_f, or null); ties go to the smaller
 // codeword.
 // ---------------------------------------------------------------------------
+constexpr int kAsgTok = 128;                  // tokens per workgroup
+constexpr int kAsgLd = kHeadDim + 4;          // LDS row stride (floats)
+typedef float asg_v4f __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ void sub_fold(float& d, int& i, float od, int oi) {
+    if (od < d || (od == d && oi < i)) {
+        d = od;
+        i = oi;
+    }
+}
+
 template <typename PQ>
 constexpr int kSubRound = PQ::K >= 256 ? 4 : PQ::M;   // subspaces per LDS round
 template <typename PQ>
@@ -786,7 +946,7 @@ __global__ __launch_bounds__(kAsgThreads) void subspace_kernel(
                     const int zl = ct * 16 + 4 * q + i;   // codeword of row 4 q + i
                     const float p2 = pn[mm * K + zl];
 #pragma unroll
-                    for (int tt = 0; tt < 2; ++tt) asg_fold(best_d[tt], best_z[tt], fmaf(-2.0f, acc[tt][i], p2), zl);
+                    for (int tt = 0; tt < 2; ++tt) sub_fold(best_d[tt], best_z[tt], fmaf(-2.0f, acc[tt][i], p2), zl);
                 }
             }
 #pragma unroll
@@ -799,7 +959,7 @@ __global__ __launch_bounds__(kAsgThreads) void subspace_kernel(
                     r2 += __shfl_xor(r2, off);
                     const float od = __shfl_xor(best_d[tt], off);
                     const int oz = __shfl_xor(best_z[tt], off);
-                    asg_fold(best_d[tt], best_z[tt], od, oz);
+                    sub_fold(best_d[tt], best_z[tt], od, oz);
                 }
                 const int tk = wave * 32 + tt * 16 + col;
                 if (q == 0 && tk < nt) {
@@ -830,16 +990,23 @@ hipError_t launch_subspace(const Dims& D, const BatchInts& lo, const BatchInts& 
 }
 
 hipError_t launch_assign(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
-                         const KV& kv, const float* centroids, int32_t* ids_tm, float* norms_tm,
-                         float* dist_c, hipStream_t s) {
+                         const KV& kv, const float* centroids, void* split, int32_t* ids_tm,
+                         float* norms_tm, float* dist_c, hipStream_t s) {
     if (max_n <= 0) return hipSuccess;
-    const dim3 grid((max_n + kAsgTok - 1) / kAsgTok, D.Hkv, D.B);
+    const int n_tile = (D.n_list + kTileCen - 1) / kTileCen;
+    __bf16* parts = static_cast<__bf16*>(split);
+    hipLaunchKernelGGL(split_centers_kernel, dim3(n_tile, D.B * D.Hkv), dim3(kTileCen * 8), 0, s, D, centroids,
+                       parts);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int tok = kAsgWaves * 32 * (kv.bf16 ? AsgTokens<bf16_t>::kTiles : AsgTokens<float>::kTiles);
+    const dim3 grid((max_n + tok - 1) / tok, D.Hkv, D.B);
     if (kv.bf16)
-        hipLaunchKernelGGL(assign_kernel<bf16_t>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv,
-                           centroids, ids_tm, norms_tm, dist_c);
+        hipLaunchKernelGGL(assign_kernel<bf16_t>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv, parts, n_tile,
+                           ids_tm, norms_tm, dist_c);
     else
-        hipLaunchKernelGGL(assign_kernel<float>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv,
-                           centroids, ids_tm, norms_tm, dist_c);
+        hipLaunchKernelGGL(assign_kernel<float>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv, parts, n_tile,
+                           ids_tm, norms_tm, dist_c);
     return hipGetLastError();
 }
 

@@ -276,10 +276,11 @@ hipError_t static_scratch(void** ptr);
 hipError_t launch_glob_mean(const Dims& D, const Index& ix, float* glob, hipStream_t s);
 // The coarse assignment of the build on the matrix cores: the nearest center
 // of every token of R_b (ids_tm), its norm, and its squared distance (dist_c,
-// or null).
+// or null). split: split_center_bytes of scratch.
 hipError_t launch_assign(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
-                         const KV& kv, const float* centroids, int32_t* ids_tm, float* norms_tm,
-                         float* dist_c, hipStream_t s);
+                         const KV& kv, const float* centroids, void* split, int32_t* ids_tm,
+                         float* norms_tm, float* dist_c, hipStream_t s);
+size_t split_center_bytes(const Dims& D);
 // The codeword search of the build on the matrix cores, for tokens whose
 // lists are in ids_tm: norms, codes and the chosen distances (dist_f or null).
 hipError_t launch_subspace(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
@@ -299,6 +300,7 @@ struct BuildBufs {
     float* dist_f;       // [B, Hkv, rcap, M]
     int32_t* seg_hist;   // [problems, segments of 4096 tokens, keys] counts, then first positions
                          //   (problems with at most 1024 keys)
+    void* split;         // split_center_bytes
 };
 constexpr int kBuildSegTok = 4096;   // tokens per segment of the build's grouping
 // kind: 0 coarse centers over directions, 1 codewords over residual slices,
