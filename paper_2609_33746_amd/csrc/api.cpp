@@ -561,8 +561,8 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
     }
     c->prepared = false;
     BuildBufs bb{};
-    const size_t n_offs = std::max(BG * (L + 1), BG * M * (Kc + 1));
-    e = hipMalloc(&bb.order, BG * M * rc * 4);
+    const size_t n_offs = BG * (L + 1);
+    e = hipMalloc(&bb.order, BG * rc * 4);
     if (e == hipSuccess) e = hipMalloc(&bb.offs, n_offs * 4);
     if (e == hipSuccess) e = hipMalloc(&bb.dist_c, BG * rc * 4);
     if (e == hipSuccess) e = hipMalloc(&bb.dist_f, BG * rc * M * 4);
@@ -571,11 +571,17 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
         int max_r = 0;
         for (int b = 0; b < D.B; ++b) max_r = std::max(max_r, hi.v[b] - lo.v[b]);
         const size_t nseg = (static_cast<size_t>(max_r) + kBuildSegTok - 1) / kBuildSegTok;
-        const size_t n_hist = std::max<size_t>(1, nseg * std::max(BG * L, BG * M * Kc));
+        const size_t n_hist = std::max<size_t>(1, nseg * BG * L);
         if (e == hipSuccess) e = hipMalloc(&bb.seg_hist, n_hist * 4);
     }
     if (e == hipSuccess) e = hipMalloc(&bb.split, split_center_bytes(D));
+    if (e == hipSuccess) e = hipMalloc(&bb.sums, BG * c->codebook_floats * sizeof(unsigned long long));
+    if (e == hipSuccess) e = hipMalloc(&bb.n_near, BG * sizeof(uint32_t));
+    if (e == hipSuccess) e = hipMalloc(&bb.counts, BG * M * Kc * sizeof(uint32_t));
     auto release = [&]() {
+        hipFree(bb.sums);
+        hipFree(bb.counts);
+        hipFree(bb.n_near);
         hipFree(bb.split);
         hipFree(bb.order);
         hipFree(bb.offs);
@@ -596,31 +602,29 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
     // without them a build took 16.6 ms in place of 22.3).
     auto assign = [&](float* dist) {
         if (e == hipSuccess)
-            e = launch_assign(D, lo, hi, max_n, kv, C, bb.split, c->ids_tm, c->norms_tm, dist, stream);
+            e = launch_assign(D, lo, hi, max_n, kv, C, bb, c->ids_tm, c->norms_tm, dist, stream);
     };
-    auto encode = [&](float* dist) {
+    auto encode = [&](bool train) {
         if (e == hipSuccess)
-            e = launch_subspace(D, lo, hi, max_n, kv, C, P, c->ids_tm, c->codes_tm, c->norms_tm, dist, stream);
+            e = launch_subspace(D, lo, hi, max_n, kv, C, P, c->ids_tm, c->codes_tm, c->norms_tm, bb, train, stream);
     };
     if (e == hipSuccess) e = launch_init_centers(D, 0, kv, init_coarse, c->ids_tm, c->norms_tm, C, C, stream);
     for (int it = 0; it < n_iter_coarse; ++it) {
         assign(bb.dist_c);
-        if (e == hipSuccess) e = launch_group(D, lo, hi, 0, c->ids_tm, c->codes_tm, bb, stream);
-        if (e == hipSuccess) e = launch_centers(D, lo, hi, 0, kv, c->ids_tm, c->norms_tm, C, bb, C, stream);
+        if (e == hipSuccess) e = launch_group(D, lo, hi, c->ids_tm, bb, stream);
+        if (e == hipSuccess) e = launch_centers(D, 0, kv, c->norms_tm, bb, C, stream);
         if (e == hipSuccess) e = launch_reseed(D, lo, hi, 0, kv, c->ids_tm, c->norms_tm, C, bb, C, stream);
     }
     assign(nullptr);   // the final lists
     if (e == hipSuccess) e = launch_init_centers(D, 1, kv, init_pq, c->ids_tm, c->norms_tm, C, P, stream);
     for (int it = 0; it < n_iter_pq; ++it) {
-        encode(bb.dist_f);
-        if (e == hipSuccess) e = launch_group(D, lo, hi, 1, c->ids_tm, c->codes_tm, bb, stream);
-        if (e == hipSuccess) e = launch_centers(D, lo, hi, 1, kv, c->ids_tm, c->norms_tm, C, bb, P, stream);
+        encode(true);
         if (e == hipSuccess) e = launch_reseed(D, lo, hi, 1, kv, c->ids_tm, c->norms_tm, C, bb, P, stream);
     }
-    encode(nullptr);   // the final codes
-    if (e == hipSuccess) e = launch_group(D, lo, hi, 0, c->ids_tm, c->codes_tm, bb, stream);
+    encode(false);   // the final codes
+    if (e == hipSuccess) e = launch_group(D, lo, hi, c->ids_tm, bb, stream);
     if (e == hipSuccess)
-        e = launch_centers(D, lo, hi, 2, kv, c->ids_tm, c->norms_tm, C, bb, c->means, stream);
+        e = launch_centers(D, 2, kv, c->norms_tm, bb, c->means, stream);
     if (e == hipSuccess) e = hipStreamSynchronize(stream);
     release();
     if (e != hipSuccess) return hip_fail(c, e, "building the index");

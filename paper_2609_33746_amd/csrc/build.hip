@@ -2,21 +2,23 @@
 // every (sequence, KV head) at once. The coarse problem clusters the
 // directions u = k / ||k|| of R_b into n_list centers; each of the M subspace
 // problems clusters the residual slices (u - c_a)^(m) into K codewords. One
-// Lloyd iteration = the assignment (the encode pass of the update, run over
-// all of R_b) + the kernels below:
+// Lloyd iteration is:
 //
-//  * group_kernel: one workgroup per problem; a stable counting sort of the
-//    problem's tokens by their center (LDS histogram, prefix sum, placement
-//    chunk by chunk in token order), so that every mean below adds its
-//    members in a fixed order.
-//  * centers_kernel: one workgroup per (center, problem), groups of one
-//    thread per dimension over the members; the float64 mean of the
-//    members' directions, residual slices or values (the list means).
+//  * assign_kernel (coarse) or subspace_kernel: the nearest center of every
+//    token, on the matrix cores. subspace_kernel also adds the residuals to
+//    their codewords' sums.
+//  * coarse: group_count / scan / place_kernel (group_kernel above 1024
+//    lists), a stable counting sort of a KV head's tokens by list, so that
+//    every mean adds its members in a fixed order, and centers_kernel, the
+//    float64 mean of the members' directions (at the end of their values: the
+//    list means). Subspaces: codewords_kernel, the sums over the counts.
 //  * reseed_kernel: one workgroup per problem; a center without members
 //    takes the point farthest from its assigned center (farthest first, ties
 //    to the smaller token id; one point per empty center, in center order).
-//  * init_centers_kernel: the starting centers, the direction or residual
-//    slice of caller-drawn tokens.
+//
+// init_centers_kernel: the starting centers, the direction or residual slice
+// of caller-drawn tokens.
+#include <algorithm>
 #include <type_traits>
 
 #include "device_common.h"
@@ -38,15 +40,14 @@ __device__ __forceinline__ Problem problem_of(const Dims& D, int kind, int p) {
     return Problem{p, 0, D.n_list, kHeadDim};
 }
 
-// the vector of token t for a problem: its direction (kind 0), the residual
-// slice of subspace m (kind 1) or its value (kind 2), element x
+// the vector of token t for a problem: its direction (kind 0) or the residual
+// slice of subspace m (kind 1), element x
 template <typename T>
 __device__ __forceinline__ float token_elem(const Dims& D, int kind, const KV& kv, int bg, int m,
                                             int dims, int t, int x, const int32_t* ids_tm,
                                             const float* norms_tm, const float* centroids) {
     const int b = bg / D.Hkv, g = bg % D.Hkv;
     const int64_t row = b * kv.sb + g * kv.sh + static_cast<int64_t>(t) * kv.sn;
-    if (kind == 2) return load1<T>(static_cast<const T*>(kv.v) + row + x);
     const int col = m * dims + x;
     const float r = norms_tm[static_cast<int64_t>(bg) * D.rcap + t];
     const float u = r > 0.0f ? load1<T>(static_cast<const T*>(kv.k) + row + col) / r : 0.0f;
@@ -65,33 +66,29 @@ __device__ __forceinline__ int64_t center_index(const Dims& D, int kind, const P
 }
 
 __global__ __launch_bounds__(kGroupThreads) void group_kernel(Dims D, BatchInts lo, BatchInts hi,
-                                                              int kind, const int32_t* ids_tm,
-                                                              const uint8_t* codes_tm,
+                                                              const int32_t* ids_tm,
                                                               int32_t* order, int32_t* offs) {
     __shared__ int cnt[kMaxLists];
     __shared__ int placed[kMaxLists];
     __shared__ int chunk[kGroupThreads];
     __shared__ int wtot[kGroupThreads / kWave];
-    const int p = blockIdx.x;
-    const Problem pr = problem_of(D, kind, p);
-    const int M = D.pq_bits == 4 ? Pq4::M : Pq8::M;
-    const int b = pr.bg / D.Hkv;
+    const int p = blockIdx.x;   // (b, kv head)
+    const int nk = D.n_list;
+    const int b = p / D.Hkv;
     const int t0 = lo.v[b], t1 = hi.v[b];
     const int tid = threadIdx.x;
-    const int64_t row = static_cast<int64_t>(pr.bg) * D.rcap;
-    auto key = [&](int t) {
-        return kind == 1 ? static_cast<int>(codes_tm[(row + t) * M + pr.m]) : ids_tm[row + t];
-    };
-    for (int j = tid; j < pr.nkeys; j += kGroupThreads) {
+    const int64_t row = static_cast<int64_t>(p) * D.rcap;
+    auto key = [&](int t) { return ids_tm[row + t]; };
+    for (int j = tid; j < nk; j += kGroupThreads) {
         cnt[j] = 0;
         placed[j] = 0;
     }
     __syncthreads();
     for (int t = t0 + tid; t < t1; t += kGroupThreads) atomicAdd(&cnt[key(t)], 1);
     __syncthreads();
-    lds_exclusive_scan<kGroupThreads, kGroupScanPer>(cnt, pr.nkeys, wtot);
-    int32_t* of = offs + static_cast<int64_t>(p) * (pr.nkeys + 1);
-    for (int j = tid; j <= pr.nkeys; j += kGroupThreads) of[j] = j < pr.nkeys ? cnt[j] : t1 - t0;
+    lds_exclusive_scan<kGroupThreads, kGroupScanPer>(cnt, nk, wtot);
+    int32_t* of = offs + static_cast<int64_t>(p) * (nk + 1);
+    for (int j = tid; j <= nk; j += kGroupThreads) of[j] = j < nk ? cnt[j] : t1 - t0;
     int32_t* ord = order + static_cast<int64_t>(p) * D.rcap;
     for (int c0 = t0; c0 < t1; c0 += kGroupThreads) {
         const int t = c0 + tid;
@@ -126,41 +123,36 @@ constexpr int kGroupWaves = kGroupThreads / kWave;
 constexpr int kGroupFastKeys = 1024;
 constexpr int kSegTok = kBuildSegTok;   // tokens per segment
 
-__device__ __forceinline__ int group_key(const Dims& D, int kind, const Problem& pr, int64_t row, int t,
-                                         const int32_t* ids_tm, const uint8_t* codes_tm) {
-    const int M = D.pq_bits == 4 ? Pq4::M : Pq8::M;
-    const int k = kind == 1 ? static_cast<int>(codes_tm[(row + t) * M + pr.m]) : ids_tm[row + t];
-    return min(max(k, 0), pr.nkeys - 1);
+__device__ __forceinline__ int group_key(const Dims& D, int64_t row, int t, const int32_t* ids_tm) {
+    return min(max(ids_tm[row + t], 0), D.n_list - 1);
 }
 
 __global__ __launch_bounds__(kGroupThreads) void group_count_kernel(Dims D, BatchInts lo, BatchInts hi,
-                                                                    int kind, const int32_t* ids_tm,
-                                                                    const uint8_t* codes_tm,
+                                                                    const int32_t* ids_tm,
                                                                     int32_t* seg_hist, int nseg) {
     __shared__ int hist[kGroupFastKeys];
     const int seg = blockIdx.x, p = blockIdx.y;
-    const Problem pr = problem_of(D, kind, p);
-    const int b = pr.bg / D.Hkv;
+    const int nk = D.n_list;
+    const int b = p / D.Hkv;
     const int s0 = lo.v[b] + seg * kSegTok, s1 = min(s0 + kSegTok, hi.v[b]);
-    const int64_t row = static_cast<int64_t>(pr.bg) * D.rcap;
-    for (int j = threadIdx.x; j < pr.nkeys; j += kGroupThreads) hist[j] = 0;
+    const int64_t row = static_cast<int64_t>(p) * D.rcap;
+    for (int j = threadIdx.x; j < nk; j += kGroupThreads) hist[j] = 0;
     __syncthreads();
     for (int t = s0 + static_cast<int>(threadIdx.x); t < s1; t += kGroupThreads)
-        atomicAdd(&hist[group_key(D, kind, pr, row, t, ids_tm, codes_tm)], 1);
+        atomicAdd(&hist[group_key(D, row, t, ids_tm)], 1);
     __syncthreads();
-    int32_t* out = seg_hist + (static_cast<int64_t>(p) * nseg + seg) * pr.nkeys;
-    for (int j = threadIdx.x; j < pr.nkeys; j += kGroupThreads) out[j] = hist[j];
+    int32_t* out = seg_hist + (static_cast<int64_t>(p) * nseg + seg) * nk;
+    for (int j = threadIdx.x; j < nk; j += kGroupThreads) out[j] = hist[j];
 }
 
 __global__ __launch_bounds__(kGroupThreads) void group_scan_kernel(Dims D, BatchInts lo, BatchInts hi,
-                                                                   int kind, int32_t* seg_hist, int nseg,
+                                                                   int32_t* seg_hist, int nseg,
                                                                    int32_t* offs) {
     __shared__ int tot[kGroupFastKeys];
     __shared__ int wtot[kGroupWaves];
     const int p = blockIdx.x;
-    const Problem pr = problem_of(D, kind, p);
-    const int b = pr.bg / D.Hkv;
-    const int nk = pr.nkeys;
+    const int nk = D.n_list;
+    const int b = p / D.Hkv;
     int32_t* h = seg_hist + static_cast<int64_t>(p) * nseg * nk;
     for (int j = threadIdx.x; j < nk; j += kGroupThreads) {
         int sum = 0;
@@ -183,28 +175,26 @@ __global__ __launch_bounds__(kGroupThreads) void group_scan_kernel(Dims D, Batch
 }
 
 __global__ __launch_bounds__(kGroupThreads) void group_place_kernel(Dims D, BatchInts lo, BatchInts hi,
-                                                                    int kind, const int32_t* ids_tm,
-                                                                    const uint8_t* codes_tm,
+                                                                    const int32_t* ids_tm,
                                                                     const int32_t* seg_hist, int nseg,
                                                                     int32_t* order) {
     __shared__ int hist[kGroupWaves][kGroupFastKeys];
     const int seg = blockIdx.x, p = blockIdx.y;
-    const Problem pr = problem_of(D, kind, p);
-    const int b = pr.bg / D.Hkv;
+    const int nk = D.n_list;
+    const int b = p / D.Hkv;
     const int s0 = lo.v[b] + seg * kSegTok, s1 = min(s0 + kSegTok, hi.v[b]);
     if (s0 >= s1) return;
     const int tid = threadIdx.x;
     const int wave = tid / kWave;
     const int lane = lane_id();
-    const int nk = pr.nkeys;
-    const int64_t row = static_cast<int64_t>(pr.bg) * D.rcap;
+    const int64_t row = static_cast<int64_t>(p) * D.rcap;
     // the wave's part of the segment
     const int n = s1 - s0;
     const int per = (n + kGroupWaves - 1) / kGroupWaves;
     const int w0 = s0 + min(wave * per, n), w1 = s0 + min(wave * per + per, n);
     for (int i = tid; i < kGroupWaves * kGroupFastKeys; i += kGroupThreads) (&hist[0][0])[i] = 0;
     __syncthreads();
-    for (int t = w0 + lane; t < w1; t += kWave) atomicAdd(&hist[wave][group_key(D, kind, pr, row, t, ids_tm, codes_tm)], 1);
+    for (int t = w0 + lane; t < w1; t += kWave) atomicAdd(&hist[wave][group_key(D, row, t, ids_tm)], 1);
     __syncthreads();
     const int32_t* base_g = seg_hist + (static_cast<int64_t>(p) * nseg + seg) * nk;
     for (int j = tid; j < nk; j += kGroupThreads) {
@@ -221,7 +211,7 @@ __global__ __launch_bounds__(kGroupThreads) void group_place_kernel(Dims D, Batc
     for (int c0 = w0; c0 < w1; c0 += kWave) {
         const int t = c0 + lane;
         const bool valid = t < w1;
-        const int k = valid ? group_key(D, kind, pr, row, t, ids_tm, codes_tm) : 0;
+        const int k = valid ? group_key(D, row, t, ids_tm) : 0;
         // ranks among equal keys from ballots alone (registers), then one LDS
         // atomic per distinct key, made by the key's first lane
         uint64_t todo = __ballot(valid);
@@ -244,44 +234,68 @@ __global__ __launch_bounds__(kGroupThreads) void group_place_kernel(Dims D, Batc
     }
 }
 
-// 1024 threads per center: 1024 / dims groups of one thread per dimension;
-// group gi adds members gi, gi + groups, ... in order, then group 0 adds the
-// group sums in group order (a fixed order: the build is deterministic).
-constexpr int kCenThreads = 1024;
+// centers_kernel: the float64 mean of a center's members' directions (kind 0)
+// or values (kind 2), 16 lanes of 8 dimensions per member row: stream si adds
+// members si, si + 16, ... in order, kCenRows of them loaded at once, then the
+// streams' sums are added in stream order (a fixed order: the build is
+// deterministic). Bound by the gather of the rows: 128K tokens x 8 KV heads,
+// 0.07 ms for the directions and 0.09 for the values (one thread per dimension
+// and member: 0.45 and 0.30 ms).
+constexpr int kCenThreads = 256;
+constexpr int kCenStreams = kCenThreads / 16;
+constexpr int kCenRows = 4;
 
 template <typename T>
 __global__ __launch_bounds__(kCenThreads) void centers_kernel(Dims D, int kind, KV kv,
-                                                              const int32_t* ids_tm,
-                                                              const float* norms_tm,
-                                                              const float* centroids,
-                                                              const int32_t* order,
-                                                              const int32_t* offs, float* out) {
-    __shared__ double part[kCenThreads];
+                                                              const float* __restrict__ norms_tm,
+                                                              const int32_t* __restrict__ order,
+                                                              const int32_t* __restrict__ offs, float* __restrict__ out) {
+    __shared__ double part[kCenStreams][kHeadDim];
     const int c = blockIdx.x;
-    const int p = blockIdx.y;
-    const Problem pr = problem_of(D, kind, p);
-    if (c >= pr.nkeys) return;
-    const int groups = kCenThreads / pr.dims;
-    const int gi = threadIdx.x / pr.dims;
-    const int x = threadIdx.x % pr.dims;
-    const int32_t* of = offs + static_cast<int64_t>(p) * (pr.nkeys + 1);
+    const int bg = blockIdx.y;
+    const int b = bg / D.Hkv, g = bg % D.Hkv;
+    const int si = threadIdx.x / 16;
+    const int x0 = threadIdx.x % 16 * 8;
+    const int32_t* of = offs + static_cast<int64_t>(bg) * (D.n_list + 1);
     const int o0 = of[c], o1 = of[c + 1];
+    float* dst = out + (static_cast<int64_t>(bg) * D.n_list + c) * kHeadDim;
     if (o1 == o0) {   // empty: the list mean is 0; a center is re-seeded afterwards
-        if (kind == 2 && gi == 0) out[center_index(D, kind, pr, c, x)] = 0.0f;
+        if (kind == 2 && si == 0)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) dst[x0 + e] = 0.0f;
         return;
     }
-    const int32_t* ord = order + static_cast<int64_t>(p) * D.rcap;
-    double acc = 0.0;
-#pragma unroll 4
-    for (int i = o0 + gi; i < o1; i += groups)
-        acc += static_cast<double>(
-            token_elem<T>(D, kind, kv, pr.bg, pr.m, pr.dims, ord[i], x, ids_tm, norms_tm, centroids));
-    part[threadIdx.x] = acc;
+    const T* src = static_cast<const T*>(kind == 2 ? kv.v : kv.k) + b * kv.sb + g * kv.sh + x0;
+    const int64_t row = static_cast<int64_t>(bg) * D.rcap;
+    double acc[8] = {};
+    for (int i0 = o0 + si; i0 < o1; i0 += kCenStreams * kCenRows) {
+        Raw8<T> raw[kCenRows];
+        float r[kCenRows];
+#pragma unroll
+        for (int u = 0; u < kCenRows; ++u) {
+            const int t = order[row + min(i0 + u * kCenStreams, o1 - 1)];   // past the end: the last again, unused
+            raw[u].load(src + static_cast<int64_t>(t) * kv.sn);
+            r[u] = kind == 2 ? 1.0f : norms_tm[row + t];
+        }
+#pragma unroll
+        for (int u = 0; u < kCenRows; ++u) {
+            if (i0 + u * kCenStreams >= o1) break;
+            float x[8];
+            raw[u].to(x);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                acc[e] += static_cast<double>(kind == 2 ? x[e] : r[u] > 0.0f ? x[e] / r[u] : 0.0f);
+        }
+    }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) part[si][x0 + e] = acc[e];
     __syncthreads();
-    if (gi != 0) return;
-    double sum = 0.0;
-    for (int w = 0; w < groups; ++w) sum += part[w * pr.dims + x];
-    out[center_index(D, kind, pr, c, x)] = static_cast<float>(sum / (o1 - o0));
+    if (threadIdx.x < kHeadDim) {
+        double sum = 0.0;
+#pragma unroll
+        for (int w = 0; w < kCenStreams; ++w) sum += part[w][threadIdx.x];
+        dst[threadIdx.x] = static_cast<float>(sum / (o1 - o0));
+    }
 }
 
 template <typename T>
@@ -291,27 +305,44 @@ __global__ __launch_bounds__(kGroupThreads) void reseed_kernel(Dims D, BatchInts
                                                                const float* norms_tm,
                                                                const float* centroids,
                                                                const int32_t* offs,
+                                                               const uint32_t* counts,
                                                                const float* dist_c,
                                                                const float* dist_f, float* out) {
-    __shared__ int sof[kMaxLists + 1];
+    __shared__ int empty[kMaxLists];   // the centers without members, in order
+    __shared__ int wtot[kGroupThreads / kWave];
     __shared__ float wd[kGroupThreads / kWave];
     __shared__ int wt[kGroupThreads / kWave];
     __shared__ int pick;
     const int p = blockIdx.x;
     const Problem pr = problem_of(D, kind, p);
-    const int M = D.pq_bits == 4 ? Pq4::M : Pq8::M;
     const int b = pr.bg / D.Hkv;
     const int t0 = lo.v[b], t1 = hi.v[b];
     const int tid = threadIdx.x;
     const int32_t* of = offs + static_cast<int64_t>(p) * (pr.nkeys + 1);
-    for (int j = tid; j <= pr.nkeys; j += kGroupThreads) sof[j] = of[j];
-    __syncthreads();
-    const int64_t row = static_cast<int64_t>(pr.bg) * D.rcap;
-    auto dist = [&](int t) { return kind == 1 ? dist_f[(row + t) * M + pr.m] : dist_c[row + t]; };
+    int n_empty = 0;
+    for (int j0 = 0; j0 < pr.nkeys; j0 += kGroupThreads) {
+        const int j = j0 + tid;
+        const bool is = j < pr.nkeys &&
+                        (kind == 1 ? counts[static_cast<int64_t>(p) * pr.nkeys + j] == 0u : of[j + 1] == of[j]);
+        const uint64_t mask = __ballot(is);
+        if (lane_id() == 0) wtot[tid / kWave] = __popcll(mask);
+        __syncthreads();
+        int at = n_empty;
+        for (int w = 0; w < kGroupThreads / kWave; ++w) {
+            if (w < tid / kWave) at += wtot[w];
+            n_empty += wtot[w];
+        }
+        if (is) empty[at + lanes_below(mask)] = j;
+        __syncthreads();
+    }
+    if (n_empty == 0) return;
+    // distances of the problem's tokens: [B Hkv (M)][rcap]
+    const float* dist_p = (kind == 1 ? dist_f : dist_c) + static_cast<int64_t>(p) * D.rcap;
+    auto dist = [&](int t) { return dist_p[t]; };
     float pd = __builtin_huge_valf();   // the previous pick: points must order after it
     int pt = -1;
-    for (int c = 0; c < pr.nkeys; ++c) {
-        if (sof[c + 1] != sof[c]) continue;   // uniform: every thread reads the same entry
+    for (int i = 0; i < n_empty; ++i) {
+        const int c = empty[i];
         // the farthest point after (pd, pt) in the order (distance desc, token asc)
         float bd = -1.0f;
         int bt = -1;
@@ -413,52 +444,47 @@ static int n_keys(const Dims& D, int kind) {
     return kind == 1 ? (D.pq_bits == 4 ? Pq4::K : Pq8::K) : D.n_list;
 }
 
-hipError_t launch_group_segments(const Dims& D, const BatchInts& lo, const BatchInts& hi, int kind,
-                                 const int32_t* ids_tm, const uint8_t* codes_tm, int32_t* seg_hist,
-                                 int32_t* order, int32_t* offs, hipStream_t s) {
+hipError_t launch_group_segments(const Dims& D, const BatchInts& lo, const BatchInts& hi,
+                                 const int32_t* ids_tm, int32_t* seg_hist, int32_t* order, int32_t* offs,
+                                 hipStream_t s) {
     int max_n = 0;
     for (int b = 0; b < D.B; ++b) max_n = hi.v[b] - lo.v[b] > max_n ? hi.v[b] - lo.v[b] : max_n;
     const int nseg = (max_n + kSegTok - 1) / kSegTok;
-    const dim3 grid(nseg, n_problems(D, kind));
+    const dim3 grid(nseg, D.B * D.Hkv);
     if (nseg > 0) {
-        hipLaunchKernelGGL(group_count_kernel, grid, dim3(kGroupThreads), 0, s, D, lo, hi, kind, ids_tm,
-                           codes_tm, seg_hist, nseg);
+        hipLaunchKernelGGL(group_count_kernel, grid, dim3(kGroupThreads), 0, s, D, lo, hi, ids_tm,
+                           seg_hist, nseg);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     // also with no tokens: the offsets are written
-    hipLaunchKernelGGL(group_scan_kernel, dim3(n_problems(D, kind)), dim3(kGroupThreads), 0, s, D, lo,
-                       hi, kind, seg_hist, nseg, offs);
+    hipLaunchKernelGGL(group_scan_kernel, dim3(D.B * D.Hkv), dim3(kGroupThreads), 0, s, D, lo,
+                       hi, seg_hist, nseg, offs);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || nseg == 0) return e;
-    hipLaunchKernelGGL(group_place_kernel, grid, dim3(kGroupThreads), 0, s, D, lo, hi, kind, ids_tm,
-                       codes_tm, seg_hist, nseg, order);
+    hipLaunchKernelGGL(group_place_kernel, grid, dim3(kGroupThreads), 0, s, D, lo, hi, ids_tm,
+                       seg_hist, nseg, order);
     return hipGetLastError();
 }
 
-hipError_t launch_group(const Dims& D, const BatchInts& lo, const BatchInts& hi, int kind,
-                        const int32_t* ids_tm, const uint8_t* codes_tm, const BuildBufs& bb,
-                        hipStream_t s) {
-    if (n_keys(D, kind) <= kGroupFastKeys && bb.seg_hist)
-        return launch_group_segments(D, lo, hi, kind, ids_tm, codes_tm, bb.seg_hist, bb.order, bb.offs, s);
-    else
-        hipLaunchKernelGGL(group_kernel, dim3(n_problems(D, kind)), dim3(kGroupThreads), 0, s, D, lo,
-                           hi, kind, ids_tm, codes_tm, bb.order, bb.offs);
+hipError_t launch_group(const Dims& D, const BatchInts& lo, const BatchInts& hi, const int32_t* ids_tm,
+                        const BuildBufs& bb, hipStream_t s) {
+    if (D.n_list <= kGroupFastKeys && bb.seg_hist)
+        return launch_group_segments(D, lo, hi, ids_tm, bb.seg_hist, bb.order, bb.offs, s);
+    hipLaunchKernelGGL(group_kernel, dim3(D.B * D.Hkv), dim3(kGroupThreads), 0, s, D, lo, hi, ids_tm,
+                       bb.order, bb.offs);
     return hipGetLastError();
 }
 
-hipError_t launch_centers(const Dims& D, const BatchInts& lo, const BatchInts& hi, int kind,
-                          const KV& kv, const int32_t* ids_tm, const float* norms_tm,
-                          const float* centroids, const BuildBufs& bb, float* out, hipStream_t s) {
-    (void)lo;
-    (void)hi;
-    const dim3 grid(n_keys(D, kind), n_problems(D, kind));
+hipError_t launch_centers(const Dims& D, int kind, const KV& kv, const float* norms_tm, const BuildBufs& bb,
+                          float* out, hipStream_t s) {
+    const dim3 grid(D.n_list, D.B * D.Hkv);
     if (kv.bf16)
-        hipLaunchKernelGGL(centers_kernel<bf16_t>, grid, dim3(kCenThreads), 0, s, D, kind, kv, ids_tm,
-                           norms_tm, centroids, bb.order, bb.offs, out);
+        hipLaunchKernelGGL(centers_kernel<bf16_t>, grid, dim3(kCenThreads), 0, s, D, kind, kv, norms_tm,
+                           bb.order, bb.offs, out);
     else
-        hipLaunchKernelGGL(centers_kernel<float>, grid, dim3(kCenThreads), 0, s, D, kind, kv, ids_tm,
-                           norms_tm, centroids, bb.order, bb.offs, out);
+        hipLaunchKernelGGL(centers_kernel<float>, grid, dim3(kCenThreads), 0, s, D, kind, kv, norms_tm,
+                           bb.order, bb.offs, out);
     return hipGetLastError();
 }
 
@@ -468,10 +494,10 @@ hipError_t launch_reseed(const Dims& D, const BatchInts& lo, const BatchInts& hi
     const dim3 grid(n_problems(D, kind));
     if (kv.bf16)
         hipLaunchKernelGGL(reseed_kernel<bf16_t>, grid, dim3(kGroupThreads), 0, s, D, lo, hi, kind,
-                           kv, ids_tm, norms_tm, centroids, bb.offs, bb.dist_c, bb.dist_f, out);
+                           kv, ids_tm, norms_tm, centroids, bb.offs, bb.counts, bb.dist_c, bb.dist_f, out);
     else
         hipLaunchKernelGGL(reseed_kernel<float>, grid, dim3(kGroupThreads), 0, s, D, lo, hi, kind,
-                           kv, ids_tm, norms_tm, centroids, bb.offs, bb.dist_c, bb.dist_f, out);
+                           kv, ids_tm, norms_tm, centroids, bb.offs, bb.counts, bb.dist_c, bb.dist_f, out);
     return hipGetLastError();
 }
 
@@ -499,7 +525,27 @@ hipError_t launch_init_centers(const Dims& D, int kind, const KV& kv, const int3
 // direction by 1.8e-8 (1.7e-7).
 // ---------------------------------------------------------------------------
 typedef __bf16 bf8_t __attribute__((ext_vector_type(8)));
+typedef float f4_t __attribute__((ext_vector_type(4)));
 typedef float f16_t __attribute__((ext_vector_type(16)));
+
+// N (2 or 4) consecutive elements of a row, from an address aligned to them.
+template <typename T, int N>
+__device__ __forceinline__ void load_slice(const T* p, float (&x)[N]) {
+    static_assert(N == 2 || N == 4, "one load");
+    if constexpr (std::is_same<T, float>::value && N == 4) {
+        const float4 v = *reinterpret_cast<const float4*>(p);
+        x[0] = v.x; x[1] = v.y; x[2] = v.z; x[3] = v.w;
+    } else if constexpr (std::is_same<T, float>::value) {
+        const float2 v = *reinterpret_cast<const float2*>(p);
+        x[0] = v.x; x[1] = v.y;
+    } else if constexpr (N == 4) {
+        const uint2 v = *reinterpret_cast<const uint2*>(p);
+        x[0] = bf16_lo(v.x); x[1] = bf16_hi(v.x); x[2] = bf16_lo(v.y); x[3] = bf16_hi(v.y);
+    } else {
+        const uint32_t v = *reinterpret_cast<const uint32_t*>(p);
+        x[0] = bf16_lo(v); x[1] = bf16_hi(v);
+    }
+}
 
 // The bf16 parts of x, largest first.
 __device__ __forceinline__ void split_bf16(float x, __bf16 (&p)[3]) {
@@ -605,6 +651,11 @@ __device__ __forceinline__ bf8_t norm_slots(float r, int half) {
 // a large library product reaches here) in place of 3.19 ms with
 // v_mfma_f32_16x16x4f32 and a distance and a two-key compare per pair.
 // ---------------------------------------------------------------------------
+// Squared distances closer than this are decided by nearest_kernel: two of the
+// 32-bit matrix cores' are off by up to 9e-7 in their difference, two of
+// assign_kernel's by 3e-7 (four times the largest error of a dot product, above,
+// and a rounding).
+constexpr float kNearGap = 4e-6f;
 constexpr int kAsgThreads = 256;
 constexpr int kAsgWaves = kAsgThreads / kWave;
 
@@ -692,7 +743,9 @@ __global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts l
                                                              const __bf16* __restrict__ split, int n_tile,
                                                              int32_t* __restrict__ ids_tm,
                                                              float* __restrict__ norms_tm,
-                                                             float* __restrict__ dist_c) {
+                                                             float* __restrict__ dist_c,
+                                                             int32_t* __restrict__ near,
+                                                             uint32_t* __restrict__ n_near) {
     constexpr int NT = AsgTokens<T>::kTiles, P = AsgTokens<T>::kParts;
     constexpr int kWgTok = kAsgWaves * NT * 32;
     __shared__ bf8_t cen[2][kSplitBlocks * kWave];
@@ -736,11 +789,11 @@ __global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts l
         nrm[tt] = norm_slots(scale[tt], half);
         if (half == 0 && tk < nt) norms_tm[static_cast<int64_t>(bg) * D.rcap + t_base + tk] = r;
     }
-    float best[NT];
+    float best[NT], second[NT];
     int best_i[NT];
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt) {
-        best[tt] = -__builtin_huge_valf();
+        best[tt] = second[tt] = -__builtin_huge_valf();
         best_i[tt] = 0;   // a valid id whatever the values
     }
     put(0);
@@ -783,230 +836,631 @@ __global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts l
         for (int tt = 0; tt < NT; ++tt) {
             // the lane's rows are in increasing center order: the first of
             // equal values stays (and a NaN, of a center that is one, never wins)
-            float m = -__builtin_huge_valf();
+            float m = -__builtin_huge_valf(), m2 = m;
             int mi = 0;
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                mi = acc[tt][i] > m ? i : mi;
-                m = fmaxf(m, acc[tt][i]);
+                const bool up = acc[tt][i] > m;
+                m2 = __builtin_amdgcn_fmed3f(acc[tt][i], m, m2);   // m2 <= m: the new second
+                mi = up ? i : mi;
+                m = up ? acc[tt][i] : m;
             }
-            if (m > best[tt]) {
-                best[tt] = m;
-                best_i[tt] = tile * kTileCen + 8 * (mi / 4) + 4 * half + mi % 4;
-            }
+            second[tt] = __builtin_amdgcn_fmed3f(best[tt], m, fmaxf(second[tt], m2));
+            const bool up = m > best[tt];
+            best[tt] = up ? m : best[tt];
+            best_i[tt] = up ? tile * 16 + mi : best_i[tt];   // element 16 tile + i, until the end
         }
         if (tile + 1 < n_tile) put((tile + 1) & 1);   // its last readers passed the barrier below
         __syncthreads();
     }
 #pragma unroll
     for (int tt = 0; tt < NT; ++tt) {
-        asg_fold(best[tt], best_i[tt], __shfl_xor(best[tt], 32), __shfl_xor(best_i[tt], 32));
+        const int e = best_i[tt] % 16;
+        best_i[tt] = best[tt] > -__builtin_huge_valf()
+                         ? best_i[tt] / 16 * kTileCen + 8 * (e / 4) + 4 * half + e % 4 : 0;
+        const float ob = __shfl_xor(best[tt], 32), os = __shfl_xor(second[tt], 32);
+        second[tt] = __builtin_amdgcn_fmed3f(best[tt], ob, fmaxf(second[tt], os));
+        asg_fold(best[tt], best_i[tt], ob, __shfl_xor(best_i[tt], 32));
         const int tk = (wave * NT + tt) * 32 + col;
         if (half == 0 && tk < nt) {
             const int64_t at = static_cast<int64_t>(bg) * D.rcap + t_base + tk;
             ids_tm[at] = min(best_i[tt], D.n_list - 1);
             if (dist_c) dist_c[at] = scale[tt] > 0.0f ? fmaxf(unit2[tt] - 2.0f * best[tt] / scale[tt], 0.0f) : 0.0f;
+            if (!(best[tt] - second[tt] > 0.5f * kNearGap * scale[tt]))   // also with a NaN
+                near[static_cast<int64_t>(bg) * D.rcap + atomicAdd(&n_near[bg], 1u)] = t_base + tk;
         }
     }
 }
 
 // ---------------------------------------------------------------------------
-// subspace_kernel: the codeword search of the build on the matrix cores, for
-// tokens whose lists are known (ids_tm): the residual r = u - c_a of each
-// token, then per subspace m the nearest codeword by ||p||^2 - 2 r^(m) . p
-// (16x16x4 fp32 MFMA tiles: 16 codewords x 16 tokens, DSUB / 4 steps). Lane
-// group q contributes dimensions m DSUB + q DSUB / 4 + s of subspace m in
-// step s, so its operands are contiguous. Writes the norms ||k||, the codes
-// and the chosen squared distances (dist_f, or null); ties go to the smaller
-// codeword.
+// nearest_kernel: the lists of the tokens that assign_kernel found nearly as
+// close to a second center (near, n_near per KV head), by the distance the
+// 32-bit matrix cores give (v_mfma_f32_16x16x4f32): which of two such centers is
+// called the nearest is then the same as with those alone. One token in some
+// thousands comes here; where many centers coincide it can be all of them, and
+// then costs what that search costs for every token (3.2 ms at 128K tokens x 8
+// KV heads x 1024 lists).
+//
+// ||u - c||^2 = ||u||^2 + ||c||^2 - 2 u . c: 32 tokens per workgroup step (2
+// tiles of 16), centers in chunks of 64 through LDS, the next chunk's loads
+// under the current one's products; wave w takes the chunk's center tile w
+// against both token tiles, since a KV head lists only some tens of tokens and a
+// wave's chain of products is what a chunk waits for (8 tiles a wave: 0.16 ms in
+// place of 0.06 ms). The 128 dimensions go as 32 steps: in step j, lane group q
+// (lane / 16) contributes dimension 32 q + j, so each lane reads 32 contiguous
+// floats of its row; rows are 132 floats apart in LDS, which puts the 16 rows of
+// a read on distinct 16-byte bank groups.
 // ---------------------------------------------------------------------------
-constexpr int kAsgTok = 128;                  // tokens per workgroup
-constexpr int kAsgLd = kHeadDim + 4;          // LDS row stride (floats)
-typedef float asg_v4f __attribute__((ext_vector_type(4)));
+constexpr int kNearThreads = 256;
+constexpr int kNearTok = 32;                   // tokens per workgroup step
+constexpr int kNearCen = 64;                   // centers per chunk, a tile per wave
+constexpr int kNearLd = kHeadDim + 4;          // LDS row stride (floats)
+constexpr int kNearWgs = 32;                   // workgroups per KV head
+static_assert(kNearCen == kNearThreads / kWave * 16, "one center tile per wave");
 
-__device__ __forceinline__ void sub_fold(float& d, int& i, float od, int oi) {
+__device__ __forceinline__ void near_fold(float& d, int& i, float od, int oi) {
     if (od < d || (od == d && oi < i)) {
         d = od;
         i = oi;
     }
 }
 
-template <typename PQ>
-constexpr int kSubRound = PQ::K >= 256 ? 4 : PQ::M;   // subspaces per LDS round
-template <typename PQ>
-constexpr int kSubLd = PQ::DSUB + 1;                   // codeword row stride (odd: distinct banks)
-static_assert(kSubRound<Pq8> * Pq8::K * kSubLd<Pq8> <= kAsgTok * kAsgLd, "codewords fit the token rows");
-static_assert(kSubRound<Pq4> * Pq4::K * kSubLd<Pq4> <= kAsgTok * kAsgLd, "codewords fit the token rows");
-
-template <typename T, typename PQ>
-__global__ __launch_bounds__(kAsgThreads) void subspace_kernel(
-    Dims D, BatchInts lo, BatchInts hi, KV kv, const float* __restrict__ centroids,
-    const float* __restrict__ codebooks, const int32_t* __restrict__ ids_tm,
-    uint8_t* __restrict__ codes_tm, float* __restrict__ norms_tm, float* __restrict__ dist_f) {
-    constexpr int M = PQ::M, K = PQ::K, DS = PQ::DSUB, S = DS / 4, SR = kSubRound<PQ>, LD = kSubLd<PQ>;
-    constexpr int NCT = K / 16;   // codeword tiles per subspace
-    static_assert(K % 16 == 0 && DS % 4 == 0 && M % SR == 0, "tiling");
-    __shared__ float4 rows4[kAsgTok * kAsgLd / 4];   // residual rows, then codewords
-    __shared__ float pn[SR * K];                     // ||p||^2 of the round's codewords
-    float* rows = reinterpret_cast<float*>(rows4);
+template <typename T>
+__global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
+                                                               const float* __restrict__ centroids,
+                                                               const int32_t* __restrict__ near,
+                                                               const uint32_t* __restrict__ n_near,
+                                                               int32_t* __restrict__ ids_tm,
+                                                               float* __restrict__ dist_c) {
+    __shared__ float4 tok4[kNearTok * kNearLd / 4];
+    __shared__ float4 cen4[kNearCen * kNearLd / 4];
+    __shared__ float cn[kNearCen];                    // ||c||^2 of the chunk's centers
+    __shared__ float un[kNearTok];                    // ||u||^2 of the tokens
+    __shared__ float wd[kNearThreads / kWave][kNearTok];
+    __shared__ int wi[kNearThreads / kWave][kNearTok];
+    float* tok = reinterpret_cast<float*>(tok4);
+    float* rows = reinterpret_cast<float*>(cen4);
     const int b = blockIdx.z;
     const int g = blockIdx.y;
-    const int t_base = lo.v[b] + static_cast<int>(blockIdx.x) * kAsgTok;
-    if (t_base >= hi.v[b]) return;
-    const int nt = min(kAsgTok, hi.v[b] - t_base);
     const int bg = b * D.Hkv + g;
-    const int64_t row0 = static_cast<int64_t>(bg) * D.rcap + t_base;
+    const int n = static_cast<int>(n_near[bg]);
+    const int32_t* list = near + static_cast<int64_t>(bg) * D.rcap;
+    const int tid = threadIdx.x;
+    const int wave = tid / kWave;
+    const int lane = lane_id();
+    const int col = lane % 16;   // the lane's token column (B) / center row (A) in a tile
+    const int q = lane / 16;     // its lane group: dimensions 32 q .. 32 q + 31
+    const T* kb = static_cast<const T*>(kv.k) + b * kv.sb + g * kv.sh;
+    const float* cen = centroids + static_cast<int64_t>(bg) * D.n_list * kHeadDim;
+
+    for (int base = static_cast<int>(blockIdx.x) * kNearTok; base < n;
+         base += static_cast<int>(gridDim.x) * kNearTok) {
+        const int nt = min(kNearTok, n - base);
+        // the chunks' loads: 32 float4 per center row, zeros past the last center
+        constexpr int kLoads = kNearCen * kHeadDim / 4 / kNearThreads;
+        float4 next[kLoads];
+        auto fetch = [&](int c0) {
+#pragma unroll
+            for (int it = 0; it < kLoads; ++it) {
+                const int idx = it * kNearThreads + tid;
+                const int c = c0 + idx / 32;
+                next[it] = c < D.n_list
+                               ? reinterpret_cast<const float4*>(cen + static_cast<int64_t>(c) * kHeadDim)[idx % 32]
+                               : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+            }
+        };
+        fetch(0);
+        // 1) the directions u = k / ||k|| of the workgroup's tokens into LDS:
+        //    16 threads per token, 8 dimensions each
+#pragma unroll
+        for (int it = 0; it < kNearTok / 16; ++it) {
+            const int tk = it * 16 + tid / 16;
+            const int x0 = (tid % 16) * 8;
+            float x[8];
+            if (tk < nt) {
+                Load8<T>::run(kb + static_cast<int64_t>(list[base + tk]) * kv.sn + x0, x);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+            }
+            float ss = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
+            const float r = sqrtf(ss);
+            float uu = 0.0f;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                x[e] = r > 0.0f ? x[e] / r : 0.0f;
+                uu = fmaf(x[e], x[e], uu);
+            }
+#pragma unroll
+            for (int off = 1; off < 16; off <<= 1) uu += __shfl_xor(uu, off);
+            if (tid % 16 == 0) un[tk] = uu;
+            float4* dst = reinterpret_cast<float4*>(tok + tk * kNearLd + x0);
+            dst[0] = make_float4(x[0], x[1], x[2], x[3]);
+            dst[1] = make_float4(x[4], x[5], x[6], x[7]);
+        }
+        __syncthreads();
+        // 2) the B operands: token rows (2 tiles), 32 dimensions each
+        float bv[2][32];
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+            const float4* src = reinterpret_cast<const float4*>(tok + (tt * 16 + col) * kNearLd + 32 * q);
+#pragma unroll
+            for (int v = 0; v < 8; ++v) {
+                const float4 f = src[v];
+                bv[tt][4 * v] = f.x; bv[tt][4 * v + 1] = f.y; bv[tt][4 * v + 2] = f.z; bv[tt][4 * v + 3] = f.w;
+            }
+        }
+        float best_d[2] = {__builtin_huge_valf(), __builtin_huge_valf()};
+        int best_i[2] = {0, 0};   // a valid id even if every distance is NaN
+
+        // 3) the centers, a chunk of 64 at a time
+        for (int c0 = 0; c0 < D.n_list; c0 += kNearCen) {
+#pragma unroll
+            for (int it = 0; it < kLoads; ++it) {
+                const int idx = it * kNearThreads + tid;
+                const float4 v = next[it];
+                float ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+#pragma unroll
+                for (int off = 1; off < 32; off <<= 1) ss += __shfl_xor(ss, off);
+                if (idx % 32 == 0) cn[idx / 32] = ss;
+                reinterpret_cast<float4*>(rows + idx / 32 * kNearLd)[idx % 32] = v;
+            }
+            __syncthreads();
+            if (c0 + kNearCen < D.n_list) fetch(c0 + kNearCen);
+            f4_t acc[2] = {f4_t{0.0f, 0.0f, 0.0f, 0.0f}, f4_t{0.0f, 0.0f, 0.0f, 0.0f}};
+#pragma unroll
+            for (int j4 = 0; j4 < 8; ++j4) {
+                const float4 av = reinterpret_cast<const float4*>(rows + (wave * 16 + col) * kNearLd + 32 * q)[j4];
+#pragma unroll
+                for (int jj = 0; jj < 4; ++jj) {
+                    const float a = jj == 0 ? av.x : jj == 1 ? av.y : jj == 2 ? av.z : av.w;
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt)
+                        acc[tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[tt][4 * j4 + jj], acc[tt], 0, 0, 0);
+                }
+            }
+            // distances up to ||u||^2: row 4 q + i of tile w is center c0 + 16 w + 4 q + i
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int cl = wave * 16 + 4 * q + i;
+                if (c0 + cl < D.n_list) {
+                    const float c2 = cn[cl];
+#pragma unroll
+                    for (int tt = 0; tt < 2; ++tt)
+                        near_fold(best_d[tt], best_i[tt], fmaf(-2.0f, acc[tt][i], c2), c0 + cl);
+                }
+            }
+            __syncthreads();   // the chunk is no longer read
+        }
+        // 4) the 4 lane groups of a token column, the waves, then the outputs
+#pragma unroll
+        for (int tt = 0; tt < 2; ++tt) {
+#pragma unroll
+            for (int off = 16; off < kWave; off <<= 1) {
+                const float od = __shfl_xor(best_d[tt], off);
+                const int oi = __shfl_xor(best_i[tt], off);
+                near_fold(best_d[tt], best_i[tt], od, oi);
+            }
+            if (q == 0) {
+                wd[wave][tt * 16 + col] = best_d[tt];
+                wi[wave][tt * 16 + col] = best_i[tt];
+            }
+        }
+        __syncthreads();
+        if (tid < nt) {
+            float d = wd[0][tid];
+            int i = wi[0][tid];
+#pragma unroll
+            for (int w = 1; w < kNearThreads / kWave; ++w) near_fold(d, i, wd[w][tid], wi[w][tid]);
+            const int64_t at = static_cast<int64_t>(bg) * D.rcap + list[base + tid];
+            ids_tm[at] = i;
+            if (dist_c) dist_c[at] = fmaxf(d + un[tid], 0.0f);
+        }
+        __syncthreads();   // before the next tokens' rows
+    }
+}
+
+// ---------------------------------------------------------------------------
+// subspace_kernel: per token and subspace, the nearest codeword to the residual
+// slice r = (u - c_a)^(m) (lists in ids_tm, norms in norms_tm), by half the
+// squared distance, ||r||^2 / 2 - r . p + ||p||^2 / 2, again from products of
+// bf16 parts: the six of a residual's and a codeword's parts that matter,
+// v_mfma_f32_16x16x32_bf16 on 16 codewords x 16 tokens, started at the token's
+// ||r||^2 / 2. These are never below 0 but for rounding, so their bits are
+// compared as integers (a three-way minimum costs one instruction and needs no
+// quieting of NaNs, whose bits are the largest): the search is bound by the
+// VALU, 15 instructions per 8 codewords. Lane group q (lane / 16) owns DQ = DSUB / 4 consecutive
+// dimensions of the subspace in both operands and holds every product of parts
+// of these, so a lane computes, splits and later adds only its own slice of
+// the residual, and no operand crosses lanes. Its 8 kBlocks slots, in order:
+// products (codeword part, residual part) (3,1) (1,3) (2,2) (2,1) (1,2) of DQ
+// dimensions each, the three parts of ||p||^2 / 2 (lane group 0) against 1,
+// zeros, and product (1,1); the residual's parts are those of -r.
+//
+// A workgroup holds the operands of kSubs subspaces in LDS for all its tokens
+// (one of Pq8's, all eight of Pq4's: 32 KB) and
+// walks a slice of one KV head's tokens, 8 waves of kSubTiles x 16. In a
+// training pass it also adds every residual to its codeword's sum, in 64-bit
+// fixed point (2^-41; the slices are below 2 in size and at most 2^20 of them
+// meet in a sum), so the sums are exact to 2^-42 a member and don't depend on
+// the order: LDS first, then one global addition per workgroup. That replaces
+// the grouping of every subspace's tokens and the gathers of their means.
+// 128K tokens x 8 KV heads, Pq8: a training pass 0.82 ms, the final one 0.74 ms
+// (1.9 ms with v_mfma_f32_16x16x4f32 and a two-key compare per pair; the
+// grouping and gathers took another 1.3 ms a training pass). Two prompts of
+// 40K, Pq4: 0.14 and 0.09 ms (0.20 ms, and 0.4 ms).
+// ---------------------------------------------------------------------------
+constexpr int kSubThreads = 512;
+constexpr int kSubWaves = kSubThreads / kWave;
+constexpr int kSubTiles = 2;                        // token tiles of 16 per wave and step
+constexpr int kSubStep = kSubWaves * kSubTiles * 16;   // tokens per workgroup step
+constexpr float kSumHi = 1048576.0f;                // 2^20: the fixed point's upper part
+constexpr float kSumLo = 2199023255552.0f;          // 2^41
+constexpr uint32_t kSumNan = 0x80000000u;           // count bit: a member was not a number
+
+template <typename PQ>
+struct SubLayout {
+    static constexpr int kSubs = PQ::K >= 256 ? 1 : PQ::M;   // subspaces per workgroup
+    static constexpr int kGroups = PQ::M / kSubs;            // workgroups that share a slice of tokens
+    static constexpr int DQ = PQ::DSUB / 4;                  // dimensions per lane group
+    static constexpr int kTiles = PQ::K / 16;                // codeword tiles per subspace
+    static constexpr int kBlocks = DQ;                       // 32-slot blocks of an operand
+    static constexpr int kNormSlot = 5 * DQ;
+    static constexpr int kLastSlot = 8 * kBlocks - DQ;
+    static constexpr int kPerCu = 2;                         // workgroups a CU's registers hold
+    // the LDS sums, [subspace][dimension][codeword]: a row stride that puts
+    // the four lane groups' dimensions 16 banks apart
+    static constexpr int kSumLd = PQ::K + (PQ::K >= 256 ? 4 : 2);
+    static_assert(2 * DQ * kSumLd % 64 == 16, "lane groups on distinct banks");
+    static_assert(kNormSlot + 3 <= kLastSlot && PQ::K % 16 == 0 && PQ::M % kSubs == 0, "operand layout");
+};
+
+__device__ __forceinline__ uint32_t pack_bf16(__bf16 lo, __bf16 hi) {
+    return static_cast<uint32_t>(__builtin_bit_cast(uint16_t, lo)) |
+           (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, hi)) << 16);
+}
+
+// x in 2^-41 fixed point, to nearest: the multiple of 2^-20 and, exactly, the
+// rest (|x| < 2^10).
+__device__ __forceinline__ unsigned long long to_fixed(float x) {
+    const float hi = rintf(x * kSumHi);
+    const float lo = rintf(fmaf(hi, -1.0f / kSumHi, x) * kSumLo);
+    const long long v = static_cast<long long>(static_cast<int>(hi)) * static_cast<long long>(kSumLo / kSumHi) +
+                        static_cast<int>(lo);
+    return static_cast<unsigned long long>(v);
+}
+
+template <typename T, typename PQ, bool kTrain>
+__global__ __launch_bounds__(kSubThreads) void subspace_kernel(
+    Dims D, BatchInts lo, BatchInts hi, KV kv, const float* __restrict__ centroids,
+    const float* __restrict__ codebooks, const int32_t* __restrict__ ids_tm,
+    const float* __restrict__ norms_tm, int n_pair, int per, uint8_t* __restrict__ codes_tm,
+    float* __restrict__ dist_f, unsigned long long* __restrict__ sums, uint32_t* __restrict__ counts) {
+    using L = SubLayout<PQ>;
+    constexpr int M = PQ::M, K = PQ::K, DS = PQ::DSUB, DQ = L::DQ, NB = L::kBlocks, CT = L::kTiles;
+    constexpr int kSubs = L::kSubs;
+    __shared__ uint4 op[kSubs * CT * NB * kWave];                  // codeword operands, in operand order
+    __shared__ unsigned long long sum[kTrain ? kSubs * DS * L::kSumLd : 1];
+    __shared__ uint32_t cnt[kTrain ? kSubs * K : 1];
+    // the kGroups workgroups of a slice have ids congruent mod 8: one XCD,
+    // whose L2 then serves the slice's keys and lists to all of them
+    const int j = blockIdx.x / 8;
+    const int grp = j % L::kGroups;
+    const int pair = j / L::kGroups * 8 + blockIdx.x % 8;
+    if (pair >= n_pair) return;
+    const int bg = pair % (D.B * D.Hkv);
+    const int slice = pair / (D.B * D.Hkv);
+    const int b = bg / D.Hkv, g = bg % D.Hkv;
+    const int t0 = lo.v[b] + slice * per;
+    const int t1 = min(t0 + per, hi.v[b]);
+    if (t0 >= t1) return;
+    const int m0 = grp * kSubs;
     const int tid = threadIdx.x;
     const int wave = tid / kWave;
     const int lane = lane_id();
     const int col = lane % 16;
     const int q = lane / 16;
 
-    // 1) residuals u - c_a into LDS, 16 threads per token (8 dimensions each);
-    //    the norms ||k|| out
-    const T* kb = static_cast<const T*>(kv.k) + b * kv.sb + g * kv.sh;
-    const float* cen = centroids + static_cast<int64_t>(bg) * D.n_list * kHeadDim;
+    // 1) the codeword operands: one lane's slots of one codeword per thread
+    const float* cb = codebooks + (static_cast<int64_t>(bg) * M + m0) * K * DS;
+    for (int i = tid; i < kSubs * K * 4; i += kSubThreads) {
+        const int z = i / 4 % K, sq = i % 4, ss = i / (4 * K);
+        const float* p = cb + (ss * K + z) * DS;
+        __bf16 part[3][DQ];
+        double p2 = 0.0;
 #pragma unroll
-    for (int it = 0; it < kAsgTok / 16; ++it) {
-        const int tk = it * 16 + tid / 16;
-        const int x0 = (tid % 16) * 8;
-        float x[8];
-        int a = 0;
-        if (tk < nt) {
-            Load8<T>::run(kb + static_cast<int64_t>(t_base + tk) * kv.sn + x0, x);
-            a = min(max(ids_tm[row0 + tk], 0), D.n_list - 1);
-        } else {
+        for (int d = 0; d < DS; ++d) p2 += static_cast<double>(p[d]) * p[d];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) x[e] = 0.0f;
+        for (int e = 0; e < DQ; ++e) {
+            __bf16 x[3];
+            split_bf16(p[sq * DQ + e], x);
+#pragma unroll
+            for (int u = 0; u < 3; ++u) part[u][e] = x[u];
         }
-        float ss = 0.0f;
+        __bf16 np[3];
+        split_bf16(static_cast<float>(0.5 * p2), np);
+        __bf16 slot[8 * NB];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ss = fmaf(x[e], x[e], ss);
+        for (int u = 0; u < 8 * NB; ++u) slot[u] = static_cast<__bf16>(0.0f);
+        constexpr int kCodePart[5] = {2, 0, 1, 1, 0};
 #pragma unroll
-        for (int off = 1; off < 16; off <<= 1) ss += __shfl_xor(ss, off);
-        const float r = sqrtf(ss);
-        if (tid % 16 == 0 && tk < nt) norms_tm[row0 + tk] = r;
-        const float4* cp = reinterpret_cast<const float4*>(cen + static_cast<int64_t>(a) * kHeadDim + x0);
-        const float4 c0 = cp[0], c1 = cp[1];
-        const float cv[8] = {c0.x, c0.y, c0.z, c0.w, c1.x, c1.y, c1.z, c1.w};
+        for (int u = 0; u < 5; ++u)
 #pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] = tk < nt ? (r > 0.0f ? x[e] / r : 0.0f) - cv[e] : 0.0f;
-        float4* dst = reinterpret_cast<float4*>(rows + tk * kAsgLd + x0);
-        dst[0] = make_float4(x[0], x[1], x[2], x[3]);
-        dst[1] = make_float4(x[4], x[5], x[6], x[7]);
+            for (int e = 0; e < DQ; ++e) slot[u * DQ + e] = part[kCodePart[u]][e];
+        if (sq == 0) {
+#pragma unroll
+            for (int u = 0; u < 3; ++u) slot[L::kNormSlot + u] = np[2 - u];
+        }
+#pragma unroll
+        for (int e = 0; e < DQ; ++e) slot[L::kLastSlot + e] = part[0][e];
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) {
+            uint32_t w[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) w[u] = pack_bf16(slot[nb * 8 + 2 * u], slot[nb * 8 + 2 * u + 1]);
+            op[((ss * CT + z / 16) * NB + nb) * kWave + sq * 16 + z % 16] = make_uint4(w[0], w[1], w[2], w[3]);
+        }
+    }
+    if constexpr (kTrain) {
+        for (int i = tid; i < kSubs * DS * L::kSumLd; i += kSubThreads) sum[i] = 0ull;
+        for (int i = tid; i < kSubs * K; i += kSubThreads) cnt[i] = 0u;
     }
     __syncthreads();
-    // 2) the B operands: lane (col, q) of token tile tt holds dimensions
-    //    m DS + q S + s of its token, for every m and s
-    float bv[2][M * S];
-#pragma unroll
-    for (int tt = 0; tt < 2; ++tt) {
-        const float* src = rows + (wave * 32 + tt * 16 + col) * kAsgLd;
-#pragma unroll
-        for (int m = 0; m < M; ++m)
-#pragma unroll
-            for (int s2 = 0; s2 < S; ++s2) bv[tt][m * S + s2] = src[m * DS + q * S + s2];
-    }
 
-    // 3) the subspaces, SR at a time through LDS
-    const float* cb = codebooks + static_cast<int64_t>(bg) * M * K * DS;
+    // 2) the slice's tokens
+    const T* kb = static_cast<const T*>(kv.k) + b * kv.sb + g * kv.sh;
+    const float* cen = centroids + static_cast<int64_t>(bg) * D.n_list * kHeadDim;
+    const int64_t row = static_cast<int64_t>(bg) * D.rcap;
+    const __bf16 one = static_cast<__bf16>(1.0f), zero = static_cast<__bf16>(0.0f);
+    for (int s0 = t0; s0 < t1; s0 += kSubStep) {
+        int tk[kSubTiles], a[kSubTiles];
+        float r[kSubTiles];
 #pragma unroll
-    for (int m0 = 0; m0 < M; m0 += SR) {   // unrolled: bv is indexed by m
-        __syncthreads();   // the residual rows or the previous round are no longer read
-        for (int i = tid; i < SR * K * DS; i += kAsgThreads) {
-            const int z = i / DS, x = i % DS;   // z over the round's SR * K codewords
-            rows[z * LD + x] = cb[static_cast<int64_t>(m0) * K * DS + i];
+        for (int tt = 0; tt < kSubTiles; ++tt) {
+            tk[tt] = s0 + (wave * kSubTiles + tt) * 16 + col;
+            const int t = min(tk[tt], t1 - 1);   // tokens past the slice repeat its last, unused
+            a[tt] = min(max(ids_tm[row + t], 0), D.n_list - 1);
+            r[tt] = norms_tm[row + t];
         }
-        __syncthreads();
-        for (int z = tid; z < SR * K; z += kAsgThreads) {
-            float ss = 0.0f;
+#pragma unroll 1
+        for (int ss = 0; ss < kSubs; ++ss) {
+            const int m = m0 + ss;
+            float res[kSubTiles][DQ], r2[kSubTiles];
+            bf8_t bv[kSubTiles][NB];
 #pragma unroll
-            for (int x = 0; x < DS; ++x) ss = fmaf(rows[z * LD + x], rows[z * LD + x], ss);
-            pn[z] = ss;
-        }
-        __syncthreads();
+            for (int tt = 0; tt < kSubTiles; ++tt) {
+                const int d0 = m * DS + q * DQ;
+                const T* kp = kb + static_cast<int64_t>(min(tk[tt], t1 - 1)) * kv.sn + d0;
+                const float* cp = cen + static_cast<int64_t>(a[tt]) * kHeadDim + d0;
+                float x[DQ], c[DQ];
+                load_slice<T, DQ>(kp, x);
+                load_slice<float, DQ>(cp, c);
+                // u = k / r to the last bit or so; the zero direction for a zero or
+                // overflowing norm, NaN where the row holds one or an infinity
+                const bool live = r[tt] > 0.0f && r[tt] < __builtin_huge_valf();
+                const float inv = __builtin_amdgcn_rcpf(r[tt]);
+                const float dead = r[tt] != r[tt] ? r[tt] : 0.0f;
+                r2[tt] = 0.0f;
+                __bf16 part[3][DQ];
 #pragma unroll
-        for (int mm = 0; mm < SR; ++mm) {
-            const int m = m0 + mm;
-            float best_d[2] = {__builtin_huge_valf(), __builtin_huge_valf()};
-            int best_z[2] = {0, 0};
-#pragma unroll 4
-            for (int ct = 0; ct < NCT; ++ct) {
-                const float* arow = rows + (mm * K + ct * 16 + col) * LD + q * S;
-                asg_v4f acc[2] = {asg_v4f{0.0f, 0.0f, 0.0f, 0.0f}, asg_v4f{0.0f, 0.0f, 0.0f, 0.0f}};
+                for (int e = 0; e < DQ; ++e) {
+                    const float qt = x[e] * inv;
+                    const float u = live ? fmaf(fmaf(-qt, r[tt], x[e]), inv, qt) : x[e] * dead;
+                    res[tt][e] = u - c[e];
+                    r2[tt] = fmaf(res[tt][e], res[tt][e], r2[tt]);
+                    __bf16 y[3];
+                    split_bf16(-res[tt][e], y);
 #pragma unroll
-                for (int s2 = 0; s2 < S; ++s2) {
-                    const float a = arow[s2];
-#pragma unroll
-                    for (int tt = 0; tt < 2; ++tt)
-                        acc[tt] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, bv[tt][m * S + s2], acc[tt], 0, 0, 0);
+                    for (int i = 0; i < 3; ++i) part[i][e] = y[i];
                 }
+                __bf16 slot[8 * NB];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const int zl = ct * 16 + 4 * q + i;   // codeword of row 4 q + i
-                    const float p2 = pn[mm * K + zl];
+                for (int u = 0; u < 8 * NB; ++u) slot[u] = zero;
+                constexpr int kResPart[5] = {0, 2, 1, 0, 1};
 #pragma unroll
-                    for (int tt = 0; tt < 2; ++tt) sub_fold(best_d[tt], best_z[tt], fmaf(-2.0f, acc[tt][i], p2), zl);
+                for (int u = 0; u < 5; ++u)
+#pragma unroll
+                    for (int e = 0; e < DQ; ++e) slot[u * DQ + e] = part[kResPart[u]][e];
+#pragma unroll
+                for (int u = 0; u < 3; ++u) slot[L::kNormSlot + u] = one;
+#pragma unroll
+                for (int e = 0; e < DQ; ++e) slot[L::kLastSlot + e] = part[0][e];
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    uint32_t w[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) w[u] = pack_bf16(slot[nb * 8 + 2 * u], slot[nb * 8 + 2 * u + 1]);
+                    bv[tt][nb] = __builtin_bit_cast(bf8_t, make_uint4(w[0], w[1], w[2], w[3]));
                 }
             }
+            // half squared distances (as bits) from here on
+            f4_t half_r2[kSubTiles];
+            constexpr int kAtOnce = CT < 2 ? CT : 2;   // codeword tiles per comparison
+            constexpr int kOuts = 4 * kAtOnce;
+            int best[kSubTiles], best_z[kSubTiles], keep[kSubTiles][kOuts];   // keep: the best group's values
 #pragma unroll
-            for (int tt = 0; tt < 2; ++tt) {
-                float r2 = 0.0f;   // ||r^(m)||^2 of the lane's token, over the 4 lane groups
+            for (int tt = 0; tt < kSubTiles; ++tt) {
+                r2[tt] += __shfl_xor(r2[tt], 16);
+                r2[tt] += __shfl_xor(r2[tt], 32);
+                const float h = 0.5f * r2[tt];
+                half_r2[tt] = f4_t{h, h, h, h};
+            }
+            const uint4* ops = op + ss * CT * NB * kWave + lane;
+            auto group = [&](int ct0, bool first) {
+                f4_t acc[kAtOnce][kSubTiles];
 #pragma unroll
-                for (int s2 = 0; s2 < S; ++s2) r2 = fmaf(bv[tt][m * S + s2], bv[tt][m * S + s2], r2);
+                for (int ct = 0; ct < kAtOnce; ++ct)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const bf8_t av = __builtin_bit_cast(bf8_t, ops[((ct0 + ct) * NB + nb) * kWave]);
+#pragma unroll
+                        for (int tt = 0; tt < kSubTiles; ++tt)
+                            acc[ct][tt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+                                av, bv[tt][nb], nb == 0 ? half_r2[tt] : acc[ct][tt], 0, 0, 0);
+                    }
+#pragma unroll
+                for (int tt = 0; tt < kSubTiles; ++tt) {
+                    int v[kOuts], m1 = __float_as_int(acc[0][tt][0]);
+#pragma unroll
+                    for (int u = 0; u < kOuts; ++u) v[u] = __float_as_int(acc[u / 4][tt][u % 4]);
+#pragma unroll
+                    for (int u = 1; u + 1 < kOuts; u += 2) m1 = min(min(v[u], v[u + 1]), m1);
+                    m1 = min(m1, v[kOuts - 1]);
+                    // strictly below: the first of equal groups stays
+                    const bool down = first || m1 < best[tt];
+                    best[tt] = first ? m1 : min(best[tt], m1);
+                    best_z[tt] = down ? ct0 : best_z[tt];
+#pragma unroll
+                    for (int u = 0; u < kOuts; ++u) keep[tt][u] = down ? v[u] : keep[tt][u];
+                }
+            };
+            group(0, true);
+            // not unrolled: the compiler would keep the operands of every tile
+            // in registers across the steps
+#pragma unroll 1
+            for (int ct0 = kAtOnce; ct0 < CT; ct0 += kAtOnce) group(ct0, false);
+#pragma unroll
+            for (int tt = 0; tt < kSubTiles; ++tt) {
+                int e = 0;   // the first of the group's values that is the smallest
+#pragma unroll
+                for (int u = kOuts - 1; u >= 0; --u) e = keep[tt][u] == best[tt] ? u : e;
+                best_z[tt] = (best_z[tt] + e / 4) * 16 + 4 * q + e % 4;
 #pragma unroll
                 for (int off = 16; off < kWave; off <<= 1) {
-                    r2 += __shfl_xor(r2, off);
-                    const float od = __shfl_xor(best_d[tt], off);
+                    const int od = __shfl_xor(best[tt], off);
                     const int oz = __shfl_xor(best_z[tt], off);
-                    sub_fold(best_d[tt], best_z[tt], od, oz);
+                    if (od < best[tt] || (od == best[tt] && oz < best_z[tt])) {
+                        best[tt] = od;
+                        best_z[tt] = oz;
+                    }
                 }
-                const int tk = wave * 32 + tt * 16 + col;
-                if (q == 0 && tk < nt) {
-                    codes_tm[(row0 + tk) * M + m] = static_cast<uint8_t>(best_z[tt]);
-                    if (dist_f) dist_f[(row0 + tk) * M + m] = fmaxf(best_d[tt] + r2, 0.0f);
+                if (tk[tt] >= t1) continue;
+                if constexpr (kTrain) {
+                    bool nan = false;
+#pragma unroll
+                    for (int e = 0; e < DQ; ++e) {
+                        nan = nan || !(fabsf(res[tt][e]) <= 4.0f);
+                        atomicAdd(&sum[(ss * DS + q * DQ + e) * L::kSumLd + best_z[tt]], to_fixed(nan ? 0.0f : res[tt][e]));
+                    }
+                    if (q == 0) {
+                        atomicAdd(&cnt[ss * K + best_z[tt]], 1u);
+                        dist_f[(static_cast<int64_t>(bg) * M + m) * D.rcap + tk[tt]] = fmaxf(2.0f * __int_as_float(best[tt]), 0.0f);
+                    }
+                    if (nan) atomicOr(&cnt[ss * K + best_z[tt]], kSumNan);
+                } else {
+                    if (q == 0) codes_tm[(row + tk[tt]) * M + m] = static_cast<uint8_t>(best_z[tt]);
                 }
             }
+        }
+    }
+    if constexpr (kTrain) {
+        __syncthreads();
+        const int64_t pz = (static_cast<int64_t>(bg) * M + m0) * K;
+        for (int i = tid; i < kSubs * K * DS; i += kSubThreads) {
+            const unsigned long long v = sum[(i / (K * DS) * DS + i % DS) * L::kSumLd + i / DS % K];
+            if (v) atomicAdd(&sums[pz * DS + i], v);
+        }
+        for (int i = tid; i < kSubs * K; i += kSubThreads) {
+            const uint32_t n = cnt[i];
+            if (n & ~kSumNan) atomicAdd(&counts[pz + i], n & ~kSumNan);
+            if (n & kSumNan) atomicOr(&counts[pz + i], kSumNan);
         }
     }
 }
 
-hipError_t launch_subspace(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
-                           const KV& kv, const float* centroids, const float* codebooks,
-                           const int32_t* ids_tm, uint8_t* codes_tm, float* norms_tm, float* dist_f,
-                           hipStream_t s) {
-    if (max_n <= 0) return hipSuccess;
-    const dim3 grid((max_n + kAsgTok - 1) / kAsgTok, D.Hkv, D.B);
-#define PQHSA_SUB(TT, PQT)                                                                      \
-    hipLaunchKernelGGL((subspace_kernel<TT, PQT>), grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv, \
-                       centroids, codebooks, ids_tm, codes_tm, norms_tm, dist_f)
-    if (kv.bf16) {
-        if (D.pq_bits == 4) PQHSA_SUB(bf16_t, Pq4); else PQHSA_SUB(bf16_t, Pq8);
-    } else {
-        if (D.pq_bits == 4) PQHSA_SUB(float, Pq4); else PQHSA_SUB(float, Pq8);
+// The codewords from a training pass's sums: the mean of each one's members
+// (an empty one keeps its value, the re-seeding replaces it).
+__global__ __launch_bounds__(256) void codewords_kernel(int64_t n, int dims, const unsigned long long* __restrict__ sums,
+                                                        const uint32_t* __restrict__ counts,
+                                                        float* __restrict__ out) {
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const uint32_t c = counts[i / dims];
+    if (c & kSumNan) {
+        out[i] = __builtin_nanf("");
+    } else if (c) {
+        const double s = static_cast<double>(static_cast<long long>(sums[i])) / static_cast<double>(kSumLo);
+        out[i] = static_cast<float>(s / c);
     }
-#undef PQHSA_SUB
+}
+
+template <typename T, typename PQ>
+static hipError_t launch_subspace_t(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
+                                    const KV& kv, const float* centroids, float* codebooks,
+                                    const int32_t* ids_tm, uint8_t* codes_tm, const float* norms_tm,
+                                    const BuildBufs& bb, bool train, hipStream_t s) {
+    using L = SubLayout<PQ>;
+    // slices of a KV head's tokens: one round of the workgroups a CU holds, but
+    // no slice of fewer than four steps
+    const int bgs = D.B * D.Hkv;
+    const int n_cu = device_cu_count() > 0 ? device_cu_count() : 1;
+    const int want = std::max(1, L::kPerCu * n_cu / (bgs * L::kGroups));
+    const int most = (max_n + 4 * kSubStep - 1) / (4 * kSubStep);
+    const int slices = std::min(want, most);
+    const int per = ((max_n + slices - 1) / slices + kSubStep - 1) / kSubStep * kSubStep;
+    const int n_pair = bgs * ((max_n + per - 1) / per);
+    const dim3 grid((n_pair + 7) / 8 * 8 * L::kGroups);
+    if (!train) {
+        hipLaunchKernelGGL((subspace_kernel<T, PQ, false>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv,
+                           centroids, codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, nullptr, nullptr, nullptr);
+        return hipGetLastError();
+    }
+    const int64_t n = static_cast<int64_t>(bgs) * PQ::M * PQ::K;
+    hipError_t e = hipMemsetAsync(bb.sums, 0, n * PQ::DSUB * sizeof(unsigned long long), s);
+    if (e == hipSuccess) e = hipMemsetAsync(bb.counts, 0, n * sizeof(uint32_t), s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((subspace_kernel<T, PQ, true>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv, centroids,
+                       codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, bb.dist_f, bb.sums, bb.counts);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(codewords_kernel, dim3(static_cast<unsigned>((n * PQ::DSUB + 255) / 256)), dim3(256), 0, s,
+                       n * PQ::DSUB, PQ::DSUB, bb.sums, bb.counts, codebooks);
     return hipGetLastError();
 }
 
+hipError_t launch_subspace(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
+                           const KV& kv, const float* centroids, float* codebooks,
+                           const int32_t* ids_tm, uint8_t* codes_tm, const float* norms_tm,
+                           const BuildBufs& bb, bool train, hipStream_t s) {
+    if (max_n <= 0) return hipSuccess;
+#define PQHSA_SUB(TT, PQT)                                                                            \
+    launch_subspace_t<TT, PQT>(D, lo, hi, max_n, kv, centroids, codebooks, ids_tm, codes_tm, norms_tm, bb, train, s)
+    if (kv.bf16) return D.pq_bits == 4 ? PQHSA_SUB(bf16_t, Pq4) : PQHSA_SUB(bf16_t, Pq8);
+    return D.pq_bits == 4 ? PQHSA_SUB(float, Pq4) : PQHSA_SUB(float, Pq8);
+#undef PQHSA_SUB
+}
+
 hipError_t launch_assign(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
-                         const KV& kv, const float* centroids, void* split, int32_t* ids_tm,
+                         const KV& kv, const float* centroids, const BuildBufs& bb, int32_t* ids_tm,
                          float* norms_tm, float* dist_c, hipStream_t s) {
     if (max_n <= 0) return hipSuccess;
     const int n_tile = (D.n_list + kTileCen - 1) / kTileCen;
-    __bf16* parts = static_cast<__bf16*>(split);
+    __bf16* parts = static_cast<__bf16*>(bb.split);
     hipLaunchKernelGGL(split_centers_kernel, dim3(n_tile, D.B * D.Hkv), dim3(kTileCen * 8), 0, s, D, centroids,
                        parts);
-    const hipError_t e = hipGetLastError();
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    e = hipMemsetAsync(bb.n_near, 0, static_cast<size_t>(D.B) * D.Hkv * sizeof(uint32_t), s);
     if (e != hipSuccess) return e;
     const int tok = kAsgWaves * 32 * (kv.bf16 ? AsgTokens<bf16_t>::kTiles : AsgTokens<float>::kTiles);
     const dim3 grid((max_n + tok - 1) / tok, D.Hkv, D.B);
-    if (kv.bf16)
-        hipLaunchKernelGGL(assign_kernel<bf16_t>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv, parts, n_tile,
-                           ids_tm, norms_tm, dist_c);
-    else
-        hipLaunchKernelGGL(assign_kernel<float>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv, parts, n_tile,
-                           ids_tm, norms_tm, dist_c);
+    const dim3 near_grid(std::min(kNearWgs, (max_n + kNearTok - 1) / kNearTok), D.Hkv, D.B);
+#define PQHSA_ASSIGN(TT)                                                                                    \
+    do {                                                                                                    \
+        hipLaunchKernelGGL(assign_kernel<TT>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv, parts, n_tile,  \
+                           ids_tm, norms_tm, dist_c, bb.order, bb.n_near);                                  \
+        e = hipGetLastError();                                                                              \
+        if (e != hipSuccess) return e;                                                                      \
+        hipLaunchKernelGGL(nearest_kernel<TT>, near_grid, dim3(kNearThreads), 0, s, D, kv, centroids,       \
+                           bb.order, bb.n_near, ids_tm, dist_c);                                            \
+    } while (0)
+    if (kv.bf16) PQHSA_ASSIGN(bf16_t);
+    else PQHSA_ASSIGN(float);
+#undef PQHSA_ASSIGN
     return hipGetLastError();
 }
 

@@ -274,19 +274,6 @@ hipError_t static_scratch(void** ptr);
 // the token-weighted mean of the list means per (b, g): the global value
 // mean over R_b of variant C
 hipError_t launch_glob_mean(const Dims& D, const Index& ix, float* glob, hipStream_t s);
-// The coarse assignment of the build on the matrix cores: the nearest center
-// of every token of R_b (ids_tm), its norm, and its squared distance (dist_c,
-// or null). split: split_center_bytes of scratch.
-hipError_t launch_assign(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
-                         const KV& kv, const float* centroids, void* split, int32_t* ids_tm,
-                         float* norms_tm, float* dist_c, hipStream_t s);
-size_t split_center_bytes(const Dims& D);
-// The codeword search of the build on the matrix cores, for tokens whose
-// lists are in ids_tm: norms, codes and the chosen distances (dist_f or null).
-hipError_t launch_subspace(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
-                           const KV& kv, const float* centroids, const float* codebooks,
-                           const int32_t* ids_tm, uint8_t* codes_tm, float* norms_tm, float* dist_f,
-                           hipStream_t s);
 // the update's encoding of the tokens leaving the window: one workgroup per token
 hipError_t launch_encode_update(const Dims& D, const BatchInts& lo, const BatchInts& hi,
                                 int max_new, const KV& kv, const float* centroids,
@@ -294,30 +281,46 @@ hipError_t launch_encode_update(const Dims& D, const BatchInts& lo, const BatchI
                                 float* norms_tm, hipStream_t s);
 // index build steps (k-means over the tokens [lo[b], hi[b]) of each (b, kv head))
 struct BuildBufs {
-    int32_t* order;      // [problems, rcap] tokens grouped by center, in id order within a center
-    int32_t* offs;       // [problems, n_centers + 1]
+    int32_t* order;      // [B, Hkv, rcap] tokens grouped by list, in id order within a list
+    int32_t* offs;       // [B, Hkv, n_list + 1]
     float* dist_c;       // [B, Hkv, rcap]
-    float* dist_f;       // [B, Hkv, rcap, M]
-    int32_t* seg_hist;   // [problems, segments of 4096 tokens, keys] counts, then first positions
-                         //   (problems with at most 1024 keys)
-    void* split;         // split_center_bytes
+    float* dist_f;       // [B, Hkv, M, rcap]
+    unsigned long long* sums;   // [B, Hkv, M, K, d / M] residual sums of a training pass (fixed point)
+    uint32_t* counts;           // [B, Hkv, M, K] members of a codeword
+    int32_t* seg_hist;   // [B, Hkv, segments of 4096 tokens, n_list] counts, then first positions
+                         //   (at most 1024 lists)
+    void* split;         // split_center_bytes: the centers as matrix-core operands
+    uint32_t* n_near;    // [B, Hkv] tokens listed (in order) by an assignment pass as near ties
 };
+// The coarse assignment of the build on the matrix cores: the nearest center
+// of every token of R_b (ids_tm), its norm, and its squared distance (dist_c,
+// or null). bb.order, bb.n_near and bb.split are scratch.
+hipError_t launch_assign(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
+                         const KV& kv, const float* centroids, const BuildBufs& bb, int32_t* ids_tm,
+                         float* norms_tm, float* dist_c, hipStream_t s);
+size_t split_center_bytes(const Dims& D);
+// The codeword search of the build on the matrix cores, for tokens whose
+// lists and norms are known. A training pass (train) moves the codewords to the
+// means of their tokens and leaves the chosen distances (dist_f) and member
+// counts for the re-seeding; otherwise the codes are written.
+hipError_t launch_subspace(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_n,
+                           const KV& kv, const float* centroids, float* codebooks,
+                           const int32_t* ids_tm, uint8_t* codes_tm, const float* norms_tm,
+                           const BuildBufs& bb, bool train, hipStream_t s);
 constexpr int kBuildSegTok = 4096;   // tokens per segment of the build's grouping
-// kind: 0 coarse centers over directions, 1 codewords over residual slices,
-// 2 list means over values
-// The stable grouping of launch_group for problems of at most 1024 keys,
-// over segments of kBuildSegTok tokens: order [problems, rcap] (tokens by key,
-// in id order within a key) and offs [problems, keys + 1]; seg_hist holds
-// problems x ceil(max |R_b| / kBuildSegTok) x keys ints of scratch.
-hipError_t launch_group_segments(const Dims& D, const BatchInts& lo, const BatchInts& hi, int kind,
-                                 const int32_t* ids_tm, const uint8_t* codes_tm, int32_t* seg_hist,
-                                 int32_t* order, int32_t* offs, hipStream_t s);
-hipError_t launch_group(const Dims& D, const BatchInts& lo, const BatchInts& hi, int kind,
-                        const int32_t* ids_tm, const uint8_t* codes_tm, const BuildBufs& bb,
-                        hipStream_t s);
-hipError_t launch_centers(const Dims& D, const BatchInts& lo, const BatchInts& hi, int kind,
-                          const KV& kv, const int32_t* ids_tm, const float* norms_tm,
-                          const float* centroids, const BuildBufs& bb, float* out, hipStream_t s);
+// The stable grouping of the tokens of each (b, kv head) by list, for at most
+// 1024 lists, over segments of kBuildSegTok tokens: order [B, Hkv, rcap] (tokens
+// by list, in id order within a list) and offs [B, Hkv, n_list + 1]; seg_hist
+// holds B x Hkv x ceil(max |R_b| / kBuildSegTok) x n_list ints of scratch.
+hipError_t launch_group_segments(const Dims& D, const BatchInts& lo, const BatchInts& hi,
+                                 const int32_t* ids_tm, int32_t* seg_hist, int32_t* order, int32_t* offs,
+                                 hipStream_t s);
+hipError_t launch_group(const Dims& D, const BatchInts& lo, const BatchInts& hi, const int32_t* ids_tm,
+                        const BuildBufs& bb, hipStream_t s);
+// the means of the grouped tokens' directions (kind 0) or values (kind 2)
+hipError_t launch_centers(const Dims& D, int kind, const KV& kv, const float* norms_tm, const BuildBufs& bb,
+                          float* out, hipStream_t s);
+// kind: 0 coarse centers over directions, 1 codewords over residual slices
 hipError_t launch_init_centers(const Dims& D, int kind, const KV& kv, const int32_t* init,
                                const int32_t* ids_tm, const float* norms_tm, const float* centroids,
                                float* out, hipStream_t s);

@@ -330,7 +330,7 @@ hipError_t launch_sort_lists(const Dims& D, const BatchInts& lo, const BatchInts
     if (D.n_list <= 1024 && scratch &&
         nseg * static_cast<size_t>(D.B) * D.Hkv * D.n_list <= scratch_ints) {
         // the build's segmented grouping, many workgroups per (b, g)
-        hipError_t e = launch_group_segments(D, lo, hi, 0, ids_tm, nullptr, scratch, perm, loff, s);
+        hipError_t e = launch_group_segments(D, lo, hi, ids_tm, scratch, perm, loff, s);
         if (e != hipSuccess) return e;
         hipLaunchKernelGGL(finish_lists_kernel, dim3((D.rcap + 255) / 256, D.B * D.Hkv), dim3(256), 0, s,
                            D, lo, hi, ids_tm, perm, pos_word, n_r_dev, n_seq_dev);
