@@ -70,7 +70,7 @@ struct pqhsa_ctx {
     Work w{};
     int nsplit_max = 0;
     float* dense_partial = nullptr;
-    int dense_nsplit = 0;
+    size_t dense_partials = 0;
     size_t codebook_floats = 0;   // per (b, kv head): K * d
 
     // options
@@ -293,7 +293,7 @@ pqhsa_status pqhsa_create(const pqhsa_shape* shape, pqhsa_ctx** out) {
     c->nsplit_max = (D.n_sink + D.n_local + kTailGrowth + shape->max_topk + D.attn_rows - 1) / D.attn_rows;
     if (c->nsplit_max < 1) c->nsplit_max = 1;
     const int n_bgc = (D.n_list + kBgLists - 1) / kBgLists;
-    c->dense_nsplit = (D.rcap + kDenseRows - 1) / kDenseRows;
+    c->dense_partials = std::max<size_t>(BQ * ((D.rcap + kDenseRows - 1) / kDenseRows), kDensePartials);
 
     Work& w = c->w;
     hipError_t ea = hipSuccess;
@@ -348,7 +348,7 @@ pqhsa_status pqhsa_create(const pqhsa_shape* shape, pqhsa_ctx** out) {
     A(dev_alloc(c, &w.row_shift, BQ));
     A(dev_alloc(c, &w.row_flag, BQ));
     A(dev_alloc(c, &w.partial, BQ * (c->nsplit_max + n_bgc) * kPartStride));
-    A(dev_alloc(c, &c->dense_partial, BQ * c->dense_nsplit * kPartStride));
+    A(dev_alloc(c, &c->dense_partial, c->dense_partials * kPartStride));
     if (ea != hipSuccess) {
         const bool oom = ea == hipErrorOutOfMemory || ea == hipErrorMemoryAllocation;
         char msg[256];
@@ -804,7 +804,7 @@ pqhsa_status pqhsa_dense_decode(pqhsa_ctx* c, const void* q, const void* k, cons
             return fail(c, PQHSA_ERR_INVALID_ARGUMENT, "seq_lens[%d] = %d outside [1, max_seq]", b, seq_lens[b]);
         lens.v[b] = seq_lens[b];
     }
-    hipError_t e = launch_dense(c->D, kv, lens, c->dense_partial, out, c->dense_nsplit, stream);
+    hipError_t e = launch_dense(c->D, kv, lens, c->dense_partial, c->dense_partials, out, stream);
     if (e != hipSuccess) return hip_fail(c, e, "enqueueing the dense decode kernels");
     return PQHSA_OK;
 }
@@ -856,7 +856,8 @@ pqhsa_status pqhsa_dense_decode_noalloc(int32_t batch, int32_t n_q_heads, int32_
     D.Hkv = n_kv_heads;
     D.G = G;
     D.inv_sqrt_d = static_cast<float>(1.0 / std::sqrt(static_cast<double>(kHeadDim)));
-    e = launch_dense(D, kv, lens, static_cast<float*>(scratch), out, nsplit, stream);
+    e = launch_dense(D, kv, lens, static_cast<float*>(scratch),
+                     static_scratch_bytes() / (kPartStride * sizeof(float)), out, stream);
     if (e != hipSuccess)
         return fail(nullptr, PQHSA_ERR_HIP, "enqueueing the dense decode kernels: %s", hipGetErrorString(e));
     return PQHSA_OK;

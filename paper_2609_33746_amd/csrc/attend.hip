@@ -598,9 +598,38 @@ __device__ __forceinline__ void dense_load(Raw8<T> (&kr)[R], Raw8<T> (&vr)[R], c
 #pragma unroll
     for (int i = 0; i < R; ++i) {
         const int64_t t = min(base + i * kStreams, t1 - 1);
-        kr[i].load(kb + t * sn);
-        vr[i].load(vb + t * sn);
+        kr[i].load_nt(kb + t * sn);
+        vr[i].load_nt(vb + t * sn);
     }
+}
+
+// Cache rows per dense split. The kernel is bound by memory once about two
+// workgroups per CU stream (fewer leave loads out of flight, more pay for their
+// partials): as many splits as make that many workgroups, the same for every
+// KV head. Measured with 2048 rows always -> this, us per call (32 / 8 heads,
+// bf16): 4K tokens 62 -> 14, 16K 62 -> 21, 32K 61 -> 35, 128K 100 -> 100, four
+// sequences of 50001 179 -> 155. Sequences of different lengths take twice the
+// splits where these are long, so that the short ones' share spreads (8 of
+// 15K-30K: 151 -> 144), and none is longer than kDenseRowsMax (16 of
+// 64K-128K: 1176 -> 1143; with nontemporal loads 1007).
+static int dense_split_rows(const Dims& D, const BatchInts& lens, size_t partials) {
+    int n_min = lens.v[0], n_max = lens.v[0];
+    for (int b = 1; b < D.B; ++b) {
+        n_min = lens.v[b] < n_min ? lens.v[b] : n_min;
+        n_max = lens.v[b] > n_max ? lens.v[b] : n_max;
+    }
+    const int units = D.B * D.Hkv;
+    auto rows_for = [&](int wgs) {
+        const int nsplit = wgs / units > 1 ? wgs / units : 1;
+        const int rows = ((n_max + nsplit - 1) / nsplit + kDenseStep - 1) / kDenseStep * kDenseStep;
+        return rows < kDenseRowsMin ? kDenseRowsMin : rows > kDenseRowsMax ? kDenseRowsMax : rows;
+    };
+    const int n_cu = device_cu_count() > 0 ? device_cu_count() : 1;
+    int rows = rows_for(2 * n_cu);
+    if (n_min < n_max && rows > kDenseRowsMax / 4 && rows < kDenseRowsMax) rows = rows_for(4 * n_cu);
+    // a buffer that holds no more keeps to the splits it was sized for
+    if (static_cast<size_t>(units) * D.G * ((n_max + rows - 1) / rows) > partials) rows = kDenseRows;
+    return rows;
 }
 
 // Fold R rows into o with a lazily moved shift: o.m changes only when a row's
@@ -655,17 +684,17 @@ __device__ __forceinline__ void dense_rows(const DenseQ<T, G>& qv, Online (&o)[G
 template <typename T, int G>
 __global__ __launch_bounds__(kAttnThreads) void dense_kernel(Dims D, KV kv, BatchInts lens,
                                                              float* __restrict__ partial,
-                                                             int nsplit_max) {
+                                                             int nsplit, int rows) {
     __shared__ float sm[kStreams], sz[kStreams];
     __shared__ float sacc[kStreams * kHeadDim];
-    const int bg = blockIdx.x / nsplit_max;
-    const int split = blockIdx.x % nsplit_max;
+    const int bg = blockIdx.x / nsplit;
+    const int split = blockIdx.x % nsplit;
     const int b = bg / D.Hkv;
     const int g = bg % D.Hkv;
     const int n = lens.v[b];
-    const int t0 = split * kDenseRows;
+    const int t0 = split * rows;
     if (t0 >= n) return;
-    const int t1 = min(t0 + kDenseRows, n);
+    const int t1 = min(t0 + rows, n);
     const int lane16 = threadIdx.x & 15;
     const int stream = threadIdx.x >> 4;
     DenseQ<T, G> qv;
@@ -692,38 +721,42 @@ __global__ __launch_bounds__(kAttnThreads) void dense_kernel(Dims D, KV kv, Batc
 #pragma unroll
     for (int hh = 0; hh < G; ++hh)
         block_combine(o[hh], sm, sz, sacc,
-                      partial + ((static_cast<int64_t>(b) * D.Hq + g * G + hh) * nsplit_max + split) *
+                      partial + ((static_cast<int64_t>(b) * D.Hq + g * G + hh) * nsplit + split) *
                                     kPartStride);
 }
 
 template <typename T, int G>
 static hipError_t launch_dense_t(const Dims& D, const KV& kv, const BatchInts& lens,
-                                 float* partial, int nsplit_max, hipStream_t s) {
-    hipLaunchKernelGGL((dense_kernel<T, G>), dim3(D.B * D.Hkv * nsplit_max), dim3(kAttnThreads), 0,
-                       s, D, kv, lens, partial, nsplit_max);
+                                 float* partial, int nsplit, int rows, hipStream_t s) {
+    hipLaunchKernelGGL((dense_kernel<T, G>), dim3(D.B * D.Hkv * nsplit), dim3(kAttnThreads), 0,
+                       s, D, kv, lens, partial, nsplit, rows);
     return hipGetLastError();
 }
 
 template <typename T>
 static hipError_t launch_dense_g(const Dims& D, const KV& kv, const BatchInts& lens,
-                                 float* partial, int nsplit_max, hipStream_t s) {
+                                 float* partial, int nsplit, int rows, hipStream_t s) {
     switch (D.G) {
-        case 1: return launch_dense_t<T, 1>(D, kv, lens, partial, nsplit_max, s);
-        case 2: return launch_dense_t<T, 2>(D, kv, lens, partial, nsplit_max, s);
-        case 4: return launch_dense_t<T, 4>(D, kv, lens, partial, nsplit_max, s);
-        case 8: return launch_dense_t<T, 8>(D, kv, lens, partial, nsplit_max, s);
+        case 1: return launch_dense_t<T, 1>(D, kv, lens, partial, nsplit, rows, s);
+        case 2: return launch_dense_t<T, 2>(D, kv, lens, partial, nsplit, rows, s);
+        case 4: return launch_dense_t<T, 4>(D, kv, lens, partial, nsplit, rows, s);
+        case 8: return launch_dense_t<T, 8>(D, kv, lens, partial, nsplit, rows, s);
         default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_dense(const Dims& D, const KV& kv, const BatchInts& lens, float* partial,
-                        float* out, int nsplit_max, hipStream_t s) {
-    hipError_t e = kv.bf16 ? launch_dense_g<bf16_t>(D, kv, lens, partial, nsplit_max, s)
-                           : launch_dense_g<float>(D, kv, lens, partial, nsplit_max, s);
+                        size_t partials, float* out, hipStream_t s) {
+    int n_max = 1;
+    for (int b = 0; b < D.B; ++b) n_max = lens.v[b] > n_max ? lens.v[b] : n_max;
+    const int rows = dense_split_rows(D, lens, partials);
+    const int nsplit = (n_max + rows - 1) / rows;
+    const hipError_t e = kv.bf16 ? launch_dense_g<bf16_t>(D, kv, lens, partial, nsplit, rows, s)
+                                 : launch_dense_g<float>(D, kv, lens, partial, nsplit, rows, s);
     if (e != hipSuccess) return e;
     BatchInts ne;
-    for (int b = 0; b < D.B; ++b) ne.v[b] = (lens.v[b] + kDenseRows - 1) / kDenseRows;
-    return launch_merge_parts(D, ne, partial, nsplit_max, 0, 0, out, nullptr, nullptr, s, KTiming{});
+    for (int b = 0; b < D.B; ++b) ne.v[b] = (lens.v[b] + rows - 1) / rows;
+    return launch_merge_parts(D, ne, partial, nsplit, 0, 0, out, nullptr, nullptr, s, KTiming{});
 }
 
 }  // namespace pqhsa

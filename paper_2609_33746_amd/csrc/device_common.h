@@ -46,6 +46,15 @@ struct Load8<bf16_t> {
     }
 };
 
+// 16 bytes that this launch reads once: a nontemporal load, which does not
+// displace what the caches hold and streams faster for it (the dense decode of
+// 16 sequences of 64K-128K tokens: 5.7 -> 6.2 TB/s).
+__device__ __forceinline__ uint4 load_once(const void* p) {
+    typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+    const u32x4 v = __builtin_nontemporal_load(static_cast<const u32x4*>(p));
+    return make_uint4(v.x, v.y, v.z, v.w);
+}
+
 // Raw (unconverted) 8-element slice of a row, so that many rows can be in
 // flight before any of them is converted.
 template <typename T>
@@ -58,6 +67,9 @@ struct Raw8<float> {
         a = *reinterpret_cast<const float4*>(p);
         b = *reinterpret_cast<const float4*>(p + 4);
     }
+    // plain: each of the two loads takes half of every line, and nontemporal
+    // ones fetched lines twice (16 sequences in fp32: 301 -> 355 us)
+    __device__ __forceinline__ void load_nt(const float* p) { load(p); }
     __device__ __forceinline__ void zero() {
         a = make_float4(0.f, 0.f, 0.f, 0.f);
         b = a;
@@ -72,6 +84,7 @@ template <>
 struct Raw8<bf16_t> {
     uint4 w;
     __device__ __forceinline__ void load(const bf16_t* p) { w = *reinterpret_cast<const uint4*>(p); }
+    __device__ __forceinline__ void load_nt(const bf16_t* p) { w = load_once(p); }
     __device__ __forceinline__ void zero() { w = make_uint4(0u, 0u, 0u, 0u); }
     __device__ __forceinline__ void to(float (&x)[8]) const {
         x[0] = bf16_lo(w.x); x[1] = bf16_hi(w.x);

@@ -42,7 +42,11 @@ constexpr int kMaxSeq = 1 << kPosBits;
 constexpr int kAttnRows = 128;     // exact-set rows per split, the larger of the two sizes
 constexpr int kAttnRowsSmall = 64; // the split of small exact sets (see attn_rows_for)
 constexpr int kBgLists = 64;       // lists per background workgroup
-constexpr int kDenseRows = 2048;   // cache rows per dense split
+constexpr int kDenseRows = 2048;     // cache rows per dense split that sizes the partial buffers
+constexpr int kDenseRowsMin = 128;   // rows per split of a call (see dense_split_rows)
+constexpr int kDenseRowsMax = 4096;
+constexpr int kDenseStep = 32;       // multiples of
+constexpr int kDensePartials = 8192; // partials a context's dense buffer holds at least
 constexpr int kPartStride = 132;   // floats per partial: m, Z, pad, pad, N[128]
 constexpr int kMaxRowParts = 512;  // partials per row (exact splits + background chunks)
 constexpr int kTailGrowth = 1024;  // tokens past the local window held exact between updates
@@ -264,8 +268,10 @@ hipError_t launch_attend(const Dims& D, const BatchArgs& ba, const KV& kv, const
                          const KTiming& tm = KTiming{});
 hipError_t launch_merge(const Dims& D, const BatchArgs& ba, const Work& w, float* out,
                         int nsplit_max, int variant, hipStream_t s, const KTiming& tm = KTiming{});
+// partials: split partials the buffer holds, at least one per row and kDenseRows
+// rows of the longest sequence
 hipError_t launch_dense(const Dims& D, const KV& kv, const BatchInts& lens, float* partial,
-                        float* out, int nsplit_max, hipStream_t s);
+                        size_t partials, float* out, hipStream_t s);
 // The fixed scratch array of the entry point that allocates nothing: its size,
 // and its device address on the current device (looked up on the first call
 // per device, then kept).
