@@ -176,8 +176,17 @@ __global__ __launch_bounds__(kAttnThreads) void attend_kernel(Dims D, BatchArgs 
 #pragma unroll
         for (int i = 0; i < kRowsPerStream; ++i) {
             if (tok[i] >= 0) {
-                kr[i].load(kb + roff[i]);
-                vr[i].load(vb + roff[i]);
+                // large budgets (the 128-row splits) gather past what the caches
+                // keep for the next call: read without displacing the rest
+                // (512K tokens, 1%: the call 96.7 -> 86.0 us; four sequences, 2%:
+                // 107.3 -> 103.1; small ones lose 1 us)
+                if constexpr (kRows == kAttnRows) {
+                    kr[i].load_nt(kb + roff[i]);
+                    vr[i].load_nt(vb + roff[i]);
+                } else {
+                    kr[i].load(kb + roff[i]);
+                    vr[i].load(vb + roff[i]);
+                }
             } else {
                 kr[i].zero();
                 vr[i].zero();
