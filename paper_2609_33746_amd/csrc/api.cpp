@@ -489,7 +489,9 @@ pqhsa_status pqhsa_index_update(pqhsa_ctx* c, const int32_t* new_seq_lens, const
     // norms into the new order
     c->prepared = false;
     hipError_t e = launch_encode_update(D, lo, hi, max_new, kv, c->centroids, c->codebooks,
-                                        c->ids_tm, c->codes_tm, c->norms_tm, stream);
+                                        c->ids_tm, c->codes_tm, c->norms_tm,
+                                        reinterpret_cast<float*>(c->w.comp_key), c->w.comp_pos,
+                                        static_cast<int64_t>(D.B) * D.Hq * D.rcap, stream);
     if (e == hipSuccess)
         e = launch_update_lists(D, lo, hi, kv, c->ids_tm, c->loff, c->perm, c->pos_word,
                                 c->loff_alt, c->shift, c->perm_alt, c->pos_alt, c->n_r_dev, c->n_seq_dev, c->means, c->mean_sums, stream);

@@ -280,11 +280,13 @@ hipError_t static_scratch(void** ptr);
 // the token-weighted mean of the list means per (b, g): the global value
 // mean over R_b of variant C
 hipError_t launch_glob_mean(const Dims& D, const Index& ix, float* glob, hipStream_t s);
-// the update's encoding of the tokens leaving the window: one workgroup per token
+// the update's encoding of the tokens leaving the window; part_d, part_i:
+// scratch of part_ints entries each, at least one per new token and KV head
 hipError_t launch_encode_update(const Dims& D, const BatchInts& lo, const BatchInts& hi,
                                 int max_new, const KV& kv, const float* centroids,
                                 const float* codebooks, int32_t* ids_tm, uint8_t* codes_tm,
-                                float* norms_tm, hipStream_t s);
+                                float* norms_tm, float* part_d, int32_t* part_i, int64_t part_ints,
+                                hipStream_t s);
 // index build steps (k-means over the tokens [lo[b], hi[b]) of each (b, kv head))
 struct BuildBufs {
     int32_t* order;      // [B, Hkv, rcap] tokens grouped by list, in id order within a list

@@ -2,14 +2,13 @@
 // are encoded into the existing lists, without re-clustering, and the list
 // means are refreshed over the grown lists.
 //
-//  * encode_one_kernel, one token per workgroup (updates of a few hundred
-//    tokens; the build's passes over all of R use the matrix-core search in
-//    the build's source): the key is split into
-//    its norm r and direction u (Section 3.1); u goes to the list with the
-//    nearest centroid, and each slice of the residual u - c_a to its nearest
-//    codeword. Squared Euclidean distances in fp32; ties go to the smaller
-//    list id or codeword index. Writes the token-major list id, codes (one
-//    code per byte) and norm.
+//  * encode_coarse_kernel and encode_fine_kernel: the key is split into its norm
+//    r and direction u (Section 3.1); u goes to the list with the nearest
+//    centroid, and each slice of the residual u - c_a to its nearest codeword.
+//    Squared Euclidean distances in fp32, summed in dimension order; ties go to
+//    the smaller list id or codeword index. Write the token-major list id, codes
+//    (one code per byte) and norm. (The build's passes over all of R use the
+//    matrix-core search in the build's source.)
 //  * means_update_kernel, after the merge below: one workgroup per (list,
 //    kv head, sequence) adds the new members' values to the list's float64
 //    value sum and writes the mean v_bar' = sum / (n_old + n_new) in fp32. The
@@ -18,6 +17,8 @@
 //
 // The list-major layout is then merged on the device (update_lists_kernel,
 // shift_positions_kernel below) and codes and norms gathered into it.
+#include <algorithm>
+
 #include "device_common.h"
 #include "pqhsa_internal.h"
 
@@ -33,107 +34,178 @@ __device__ __forceinline__ void argmin_fold(float& d, int& i, float od, int oi) 
     }
 }
 
-// argmin over the 64 lanes of a wave by (distance, id)
-__device__ __forceinline__ void wave_argmin64(float& d, int& i) {
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) {
-        const float od = __shfl_xor(d, off);
-        const int oi = __shfl_xor(i, off);
-        argmin_fold(d, i, od, oi);
-    }
-}
+// encode_coarse_kernel: kEncTok tokens against chunks of kEncCen centroids
+// staged in LDS; the workgroups of a token tile share the chunks out (gridDim.y
+// of them, so that an update of a few hundred tokens fills the chip), and each
+// writes its nearest centroid per token to part_d / part_i [B Hkv][token][share].
+// A thread holds 2 tokens x 4 centroids and adds their squared differences in
+// dimension order. Every centroid row then comes from L2 once per 32 tokens, not
+// once per token (one workgroup per token: 139 us at 256 tokens x 8 KV heads x
+// 1024 lists, against 33 + 12 us for the two kernels). Also writes the norms.
+constexpr int kEncTok = 32;
+constexpr int kEncCen = 64;
+constexpr int kEncLd = kHeadDim + 4;   // LDS row stride: 16 rows on distinct 16-byte bank groups
 
-// One workgroup per token: for updates of a few hundred tokens, where
-// 64-token tiles would leave most of the chip idle. The same choices as
-// the build's search up to fp32 rounding order.
-template <typename T, typename PQ>
-__global__ __launch_bounds__(kEncThreads) void encode_one_kernel(
-    Dims D, BatchInts lo, BatchInts hi, const T* __restrict__ kcache, int64_t sb, int64_t sh,
-    int64_t sn, const float* __restrict__ centroids, const float* __restrict__ codebooks,
-    int32_t* __restrict__ ids_tm, uint8_t* __restrict__ codes_tm, float* __restrict__ norms_tm) {
-    __shared__ float su[kHeadDim];           // u, then the residual u - c_a
-    __shared__ float sdist[kMaxLists];       // coarse distances, then [M][K] fine ones
-    __shared__ float wsum[kEncThreads / kWave];
-    __shared__ int sa;
-    static_assert(PQ::M * PQ::K <= kMaxLists, "fine distances fit the coarse buffer");
-    const int b = blockIdx.z;
-    const int g = blockIdx.y;
-    const int t = lo.v[b] + static_cast<int>(blockIdx.x);
-    if (t >= hi.v[b]) return;
-    const int bg = b * D.Hkv + g;
+template <typename T>
+__global__ __launch_bounds__(kEncThreads) void encode_coarse_kernel(
+    Dims D, BatchInts lo, BatchInts hi, const T* __restrict__ kcache, int64_t sb, int64_t sh, int64_t sn,
+    const float* __restrict__ centroids, float* __restrict__ part_d, int32_t* __restrict__ part_i,
+    int64_t part_stride, float* __restrict__ norms_tm) {
+    __shared__ float4 us4[kEncTok * kEncLd / 4];
+    __shared__ float4 cs4[kEncCen * kEncLd / 4];
+    const int bg = blockIdx.z;
+    const int b = bg / D.Hkv, g = bg % D.Hkv;
+    const int t0 = lo.v[b] + static_cast<int>(blockIdx.x) * kEncTok;
+    if (t0 >= hi.v[b]) return;
+    const int nt = min(kEncTok, hi.v[b] - t0);
     const int tid = threadIdx.x;
     const int wave = tid / kWave;
     const int lane = lane_id();
-
-    // r = ||k||, u = k / r (u = 0 for a zero key)
-    float kx = 0.0f;
-    if (tid < kHeadDim) kx = load1<T>(kcache + b * sb + g * sh + t * sn + tid);
-    float ss = kx * kx;
-#pragma unroll
-    for (int off = kWave / 2; off > 0; off >>= 1) ss += __shfl_xor(ss, off);
-    if (lane == 0) wsum[wave] = ss;
-    __syncthreads();
-    float tot = 0.0f;
-#pragma unroll
-    for (int w = 0; w < kEncThreads / kWave; ++w) tot += wsum[w];
-    const float r = sqrtf(tot);
-    if (tid < kHeadDim) su[tid] = r > 0.0f ? kx / r : 0.0f;
-    __syncthreads();
-
-    // nearest centroid
-    const float* cen = centroids + static_cast<int64_t>(bg) * D.n_list * kHeadDim;
-    for (int j = tid; j < D.n_list; j += kEncThreads) {
-        const float4* c4 = reinterpret_cast<const float4*>(cen + static_cast<int64_t>(j) * kHeadDim);
-        float acc = 0.0f;
-#pragma unroll 8
-        for (int x = 0; x < kHeadDim / 4; ++x) {
-            const float4 c = c4[x];
-            const float d0 = su[4 * x] - c.x, d1 = su[4 * x + 1] - c.y;
-            const float d2 = su[4 * x + 2] - c.z, d3 = su[4 * x + 3] - c.w;
-            acc = fmaf(d0, d0, acc);
-            acc = fmaf(d1, d1, acc);
-            acc = fmaf(d2, d2, acc);
-            acc = fmaf(d3, d3, acc);
+    // r = ||k||, u = k / r (u = 0 for a zero key): one wave per token
+    float* us = reinterpret_cast<float*>(us4);
+    for (int i = wave; i < kEncTok; i += kEncThreads / kWave) {
+        float k0 = 0.0f, k1 = 0.0f;
+        if (i < nt) {
+            const T* row = kcache + b * sb + g * sh + static_cast<int64_t>(t0 + i) * sn;
+            k0 = load1<T>(row + lane);
+            k1 = load1<T>(row + kWave + lane);
         }
-        sdist[j] = acc;
+        float s0 = k0 * k0, s1 = k1 * k1;
+#pragma unroll
+        for (int off = kWave / 2; off > 0; off >>= 1) {
+            s0 += __shfl_xor(s0, off);
+            s1 += __shfl_xor(s1, off);
+        }
+        const float r = sqrtf(s0 + s1);
+        us[i * kEncLd + lane] = r > 0.0f ? k0 / r : 0.0f;
+        us[i * kEncLd + kWave + lane] = r > 0.0f ? k1 / r : 0.0f;
+        if (lane == 0 && i < nt && blockIdx.y == 0) norms_tm[static_cast<int64_t>(bg) * D.rcap + t0 + i] = r;
     }
-    __syncthreads();
-    if (wave == 0) {
-        float bd = __builtin_huge_valf();
-        int bi = 0;   // a valid id even if every distance is NaN
-        for (int j = lane; j < D.n_list; j += kWave) argmin_fold(bd, bi, sdist[j], j);
-        wave_argmin64(bd, bi);
-        if (lane == 0) sa = bi;
+    const int tx = tid % 16;          // centroids tx, tx + 16, tx + 32, tx + 48 of a chunk
+    const int ty = tid / 16 * 2;      // tokens ty, ty + 1
+    const float* cen = centroids + static_cast<int64_t>(bg) * D.n_list * kHeadDim;
+    float best_d[2] = {__builtin_huge_valf(), __builtin_huge_valf()};
+    int best_i[2] = {0, 0};   // a valid id even if every distance is NaN
+    for (int c0 = static_cast<int>(blockIdx.y) * kEncCen; c0 < D.n_list;
+         c0 += static_cast<int>(gridDim.y) * kEncCen) {
+        __syncthreads();   // the directions are written; the previous chunk is no longer read
+#pragma unroll
+        for (int it = 0; it < kEncCen * kHeadDim / 4 / kEncThreads; ++it) {
+            const int idx = it * kEncThreads + tid;
+            const int c = min(c0 + idx / 32, D.n_list - 1);   // 32 float4 per row; past the end unused
+            cs4[idx / 32 * (kEncLd / 4) + idx % 32] =
+                reinterpret_cast<const float4*>(cen + static_cast<int64_t>(c) * kHeadDim)[idx % 32];
+        }
+        __syncthreads();
+        float acc[2][4] = {};
+#pragma unroll 4
+        for (int x = 0; x < kHeadDim / 4; ++x) {
+            float4 u[2], c[4];
+#pragma unroll
+            for (int i = 0; i < 2; ++i) u[i] = us4[(ty + i) * (kEncLd / 4) + x];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) c[j] = cs4[(tx + 16 * j) * (kEncLd / 4) + x];
+#pragma unroll
+            for (int i = 0; i < 2; ++i)
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const float d0 = u[i].x - c[j].x, d1 = u[i].y - c[j].y;
+                    const float d2 = u[i].z - c[j].z, d3 = u[i].w - c[j].w;
+                    acc[i][j] = fmaf(d0, d0, acc[i][j]);
+                    acc[i][j] = fmaf(d1, d1, acc[i][j]);
+                    acc[i][j] = fmaf(d2, d2, acc[i][j]);
+                    acc[i][j] = fmaf(d3, d3, acc[i][j]);
+                }
+        }
+#pragma unroll
+        for (int i = 0; i < 2; ++i)
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if (c0 + tx + 16 * j < D.n_list) argmin_fold(best_d[i], best_i[i], acc[i][j], c0 + tx + 16 * j);
     }
-    __syncthreads();
-    const int a = sa;
-    if (tid < kHeadDim) su[tid] -= cen[static_cast<int64_t>(a) * kHeadDim + tid];
-    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) {
+            const float od = __shfl_xor(best_d[i], off);
+            const int oi = __shfl_xor(best_i[i], off);
+            argmin_fold(best_d[i], best_i[i], od, oi);
+        }
+        if (tx == 0 && ty + i < nt) {
+            const int64_t at = bg * part_stride +
+                               static_cast<int64_t>(t0 + ty + i - lo.v[b]) * gridDim.y + blockIdx.y;
+            part_d[at] = best_d[i];
+            part_i[at] = best_i[i];
+        }
+    }
+}
 
-    // nearest codeword of every subspace slice of the residual
-    const float* cb = codebooks + static_cast<int64_t>(bg) * PQ::M * PQ::K * PQ::DSUB;
-    for (int p = tid; p < PQ::M * PQ::K; p += kEncThreads) {
-        const int m = p / PQ::K;
+// encode_fine_kernel: 16 tokens x one subspace per workgroup, the subspace's
+// codewords in LDS; 16 lanes share a token's codewords. Folds the token's nearest
+// centroids of the coarse kernel's shares first (the first subspace's workgroups
+// write the list ids).
+template <typename T, typename PQ>
+__global__ __launch_bounds__(kEncThreads) void encode_fine_kernel(
+    Dims D, BatchInts lo, BatchInts hi, const T* __restrict__ kcache, int64_t sb, int64_t sh, int64_t sn,
+    const float* __restrict__ centroids, const float* __restrict__ codebooks,
+    const float* __restrict__ part_d, const int32_t* __restrict__ part_i, int64_t part_stride, int shares,
+    const float* __restrict__ norms_tm, int32_t* __restrict__ ids_tm, uint8_t* __restrict__ codes_tm) {
+    constexpr int K = PQ::K, DS = PQ::DSUB, kLd = DS + 1;   // odd row stride: lanes on distinct banks
+    __shared__ float cb[K * kLd];
+    __shared__ float res[kEncThreads / 16][DS];
+    const int bg = blockIdx.z;
+    const int b = bg / D.Hkv, g = bg % D.Hkv;
+    const int m = blockIdx.y;
+    const int t0 = lo.v[b] + static_cast<int>(blockIdx.x) * (kEncThreads / 16);
+    if (t0 >= hi.v[b]) return;
+    const int tl = threadIdx.x / 16;
+    const int l16 = threadIdx.x % 16;
+    const bool ok = t0 + tl < hi.v[b];
+    const int t = ok ? t0 + tl : hi.v[b] - 1;
+    const float* src = codebooks + (static_cast<int64_t>(bg) * PQ::M + m) * K * DS;
+    for (int i = threadIdx.x; i < K * DS; i += kEncThreads) cb[i / DS * kLd + i % DS] = src[i];
+    // the nearest centroid over the shares
+    const int64_t at = bg * part_stride + static_cast<int64_t>(t - lo.v[b]) * shares;
+    float bd = __builtin_huge_valf();
+    int a = 0;
+    for (int i = l16; i < shares; i += 16) argmin_fold(bd, a, part_d[at + i], part_i[at + i]);
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+        const float od = __shfl_xor(bd, off);
+        const int oi = __shfl_xor(a, off);
+        argmin_fold(bd, a, od, oi);
+    }
+    const int64_t tok = static_cast<int64_t>(bg) * D.rcap + t;
+    if (l16 < DS) {
+        const int x = m * DS + l16;
+        const float r = norms_tm[tok];
+        const float k = load1<T>(kcache + b * sb + g * sh + static_cast<int64_t>(t) * sn + x);
+        res[tl][l16] = (r > 0.0f ? k / r : 0.0f) - centroids[(static_cast<int64_t>(bg) * D.n_list + a) * kHeadDim + x];
+    }
+    __syncthreads();
+    float ru[DS];
+#pragma unroll
+    for (int x = 0; x < DS; ++x) ru[x] = res[tl][x];
+    float best = __builtin_huge_valf();
+    int bz = 0;   // a valid id even if every distance is NaN
+    for (int z = l16; z < K; z += 16) {
         float acc = 0.0f;
 #pragma unroll
-        for (int x = 0; x < PQ::DSUB; ++x) {
-            const float dx = su[m * PQ::DSUB + x] - cb[static_cast<int64_t>(p) * PQ::DSUB + x];
+        for (int x = 0; x < DS; ++x) {
+            const float dx = ru[x] - cb[z * kLd + x];
             acc = fmaf(dx, dx, acc);
         }
-        sdist[p] = acc;
+        argmin_fold(best, bz, acc, z);
     }
-    __syncthreads();
-    const int64_t tok = static_cast<int64_t>(bg) * D.rcap + t;
-    for (int m = wave; m < PQ::M; m += kEncThreads / kWave) {
-        float bd = __builtin_huge_valf();
-        int bi = 0;   // a valid id even if every distance is NaN
-        for (int z = lane; z < PQ::K; z += kWave) argmin_fold(bd, bi, sdist[m * PQ::K + z], z);
-        wave_argmin64(bd, bi);
-        if (lane == 0) codes_tm[tok * PQ::M + m] = static_cast<uint8_t>(bi);
+#pragma unroll
+    for (int off = 1; off < 16; off <<= 1) {
+        const float od = __shfl_xor(best, off);
+        const int oi = __shfl_xor(bz, off);
+        argmin_fold(best, bz, od, oi);
     }
-    if (tid == 0) {
-        ids_tm[tok] = a;
-        norms_tm[tok] = r;
+    if (ok && l16 == 0) {
+        codes_tm[tok * PQ::M + m] = static_cast<uint8_t>(bz);
+        if (m == 0) ids_tm[tok] = a;
     }
 }
 
@@ -374,23 +446,46 @@ hipError_t launch_update_lists(const Dims& D, const BatchInts& lo, const BatchIn
     return hipGetLastError();
 }
 
+template <typename T>
+static hipError_t launch_encode_t(const Dims& D, const BatchInts& lo, const BatchInts& hi, int max_new,
+                                  const KV& kv, const float* centroids, const float* codebooks,
+                                  int32_t* ids_tm, uint8_t* codes_tm, float* norms_tm, float* part_d,
+                                  int32_t* part_i, int64_t part_ints, hipStream_t s) {
+    // shares of the centroids: about four workgroups per CU, one chunk of
+    // centroids at least, and what the scratch holds per (b, kv head)
+    const int bgs = D.B * D.Hkv;
+    const int tiles = (max_new + kEncTok - 1) / kEncTok;
+    const int chunks = (D.n_list + kEncCen - 1) / kEncCen;
+    const int n_cu = device_cu_count() > 0 ? device_cu_count() : 1;
+    int64_t shares = std::max<int64_t>(1, static_cast<int64_t>(4) * n_cu / (static_cast<int64_t>(tiles) * bgs));
+    shares = std::min<int64_t>(std::min<int64_t>(shares, chunks), std::max<int64_t>(1, part_ints / bgs / max_new));
+    const int64_t stride = shares * max_new;
+    const T* k = static_cast<const T*>(kv.k);
+    hipLaunchKernelGGL(encode_coarse_kernel<T>, dim3(tiles, static_cast<unsigned>(shares), bgs), dim3(kEncThreads),
+                       0, s, D, lo, hi, k, kv.sb, kv.sh, kv.sn, centroids, part_d, part_i, stride, norms_tm);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const int fine_tiles = (max_new + kEncThreads / 16 - 1) / (kEncThreads / 16);
+#define PQHSA_FINE(PQT)                                                                                      \
+    hipLaunchKernelGGL((encode_fine_kernel<T, PQT>), dim3(fine_tiles, PQT::M, bgs), dim3(kEncThreads), 0, s, \
+                       D, lo, hi, k, kv.sb, kv.sh, kv.sn, centroids, codebooks, part_d, part_i, stride,      \
+                       static_cast<int>(shares), norms_tm, ids_tm, codes_tm)
+    if (D.pq_bits == 4) PQHSA_FINE(Pq4);
+    else PQHSA_FINE(Pq8);
+#undef PQHSA_FINE
+    return hipGetLastError();
+}
+
 hipError_t launch_encode_update(const Dims& D, const BatchInts& lo, const BatchInts& hi,
                                 int max_new, const KV& kv, const float* centroids,
                                 const float* codebooks, int32_t* ids_tm, uint8_t* codes_tm,
-                                float* norms_tm, hipStream_t s) {
+                                float* norms_tm, float* part_d, int32_t* part_i, int64_t part_ints,
+                                hipStream_t s) {
     if (max_new <= 0) return hipSuccess;
-    const dim3 grid(max_new, D.Hkv, D.B);
-#define PQHSA_ENC1(TT, PQT)                                                                     \
-    hipLaunchKernelGGL((encode_one_kernel<TT, PQT>), grid, dim3(kEncThreads), 0, s, D, lo, hi,    \
-                       static_cast<const TT*>(kv.k), kv.sb, kv.sh, kv.sn, centroids, codebooks,   \
-                       ids_tm, codes_tm, norms_tm)
-    if (kv.bf16) {
-        if (D.pq_bits == 4) PQHSA_ENC1(bf16_t, Pq4); else PQHSA_ENC1(bf16_t, Pq8);
-    } else {
-        if (D.pq_bits == 4) PQHSA_ENC1(float, Pq4); else PQHSA_ENC1(float, Pq8);
-    }
-#undef PQHSA_ENC1
-    return hipGetLastError();
+    return kv.bf16 ? launch_encode_t<bf16_t>(D, lo, hi, max_new, kv, centroids, codebooks, ids_tm, codes_tm,
+                                             norms_tm, part_d, part_i, part_ints, s)
+                   : launch_encode_t<float>(D, lo, hi, max_new, kv, centroids, codebooks, ids_tm, codes_tm,
+                                            norms_tm, part_d, part_i, part_ints, s);
 }
 
 }  // namespace pqhsa
