@@ -449,6 +449,28 @@ __global__ __launch_bounds__(kHeadDim) void init_centers_kernel(Dims D, int kind
         token_elem<T>(D, kind, kv, pr.bg, pr.m, pr.dims, t, x, ids_tm, norms_tm, centroids);
 }
 
+__global__ __launch_bounds__(256) void check_starts_kernel(Dims D, BatchInts lo, BatchInts hi,
+                                                           const int32_t* __restrict__ coarse,
+                                                           const int32_t* __restrict__ pq, int per_pq,
+                                                           unsigned long long* bad) {
+    const int64_t n_coarse = static_cast<int64_t>(D.B) * D.Hkv * D.n_list;
+    const int64_t n = n_coarse + static_cast<int64_t>(D.B) * D.Hkv * per_pq;
+    const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
+    if (i >= n) return;
+    const int64_t bg = i < n_coarse ? i / D.n_list : (i - n_coarse) / per_pq;
+    const int t = i < n_coarse ? coarse[i] : pq[i - n_coarse];
+    const int b = static_cast<int>(bg / D.Hkv);
+    if (t < lo.v[b] || t >= hi.v[b]) atomicMin(bad, static_cast<unsigned long long>(i));
+}
+
+hipError_t launch_check_starts(const Dims& D, const BatchInts& lo, const BatchInts& hi, const int32_t* coarse,
+                               const int32_t* pq, int per_pq, unsigned long long* bad, hipStream_t s) {
+    const int64_t n = static_cast<int64_t>(D.B) * D.Hkv * (D.n_list + per_pq);
+    hipLaunchKernelGGL(check_starts_kernel, dim3(static_cast<unsigned>((n + 255) / 256)), dim3(256), 0, s, D, lo,
+                       hi, coarse, pq, per_pq, bad);
+    return hipGetLastError();
+}
+
 static int n_problems(const Dims& D, int kind) {
     return D.B * D.Hkv * (kind == 1 ? (D.pq_bits == 4 ? Pq4::M : Pq8::M) : 1);
 }

@@ -362,6 +362,10 @@ hipError_t launch_update_lists(const Dims& D, const BatchInts& lo, const BatchIn
 // float64 value sums of the lists, |R_j| v_bar_j, for later updates
 hipError_t launch_init_sums(const Dims& D, const int32_t* loff, const float* means, double* sums,
                             hipStream_t s);
+// The build's starting tokens: the smallest flat index (coarse ones first) of
+// one outside R_b, by atomicMin into `bad` (all ones beforehand).
+hipError_t launch_check_starts(const Dims& D, const BatchInts& lo, const BatchInts& hi, const int32_t* coarse,
+                               const int32_t* pq, int per_pq, unsigned long long* bad, hipStream_t s);
 // The threshold sample's codes, norms and list ids per (b, kv head), from the
 // list-major index (after every prepare and update).
 hipError_t launch_sample_slab(const Dims& D, const Index& ix, uint8_t* samp_codes, float* samp_norms,
