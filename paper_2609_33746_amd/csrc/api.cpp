@@ -417,7 +417,7 @@ static pqhsa_status relayout(pqhsa_ctx* c, const std::vector<int32_t>& lens, hip
     c->n_r = nr;
     int nr_max = 0;
     for (int b = 0; b < B; ++b) nr_max = std::max(nr_max, nr[b]);
-    c->scan_nwg = (nr_max + kScanWaves * kSub - 1) / (kScanWaves * kSub);
+    c->scan_nwg = (nr_max + kScanChunk - 1) / kScanChunk;
     c->prepared = true;
     return PQHSA_OK;
 }
@@ -512,7 +512,7 @@ pqhsa_status pqhsa_index_update(pqhsa_ctx* c, const int32_t* new_seq_lens, const
     }
     c->seq_lens = lens;
     c->cur_len = lens;
-    c->scan_nwg = (nr_max + kScanWaves * kSub - 1) / (kScanWaves * kSub);
+    c->scan_nwg = (nr_max + kScanChunk - 1) / kScanChunk;
     c->prepared = true;
     return PQHSA_OK;
 }
@@ -731,6 +731,7 @@ static pqhsa_status decode_impl(pqhsa_ctx* c, const void* q, const void* k, cons
     BatchArgs ba{};
     int nsplit = 1;   // exact-set splits this call needs per row
     Work w = c->w;
+    w.region_shift = scan_region_shift(D, c->scan_nwg);
     if (dev_args) {
         // every split the partial buffer holds: surplus workgroups exit
         for (int b = 0; b < D.B; ++b) ba.n_r[b] = c->n_r[b];

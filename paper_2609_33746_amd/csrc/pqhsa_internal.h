@@ -31,10 +31,14 @@ constexpr int kMaxLists = 4096;
 
 constexpr int kSub = 128;          // list-major positions per wave sub-chunk
 constexpr int kScanWaves = 16;     // waves (sub-chunks) per scan workgroup
+constexpr int kScanChunk = kScanWaves * kSub;   // positions per scan workgroup step: 2048
+// a candidate region: 2^7 positions (a sub-chunk) or 2^11 (a chunk)
+constexpr int kSubShift = 7, kScanChunkShift = 11;
+static_assert(kSub == 1 << kSubShift && kScanChunk == 1 << kScanChunkShift, "region sizes");
+constexpr int kSelMaxRegions = 1024;   // regions per row the select takes
 constexpr int kMaxSamples = 2048;  // sampled positions per row for the threshold
 constexpr int kSelThreads = 1024;
 constexpr int kSelCap = 12288;     // candidates of one row held in LDS by the select kernel
-constexpr int kSelMaxSub = 1024;   // sub-chunks per row on the select kernel's fast path
 constexpr int kSampleRun = 2;      // contiguous positions per sampled run
 constexpr int kPosBits = 20;       // position / candidate word: list id << kPosBits | token id
 constexpr uint32_t kPosMask = (1u << kPosBits) - 1u;
@@ -155,9 +159,10 @@ struct Work {
     float* coarse;       // [B, Hkv, n_list, G] (q . c_j) / sqrt(d)
     float* tau_lo;       // [B, Hq] candidate threshold
     float* tau_hi;       // [B, Hq] largest sampled score (-inf when not sampled)
-    uint2* cand;         // [B, Hq, rcap] candidates compacted per sub-chunk: (score bits,
-                         //   list id << kPosBits | list-major position)
-    int32_t* cand_cnt;   // [B, Hq, nsub_cap]
+    uint2* cand;         // [B, Hq, rcap] candidates compacted per region of 2^region_shift
+                         //   positions: (score bits, list id << kPosBits | token id)
+    int32_t* cand_cnt;   // [B, Hq, nsub_cap] candidates of each region
+    int region_shift;    // the call's (scan_region_shift)
     float* seg_sum;      // [B, Hkv, nseg_cap, G] below-threshold masses; the pair
                          //   (list j, sub-chunk s) uses segment j + s
     uint32_t* comp_key;  // [B, Hq, rcap] contiguous candidates (order keys)
@@ -254,6 +259,7 @@ hipError_t launch_prologue(const Dims& D, const BatchArgs& ba, const KV& kv, con
                            const Work& w, float bias, hipStream_t s,
                            const KTiming& tm = KTiming{});
 // nwg = scan workgroups per (batch element, KV head): enough for the longest R_b
+int scan_region_shift(const Dims& D, int nwg);
 hipError_t launch_scan(const Dims& D, const BatchArgs& ba, const Index& ix, const Work& w, int nwg,
                        hipStream_t s, const KTiming& tm = KTiming{});
 // bx: variant Bx, whose per-list weights bx_w and per-entry weights bx_wsel

@@ -23,7 +23,8 @@
 // Per token and head the wave computes l~ and then either
 //   * emits (l~, list id and token id) as a top-k candidate when
 //     l~ >= tau_lo (the sampled threshold of its row), compacted in position
-//     order at the start of the sub-chunk's own region of the row's candidate
+//     order over the workgroup's chunk (or the wave's sub-chunk, see
+//     scan_region_shift) at the start of its own region of the row's candidate
 //     buffer, or
 //   * adds exp(l~ - tau_lo) (< 1) to the running mass of its inverted list.
 // Tokens below tau_lo can never be in the top-k (tau_lo <= the k-th largest
@@ -113,12 +114,16 @@ constexpr int kScanLutFloats = std::is_same<PQ, Pq4>::value ? kRep4Floats : PQ::
 // so two workgroups share a CU instead of one (the codes are read twice).
 // At most 80 SGPRs per wave (a few spill to VGPR lanes): with more, a second
 // workgroup does not fit on the CU.
-template <int G, int GT, typename PQ, bool kDev>
-__global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_num_sgpr(80))) void scan_kernel(
+// kChunked: the candidates are compacted over the workgroup's chunk, else over
+// each wave's sub-chunk (see scan_region_shift).
+template <int G, int GT, typename PQ, bool kDev, bool kChunked>
+__global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_num_sgpr(80), amdgpu_waves_per_eu(8))) void scan_kernel(
     Dims D, BatchArgs ba, Index ix, Work w, int nwg, int nwg_grid) {
     // the group LUT at a compile-time LDS address (so that an entry address
     // is one shift of a code)
     __shared__ float4 lut4[kScanLutFloats<PQ, G> / 4];
+    __shared__ int wave_cnt[2][kChunked ? G * kScanWaves : 1];   // candidates of each head and wave
+    static_assert(G * kScanWaves <= kWave && kScanWaves == 16, "one DPP row per head");
     float* lut_s = reinterpret_cast<float*>(lut4);
     constexpr int kParts = GT / G;   // workgroups per (b, g) and sub-chunk range
     static_assert(kParts * G == GT, "head split");
@@ -136,7 +141,7 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_num_sgpr(80))) 
     const int g = bg % D.Hkv;
     const int n_r = arg_n_r<kDev>(ba, w, b);
     const int chunk0 = blockIdx.x / n_units;
-    if (chunk0 * kScanWaves * kSub >= n_r) return;   // surplus workgroup of a shorter sequence
+    if (chunk0 * kScanChunk >= n_r) return;   // surplus workgroup of a shorter sequence
 
     const int tid = threadIdx.x;
     const int wave = tid / kWave;
@@ -178,121 +183,185 @@ __global__ __launch_bounds__(kScanThreads) __attribute__((amdgpu_num_sgpr(80))) 
 #pragma unroll
     for (int i = 0; i < kStage; ++i) ldst[i * kScanThreads + tid] = st[i];
     __syncthreads();
-    for (int chunk = chunk0; chunk < nwg; chunk += nwg_grid) {
+    int parity = 0;
+    for (int chunk = chunk0; chunk < nwg; chunk += nwg_grid, parity ^= 1) {
+        const int c_begin = chunk * kScanChunk;
+        if (c_begin >= n_r) break;   // later chunks start later still
         const int sc = chunk * kScanWaves + wave;
         const int p_begin = sc * kSub;
         const int p_end = min(p_begin + kSub, n_r);
-        if (p_begin >= n_r) break;   // later chunks start later still
         // 2) per 64-position step: list ids, codes and norms (addresses clamped
         //    into R_b, so every load is in bounds), issued in the order the steps
         //    use them, after the tables: each step waits only for its own data
         const typename PQ::Code* codes = reinterpret_cast<const typename PQ::Code*>(ix.codes) + base;
         uint32_t wl[kIters];   // list id << kPosBits | token id
-        typename PQ::Code cv[kIters];
-        float rv[kIters];
+        float s[kIters][G];    // the steps' scores, kept until the candidates' places are known
+        int count[G];          // the wave's candidates
 #pragma unroll
-        for (int it = 0; it < kIters; ++it) {
-            const int p = min(p_begin + it * kWave + lane, n_r - 1);
-            wl[it] = ix.pos_word[base + p];
-            cv[it] = codes[p];
-            rv[it] = ix.norms[base + p];
-        }
-        float* segs = w.seg_sum + (static_cast<int64_t>(bg) * D.nseg_cap + sc) * GT + part * G;   // + j * GT
-        int cur = __builtin_amdgcn_readfirstlane(static_cast<int>(wl[0] >> kPosBits));   // open segment's list
-        float acc[G];
-        int cbase[G];
+        for (int hh = 0; hh < G; ++hh) count[hh] = 0;
+        if (p_begin < n_r) {
+            typename PQ::Code cv[kIters];
+            float rv[kIters];
 #pragma unroll
-        for (int hh = 0; hh < G; ++hh) { acc[hh] = -0.0f; cbase[hh] = 0; }   // -0 + x folds to x
+            for (int it = 0; it < kIters; ++it) {
+                const int p = min(p_begin + it * kWave + lane, n_r - 1);
+                wl[it] = ix.pos_word[base + p];
+                cv[it] = codes[p];
+                rv[it] = ix.norms[base + p];
+            }
+            float* segs = w.seg_sum + (static_cast<int64_t>(bg) * D.nseg_cap + sc) * GT + part * G;   // + j * GT
+            int cur = __builtin_amdgcn_readfirstlane(static_cast<int>(wl[0] >> kPosBits));   // open segment's list
+            float acc[G];
+#pragma unroll
+            for (int hh = 0; hh < G; ++hh) acc[hh] = -0.0f;   // -0 + x folds to x
 
 #pragma unroll
-        for (int it = 0; it < kIters; ++it) {
-            const int p_first = p_begin + it * kWave;
-            if (p_first >= p_end) continue;   // uniform: past the end of a short last sub-chunk
-            const int p = p_first + lane;
-            const bool valid = p < p_end;
-            const uint64_t vmask = __builtin_amdgcn_ballot_w64(valid);
-            // coarse terms of the lanes' lists, gathered from the group table
-            // (neighbouring lanes mostly share a list; staging the table in
-            // LDS instead was a little slower, 12.4 against 12.3 us at 128K
-            // and 97.4 against 96.2 us at 16 sequences)
-            const int j = static_cast<int>(wl[it] >> kPosBits);
-            float cf[G];
-            load_coarse<G>(coarse + j * GT, cf);
-            float fs[G];
-            if constexpr (std::is_same<PQ, Pq4>::value) fine_sum_rep4<G>(lut_s, cv[it], fs);
-            else fine_sum<PQ, G>(lut_s, cv[it], fs);
-            // exp(l~ - tau_lo) as exp2(r log2(e) (coarse + fine) - tau_lo log2(e)):
-            // one FMA per head, with r log2(e) shared by the G heads
-            const float r_l2e = rv[it] * kLog2e;
-            float s[G], e[G];
+            for (int it = 0; it < kIters; ++it) {
+                const int p_first = p_begin + it * kWave;
+                if (p_first >= p_end) continue;   // uniform: past the end of a short last sub-chunk
+                const int p = p_first + lane;
+                const bool valid = p < p_end;
+                const uint64_t vmask = __builtin_amdgcn_ballot_w64(valid);
+                // coarse terms of the lanes' lists, gathered from the group table
+                // (neighbouring lanes mostly share a list; staging the table in
+                // LDS instead was a little slower, 12.4 against 12.3 us at 128K
+                // and 97.4 against 96.2 us at 16 sequences)
+                const int j = static_cast<int>(wl[it] >> kPosBits);
+                float cf[G];
+                load_coarse<G>(coarse + j * GT, cf);
+                float fs[G];
+                if constexpr (std::is_same<PQ, Pq4>::value) fine_sum_rep4<G>(lut_s, cv[it], fs);
+                else fine_sum<PQ, G>(lut_s, cv[it], fs);
+                // exp(l~ - tau_lo) as exp2(r log2(e) (coarse + fine) - tau_lo log2(e)):
+                // one FMA per head, with r log2(e) shared by the G heads
+                const float r_l2e = rv[it] * kLog2e;
+                float e[G];
 #pragma unroll
-            for (int hh = 0; hh < G; ++hh) {
-                const float x = cf[hh] + fs[hh];
-                s[hh] = pq_logit(rv[it], cf[hh], fs[hh]);
-                e[hh] = (valid && s[hh] < tlo[hh])
-                            ? __builtin_amdgcn_exp2f(__builtin_fmaf(r_l2e, x, -tlo_l2e[hh]))
-                            : 0.0f;
-            }
-            // close the lists that end inside this step (lists are contiguous and
-            // ascending along the lanes)
-            const int j_last = __builtin_amdgcn_readlane(j, min(p_end - p_first, kWave) - 1);
-            while (cur != j_last) {
-                const bool in = valid && j == cur;
+                for (int hh = 0; hh < G; ++hh) {
+                    const float x = cf[hh] + fs[hh];
+                    s[it][hh] = pq_logit(rv[it], cf[hh], fs[hh]);
+                    e[hh] = (valid && s[it][hh] < tlo[hh])
+                                ? __builtin_amdgcn_exp2f(__builtin_fmaf(r_l2e, x, -tlo_l2e[hh]))
+                                : 0.0f;
+                    // ballots of bare compares, masked by the valid lanes' ballot,
+                    // stay lane masks in scalar registers
+                    if constexpr (kChunked)
+                        count[hh] += __popcll(__builtin_amdgcn_ballot_w64(s[it][hh] >= tlo[hh]) & vmask);
+                }
+                // close the lists that end inside this step (lists are contiguous and
+                // ascending along the lanes)
+                const int j_last = __builtin_amdgcn_readlane(j, min(p_end - p_first, kWave) - 1);
+                while (cur != j_last) {
+                    const bool in = valid && j == cur;
 #pragma unroll
-                for (int hh = 0; hh < G; ++hh) acc[hh] += in ? e[hh] : 0.0f;
-                flush_segment<G>(segs + cur * GT, acc);
-                const int nxt = __popcll(__builtin_amdgcn_ballot_w64(j <= cur) & vmask);
-                cur = __builtin_amdgcn_readlane(j, nxt);
-            }
-            {
-                const bool in = valid && j == cur;
+                    for (int hh = 0; hh < G; ++hh) acc[hh] += in ? e[hh] : 0.0f;
+                    flush_segment<G>(segs + cur * GT, acc);
+                    const int nxt = __popcll(__builtin_amdgcn_ballot_w64(j <= cur) & vmask);
+                    cur = __builtin_amdgcn_readlane(j, nxt);
+                }
+                {
+                    const bool in = valid && j == cur;
 #pragma unroll
-                for (int hh = 0; hh < G; ++hh) acc[hh] += in ? e[hh] : 0.0f;
-            }
-            // candidates >= tau_lo, compacted in position order
+                    for (int hh = 0; hh < G; ++hh) acc[hh] += in ? e[hh] : 0.0f;
+                }
+                // candidates >= tau_lo of the sub-chunk, compacted in position order
+                if constexpr (!kChunked) {
 #pragma unroll
-            for (int hh = 0; hh < G; ++hh) {
-                // ballots of bare compares, masked by the valid lanes' ballot,
-                // stay lane masks in scalar registers
-                const uint64_t mask = __builtin_amdgcn_ballot_w64(s[hh] >= tlo[hh]) & vmask;
-                if (mask) {
-                    if (valid && s[hh] >= tlo[hh]) {
-                        const int64_t o = static_cast<int64_t>(row0 + hh) * D.rcap + p_begin +
-                                          cbase[hh] + lanes_below(mask);
-                        w.cand[o] = make_uint2(__float_as_uint(s[hh]), wl[it]);
+                    for (int hh = 0; hh < G; ++hh) {
+                        const uint64_t mask = __builtin_amdgcn_ballot_w64(s[it][hh] >= tlo[hh]) & vmask;
+                        if (mask) {
+                            if (valid && s[it][hh] >= tlo[hh])
+                                w.cand[static_cast<int64_t>(row0 + hh) * D.rcap + p_begin + count[hh] +
+                                       lanes_below(mask)] = make_uint2(__float_as_uint(s[it][hh]), wl[it]);
+                            count[hh] += __popcll(mask);
+                        }
                     }
-                    cbase[hh] += __popcll(mask);
                 }
             }
+            flush_segment<G>(segs + cur * GT, acc);
         }
-        flush_segment<G>(segs + cur * GT, acc);
+        // 3) kChunked: the candidates of the chunk's 16 waves, compacted in
+        //    position order at the start of the chunk's region of each row: every
+        //    wave's counts go to LDS (two copies in turn, so one barrier a chunk),
+        //    and lane 16 hh + w of every wave sums head hh's over waves 0 .. w
         int mine = 0;
 #pragma unroll
         for (int hh = 0; hh < G; ++hh)
-            if (lane == hh) mine = cbase[hh];
-        if (lane < G) w.cand_cnt[static_cast<int64_t>(row0 + lane) * D.nsub_cap + sc] = mine;
+            if (lane == hh) mine = count[hh];
+        if constexpr (!kChunked) {
+            if (lane < G && p_begin < n_r) w.cand_cnt[static_cast<int64_t>(row0 + lane) * D.nsub_cap + sc] = mine;
+            continue;
+        }
+        if (lane < G) wave_cnt[parity][lane * kScanWaves + wave] = mine;
+        __syncthreads();
+        int run = lane < kScanWaves * G ? wave_cnt[parity][lane % (kScanWaves * G)] : 0;
+        run += __builtin_amdgcn_update_dpp(0, run, 0x111, 0xF, 0xF, false);   // row_shr:1
+        run += __builtin_amdgcn_update_dpp(0, run, 0x112, 0xF, 0xF, false);   // row_shr:2
+        run += __builtin_amdgcn_update_dpp(0, run, 0x114, 0xF, 0xF, false);   // row_shr:4
+        run += __builtin_amdgcn_update_dpp(0, run, 0x118, 0xF, 0xF, false);   // row_shr:8
+        if (wave == kScanWaves - 1 && lane % kScanWaves == kScanWaves - 1 && lane / kScanWaves < G)
+            w.cand_cnt[static_cast<int64_t>(row0 + lane / kScanWaves) * D.nsub_cap + chunk] = run;
+        if (p_begin >= n_r) continue;
+        const int uwave = __builtin_amdgcn_readfirstlane(wave);
+#pragma unroll
+        for (int hh = 0; hh < G; ++hh) {
+            if (!count[hh]) continue;
+            int at = __builtin_amdgcn_readlane(run, hh * kScanWaves + uwave) - count[hh];
+            uint2* out = w.cand + static_cast<int64_t>(row0 + hh) * D.rcap + c_begin;
+#pragma unroll
+            for (int it = 0; it < kIters; ++it) {
+                const int p_first = p_begin + it * kWave;
+                if (p_first >= p_end) continue;
+                const bool valid = p_first + lane < p_end;
+                const uint64_t mask = __builtin_amdgcn_ballot_w64(s[it][hh] >= tlo[hh]) &
+                                      __builtin_amdgcn_ballot_w64(valid);
+                if (valid && s[it][hh] >= tlo[hh])
+                    out[at + lanes_below(mask)] = make_uint2(__float_as_uint(s[it][hh]), wl[it]);
+                at += __popcll(mask);
+            }
+        }
     }
 }
 
 constexpr size_t kScanLdsMax = 160 * 1024;   // LDS of one workgroup on gfx950
 constexpr int kScanMaxChunks = 4;
 
-template <int G, int GT, typename PQ, bool kDev>
+// Chunks per workgroup: as many as the grid has rounds of the workgroups
+// that run at once (two per CU), at most kScanMaxChunks, each workgroup
+// staging its tables once for all of them (at 4 and 16 sequences 4
+// chunks per workgroup beat 1, 2, 8 and 16).
+static int chunks_per_wg(int n_units, int nwg) {
+    const int n_cu = device_cu_count();
+    const int64_t resident = static_cast<int64_t>(2) * (n_cu > 0 ? n_cu : 1);
+    return static_cast<int>(
+        std::min<int64_t>(kScanMaxChunks, std::max<int64_t>(1, static_cast<int64_t>(n_units) * nwg / resident)));
+}
+static int scan_units(const Dims& D) { return D.B * D.Hkv * (D.G == 8 ? 2 : 1); }
+
+// A candidate region per chunk of 2048 positions gives the top-k stage whole
+// lines to read and a sixteenth of the counts to add up (its time, us: 128K 12.0
+// -> 10.5, 512K tokens 40 -> 28), for a barrier per chunk in the scan (12.2 ->
+// 13.0, and the call 45.1 -> 44.5; the smallest, one head of 4K tokens, 29.2 ->
+// 26.6). Where a workgroup scans several chunks with the 8-bit tables, which
+// keep the LDS busy throughout, that barrier costs more than the top-k stage
+// gains (16 sequences of 64K-128K: the scan 106 -> 119, the select 18.9 -> 14.8,
+// the call 218 -> 230): a region per wave of 128 positions there, for as many
+// as the select's offsets hold.
+int scan_region_shift(const Dims& D, int nwg) {
+    const bool fine = D.pq_bits == 8 && chunks_per_wg(scan_units(D), nwg) > 1 &&
+                      nwg * kScanWaves <= kSelMaxRegions;
+    return fine ? kSubShift : kScanChunkShift;
+}
+
+template <int G, int GT, typename PQ, bool kDev, bool kChunked>
 static hipError_t launch_scan_d(const Dims& D, const BatchArgs& ba, const Index& ix, const Work& w,
                                 int nwg, hipStream_t s, const KTiming& tm) {
     static_assert(kScanLutFloats<PQ, G> * 4 <= kScanLdsMax, "LDS budget");
-    const int n_units = D.B * D.Hkv * (GT / G);
-    // chunks per workgroup: as many as the grid has rounds of the workgroups
-    // that run at once (two per CU), at most kScanMaxChunks, each workgroup
-    // staging its tables once for all of them (at 4 and 16 sequences 4
-    // chunks per workgroup beat 1, 2, 8 and 16)
-    const int n_cu = device_cu_count();
-    const int64_t resident = static_cast<int64_t>(2) * (n_cu > 0 ? n_cu : 1);
-    const int cpw = static_cast<int>(
-        std::min<int64_t>(kScanMaxChunks, std::max<int64_t>(1, static_cast<int64_t>(n_units) * nwg / resident)));
+    const int n_units = scan_units(D);
+    const int cpw = chunks_per_wg(n_units, nwg);
     const int nwg_grid = (nwg + cpw - 1) / cpw;
     const dim3 grid(n_units * nwg_grid);
-    hipExtLaunchKernelGGL((scan_kernel<G, GT, PQ, kDev>), grid, dim3(kScanThreads), 0, s, tm.start,
+    hipExtLaunchKernelGGL((scan_kernel<G, GT, PQ, kDev, kChunked>), grid, dim3(kScanThreads), 0, s, tm.start,
                           tm.stop, 0, D, ba, ix, w, nwg, nwg_grid);
     return hipGetLastError();
 }
@@ -300,8 +369,13 @@ static hipError_t launch_scan_d(const Dims& D, const BatchArgs& ba, const Index&
 template <int G, int GT, typename PQ>
 static hipError_t launch_scan_t(const Dims& D, const BatchArgs& ba, const Index& ix, const Work& w,
                                 int nwg, hipStream_t s, const KTiming& tm) {
-    return w.ba_dev ? launch_scan_d<G, GT, PQ, true>(D, ba, ix, w, nwg, s, tm)
-                    : launch_scan_d<G, GT, PQ, false>(D, ba, ix, w, nwg, s, tm);
+    if constexpr (std::is_same<PQ, Pq8>::value) {
+        if (w.region_shift == kSubShift)
+            return w.ba_dev ? launch_scan_d<G, GT, PQ, true, false>(D, ba, ix, w, nwg, s, tm)
+                            : launch_scan_d<G, GT, PQ, false, false>(D, ba, ix, w, nwg, s, tm);
+    }
+    return w.ba_dev ? launch_scan_d<G, GT, PQ, true, true>(D, ba, ix, w, nwg, s, tm)
+                    : launch_scan_d<G, GT, PQ, false, true>(D, ba, ix, w, nwg, s, tm);
 }
 
 template <typename PQ>

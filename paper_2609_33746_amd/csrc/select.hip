@@ -15,7 +15,7 @@
 // row. Rows with more candidates than the LDS holds, or a very dense boundary
 // bin, use a radix select instead. Every path gives the exact top-k.
 //
-// Each wave loads the counts of its own sub-chunks and scans them with DPP,
+// A thread loads the count of one region, each wave scans its own with DPP,
 // candidate loads are issued in batches, and every workgroup-wide step is one
 // scan or reduction, so the dependency chain stays short.
 #include <algorithm>
@@ -31,9 +31,9 @@ namespace pqhsa {
 
 constexpr int kNW = kSelThreads / kWave;
 constexpr int kRankCap = 128;
-constexpr int kNzSubBits = 13;           // sub-chunk bits of a nonempty-list entry
-constexpr int kSelMaxSubWide = kMaxSeq / kSub;   // sub-chunks per row of the wide select
-static_assert((1 << kNzSubBits) >= kSelMaxSubWide, "sub-chunk ids");
+constexpr int kNzBits = 10;              // region bits of a nonempty-list entry
+static_assert((1 << kNzBits) >= kSelMaxRegions, "region ids");
+static_assert(kMaxSeq / kScanChunk <= kSelMaxRegions && kSelMaxRegions <= kSelThreads, "a region per thread");
 constexpr float kMassScale = 1099511627776.0f;       // 2^40: fixed-point weights
 constexpr float kMassUnscale = 1.0f / 1099511627776.0f;
 
@@ -125,12 +125,11 @@ __device__ __forceinline__ bool rank_boundary_bin(KeyAt key_at, TokAt tok_at, in
 // LDS layout of select_kernel (dynamic, 4-byte words), for kCap candidates:
 //   keys [kCap] | cand [kCap] | hist [kHistBins] | rank_key [kRankCap] |
 //   rank_idx [kRankCap] | rank_tok [kRankCap] | chosen bitmap [kCap / 32] |
-//   counter, flags [4] | sub-chunk offsets, or the nonempty sub-chunks, [kSelMaxSub] |
+//   counter, flags [4] | region offsets, or the nonempty regions, [kSelMaxRegions] |
 //   mass (uint64) [n_list]
 // The wide select keeps only the keys in LDS (the candidates' words go to
-// global memory), and its nonempty sub-chunks take the key area until the
-// keys are written.
-constexpr int kSelCapWide = 28672;
+// global memory).
+constexpr int kSelCapWide = 27648;
 template <int kCap>
 struct SelLayout {
     static constexpr bool kWide = kCap == kSelCapWide;
@@ -141,35 +140,35 @@ struct SelLayout {
     static constexpr int kOffRTok = kOffRIdx + kRankCap;
     static constexpr int kOffBits = kOffRTok + kRankCap;
     static constexpr int kOffCounter = kOffBits + kCap / 32;
-    static constexpr int kOffSub = kWide ? 0 : kOffCounter + 4;
-    static constexpr int kOffMass = (kOffCounter + 4 + (kWide ? 0 : kSelMaxSub) + 1) & ~1;   // 8-byte aligned
+    static constexpr int kOffRegion = kOffCounter + 4;
+    static constexpr int kOffMass = (kOffRegion + kSelMaxRegions + 1) & ~1;   // 8-byte aligned
     static constexpr size_t bytes(int n_list) { return static_cast<size_t>(kOffMass + 2 * n_list) * 4; }
     static_assert(kCap % kSelThreads == 0 && kCap % 32 == 0, "whole copy tiers and bitmap words");
     static_assert(kOffCand % 4 == 0, "16-byte candidate stores");
-    static_assert(!kWide || kCap >= kSelMaxSubWide, "the nonempty sub-chunks fit the key area");
-    static_assert(kCap < (1 << (31 - kNzSubBits)), "first-candidate indices");
+    static_assert(kCap < (1 << (31 - kNzBits)), "first-candidate indices");
 };
 // Three capacities (select_cap below picks one per call): every row's
 // candidates in LDS (one workgroup per CU); fewer (two workgroups per CU, for
-// grids of more rows than CUs); and the wide one, keys alone, for rows of more
-// than kSelMaxSub sub-chunks or more candidates than the first holds. Rows
-// beyond the capacity take the global-memory path.
+// grids of more rows than CUs); and the wide one, keys alone, for rows likely to
+// have more candidates than the first holds. Rows beyond the capacity take the
+// global-memory path.
 constexpr int kSelCapSmall = 7168;
 constexpr size_t kLdsPerCu = 160 * 1024;
 static_assert(SelLayout<kSelCapWide>::bytes(kMaxLists) + sizeof(SelectScratch) + sizeof(BlockScratch) <= kLdsPerCu,
               "the wide select fits a CU at the most lists");
 
 // Read the candidates first + u kSelThreads + tid, u < N, of the row's
-// `total` (>= 1) from their sub-chunk slots (one workgroup per CU):
+// `total` (>= 1) from their regions (one workgroup per CU):
 // neighbouring lanes read neighbouring slots. Candidate i lives in the
-// sub-chunk sc with pre[sc] <= i < pre[sc + 1] (the last of equal offsets, so
-// empty sub-chunks never match). Every thread searches all of its indices
-// together and issues all loads before using any, so the copy costs one search
-// chain and one memory round trip (indices past the end repeat the last
-// candidate's load).
-template <int N, int kMaxSub>
+// region c with pre[c] <= i < pre[c + 1] (the last of equal offsets, so
+// empty regions never match). Every thread searches all of its indices
+// together (top: half the power of two at or above nreg, 0 for one region) and
+// issues all loads before using any, so the copy costs one search chain and one
+// memory round trip (indices past the end repeat the last candidate's load).
+template <int N>
 __device__ __forceinline__ void read_candidates_search(const uint2* __restrict__ cand, const int* pre,
-                                                       int nsub, int first, int total, uint2 (&rec)[N]) {
+                                                       int nreg, int rshift, int top, int first, int total,
+                                                       uint2 (&rec)[N]) {
     const int tid = threadIdx.x;
     // the N searches advance together, one step at a time, so their LDS
     // reads overlap instead of forming one long dependent chain
@@ -179,89 +178,77 @@ __device__ __forceinline__ void read_candidates_search(const uint2* __restrict__
         ci[u] = min(first + u * kSelThreads + tid, total - 1);
         cs[u] = 0;
     }
-#pragma unroll
-    for (int step = kMaxSub / 2; step > 0; step >>= 1) {
+    for (int step = top; step > 0; step >>= 1) {
         int pv[N];
 #pragma unroll
-        for (int u = 0; u < N; ++u) pv[u] = pre[min(cs[u] + step, nsub - 1)];
+        for (int u = 0; u < N; ++u) pv[u] = pre[min(cs[u] + step, nreg - 1)];
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             const int t = cs[u] + step;
-            if (t < nsub && pv[u] <= ci[u]) cs[u] = t;
+            if (t < nreg && pv[u] <= ci[u]) cs[u] = t;
         }
     }
 #pragma unroll
     for (int u = 0; u < N; ++u)   // slot in [0, count)
-        rec[u] = cand[static_cast<int64_t>(cs[u]) * kSub + (ci[u] - pre[cs[u]])];
+        rec[u] = cand[(static_cast<int64_t>(cs[u]) << rshift) + (ci[u] - pre[cs[u]])];
 }
 
-// Read the N consecutive candidates first + N tid + u, u < N. nzl lists the
-// row's n_nz nonempty sub-chunks in position order, each as (index of its
-// first candidate << kNzSubBits | sub-chunk), n_nz <= kMaxNz (a power of two).
+// Read the N consecutive candidates N tid + u, u < N. nzl lists the
+// row's n_nz nonempty regions in position order, each as (index of its
+// first candidate << kNzBits | region).
 // One binary search over nzl finds the entry of the thread's first index, and
-// since every listed sub-chunk holds at least one candidate, index N tid + u
-// lies at most u entries further, which batches of kWin reads settle. All
+// since every listed region holds at least one candidate, index N tid + u
+// lies at most u entries further, which one batch of N reads settles. All
 // loads are issued before any is used, so the copy costs one search chain and
 // one memory round trip (indices past the end repeat the last candidate's
 // load).
-template <int N, int kMaxNz>
+template <int N>
 __device__ __forceinline__ void read_candidates_runs(const uint2* __restrict__ cand, const int* nzl,
-                                                     int n_nz, int first, int total, uint2 (&rec)[N]) {
-    constexpr int kWin = N % 8 == 0 ? 8 : N % 7 == 0 ? 7 : N % 6 == 0 ? 6 : N;
-    static_assert(N % kWin == 0, "whole windows");
-    const int i0 = min(first + N * static_cast<int>(threadIdx.x), total - 1);
+                                                     int n_nz, int rshift, int top, int total,
+                                                     uint2 (&rec)[N]) {
+    const int i0 = min(N * static_cast<int>(threadIdx.x), total - 1);
     int k = 0;   // the last entry whose first index is <= i0
-#pragma unroll
-    for (int step = kMaxNz / 2; step > 0; step >>= 1) {
+    for (int step = top; step > 0; step >>= 1) {
         const int t = k + step;
-        if (t < n_nz && (nzl[min(t, n_nz - 1)] >> kNzSubBits) <= i0) k = t;
+        if (t < n_nz && (nzl[min(t, n_nz - 1)] >> kNzBits) <= i0) k = t;
     }
+    int ent[N];   // entries k .. k + N - 1 (the last one repeated past the list)
 #pragma unroll
-    for (int w0 = 0; w0 < N; w0 += kWin) {
-        // entries k .. k + kWin (the last one repeated past the list); k holds
-        // the entry of the index before the window, or of its first
-        constexpr int kEnt = kWin + 1;
-        int ent[kEnt];
+    for (int v = 0; v < N; ++v) ent[v] = nzl[min(k + v, n_nz - 1)];
 #pragma unroll
-        for (int v = 0; v < kEnt; ++v) ent[v] = nzl[min(k + v, n_nz - 1)];
-        int at = 0;
+    for (int u = 0; u < N; ++u) {
+        const int i = min(N * static_cast<int>(threadIdx.x) + u, total - 1);
+        int e = ent[0];
 #pragma unroll
-        for (int u = 0; u < kWin; ++u) {
-            const int i = min(first + N * static_cast<int>(threadIdx.x) + w0 + u, total - 1);
-            int e = ent[0];
-#pragma unroll
-            for (int v = 1; v <= u + (w0 > 0 ? 1 : 0) && v < kEnt; ++v)
-                if ((ent[v] >> kNzSubBits) <= i) {
-                    e = ent[v];
-                    if (u == kWin - 1) at = v;
-                }
-            const int sc = e & ((1 << kNzSubBits) - 1);
-            rec[w0 + u] = cand[static_cast<int64_t>(sc) * kSub + (i - (e >> kNzSubBits))];
-        }
-        k += at;
+        for (int v = 1; v <= u && v < N; ++v)
+            if ((ent[v] >> kNzBits) <= i) e = ent[v];
+        const int c = e & ((1 << kNzBits) - 1);
+        rec[u] = cand[(static_cast<int64_t>(c) << rshift) + (i - (e >> kNzBits))];
     }
 }
 
-// The copy of all candidates (first = 0) into LDS in position order: keys at
-// lds[i], words (list << kPosBits | token) at lds[kOffCand + i], or for the
-// wide select at words[i] in global memory. Tracks this thread's min / max
-// key; with fixed bins (hist != nullptr), every candidate is also counted in
-// hist at bin min((key - bkmin) >> bsh, kHistBins - 1), one LDS atomic per
-// candidate (their bins are mostly distinct).
-template <int N, int kOffCand>
+// The copy of all candidates into LDS in position order: keys at lds[i], words
+// (list << kPosBits | token) at lds[kOffCand + i], or for the wide select at
+// words[i] in global memory. Tracks this thread's min / max key; with fixed bins
+// (hist != nullptr), every candidate is also counted in hist at bin
+// min((key - bkmin) >> bsh, kHistBins - 1), one LDS atomic per candidate (their
+// bins are mostly distinct).
+template <int N, int kCap>
 __device__ __forceinline__ void copy_candidates_search(const uint2* __restrict__ cand, const int* pre,
-                                                int nsub, int total, uint32_t* lds,
+                                                int nreg, int rshift, int top, int total, uint32_t* lds, int32_t* words,
                                                 uint32_t& kmin, uint32_t& kmax, int* hist,
                                                 uint32_t bkmin, int bsh) {
+    using L = SelLayout<kCap>;
     uint2 rec[N];
-    read_candidates_search<N, kSelMaxSub>(cand, pre, nsub, 0, total, rec);
+    read_candidates_search<N>(cand, pre, nreg, rshift, top, 0, total, rec);
 #pragma unroll
     for (int u = 0; u < N; ++u) {
         const int ci = u * kSelThreads + static_cast<int>(threadIdx.x);
         const uint32_t kk = float_key(__uint_as_float(rec[u].x));
         if (ci < total) {
             lds[ci] = kk;
-            lds[kOffCand + ci] = rec[u].y;
+            if constexpr (L::kWide) words[ci] = static_cast<int32_t>(rec[u].y);
+            else lds[L::kOffCand + ci] = rec[u].y;
             kmin = min(kmin, kk);
             kmax = max(kmax, kk);
             if (hist) atomicAdd(&hist[fixed_bin(kk, bkmin, bsh)], 1);
@@ -271,14 +258,13 @@ __device__ __forceinline__ void copy_candidates_search(const uint2* __restrict__
 
 template <int N, int kCap>
 __device__ __forceinline__ void copy_candidates_runs(const uint2* __restrict__ cand, const int* nzl,
-                                                int n_nz, int total, uint32_t* lds, int32_t* words,
+                                                int n_nz, int rshift, int top, int total, uint32_t* lds,
                                                 uint32_t& kmin, uint32_t& kmax, int* hist,
                                                 uint32_t bkmin, int bsh) {
     using L = SelLayout<kCap>;
     const int tid = threadIdx.x;
     uint2 rec[N];
-    read_candidates_runs<N, L::kWide ? kSelMaxSubWide : kSelMaxSub>(cand, nzl, n_nz, 0, total, rec);
-    if constexpr (L::kWide) __syncthreads();   // nzl sits in the key area: read by every wave
+    read_candidates_runs<N>(cand, nzl, n_nz, rshift, top, total, rec);
     uint32_t kk[N], cw[N];
 #pragma unroll
     for (int u = 0; u < N; ++u) {
@@ -291,21 +277,19 @@ __device__ __forceinline__ void copy_candidates_runs(const uint2* __restrict__ c
 #pragma unroll
         for (int u = 0; u < N; u += 4) {
             *reinterpret_cast<uint4*>(lds + N * tid + u) = make_uint4(kk[u], kk[u + 1], kk[u + 2], kk[u + 3]);
-            if constexpr (!L::kWide)
-                *reinterpret_cast<uint4*>(lds + L::kOffCand + N * tid + u) =
-                    make_uint4(cw[u], cw[u + 1], cw[u + 2], cw[u + 3]);
+            *reinterpret_cast<uint4*>(lds + L::kOffCand + N * tid + u) =
+                make_uint4(cw[u], cw[u + 1], cw[u + 2], cw[u + 3]);
         }
     } else {
 #pragma unroll
         for (int u = 0; u < N; ++u) {
             lds[N * tid + u] = kk[u];
-            if constexpr (!L::kWide) lds[L::kOffCand + N * tid + u] = cw[u];
+            lds[L::kOffCand + N * tid + u] = cw[u];
         }
     }
 #pragma unroll
     for (int u = 0; u < N; ++u) {
         if (N * tid + u < total) {
-            if constexpr (L::kWide) words[N * tid + u] = static_cast<int32_t>(cw[u]);
             kmin = min(kmin, kk[u]);
             kmax = max(kmax, kk[u]);
             if (hist) atomicAdd(&hist[fixed_bin(kk[u], bkmin, bsh)], 1);
@@ -488,16 +472,13 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
     int* r_tok = reinterpret_cast<int*>(lds + L::kOffRTok);
     uint32_t* chosen = lds + L::kOffBits;
     int* counter = reinterpret_cast<int*>(lds + L::kOffCounter);
-    // the copy by nonempty sub-chunks where two workgroups share a CU (1.2 us
-    // faster at 512 rows), by a search of every index over the sub-chunk
+    // the copy by nonempty regions where two workgroups share a CU (1.2 us
+    // faster at 512 rows), by a search of every index over the region
     // offsets with one workgroup per CU (0.4 us faster at 32 rows: its loads
     // of neighbouring lanes touch neighbouring slots)
-    // (and for the wide rows, whose search would be a step per doubling longer
-    // for every index)
     constexpr bool kWide = L::kWide;
-    constexpr bool kRunsCopy = kCap == kSelCapSmall || kWide;
-    constexpr int kMaxSub = kWide ? kSelMaxSubWide : kSelMaxSub;
-    int* subl = reinterpret_cast<int*>(lds + L::kOffSub);
+    constexpr bool kRunsCopy = kCap == kSelCapSmall;
+    int* regl = reinterpret_cast<int*>(lds + L::kOffRegion);
     __shared__ SelectScratch ss;
     __shared__ BlockScratch bs;
     const int tid = threadIdx.x;
@@ -511,7 +492,8 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
     const int bg = b * D.Hkv + g;
     const int n_r = arg_n_r<kDev>(ba, w, b);
     const int k = arg_topk<kDev>(ba, w, b);
-    const int nsub = (n_r + kSub - 1) / kSub;
+    const int rshift = w.region_shift;
+    const int nreg = (n_r + (1 << rshift) - 1) >> rshift;   // <= kSelMaxRegions (scan_region_shift)
     const int64_t rbase = static_cast<int64_t>(row) * D.rcap;
     const int64_t base = static_cast<int64_t>(bg) * D.rcap;
     int32_t* sel_tok = w.sel_tok + static_cast<int64_t>(row) * D.max_topk;
@@ -541,41 +523,23 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
         bx.bx_wsel = w.bx_wsel + static_cast<int64_t>(row) * D.max_topk;
     }
 
-    // 1) candidate counts: wave w owns sub-chunks [w * spw, (w + 1) * spw), a
-    //    64 of them per step of its lanes. (launch_select sends no row of more
-    //    than kMaxSub sub-chunks here; one would be re-scanned.)
-    constexpr int kCntPer = kMaxSub / kSelThreads;
-    static_assert(kCntPer * kSelThreads == kMaxSub, "sub-chunks per lane");
-    const bool fits_sub = nsub <= kMaxSub;
-    const int spw = fits_sub ? (nsub + kNW - 1) / kNW : 0;
-    const int32_t* cnt = w.cand_cnt + static_cast<int64_t>(row) * D.nsub_cap;
+    // 1) candidate counts, a region per thread
+    const int c = tid < nreg ? w.cand_cnt[static_cast<int64_t>(row) * D.nsub_cap + tid] : 0;
+    const int top = nreg > 1 ? 1 << (31 - __clz(nreg - 1)) : 0;   // the searches' first step
     int total = 0;
-    int n_nz = 0;   // nonempty sub-chunks of the row
-    if (fits_sub) {
-        int c_l[kCntPer], incl[kCntPer];
-        uint64_t nzm[kCntPer];
-#pragma unroll
-        for (int u = 0; u < kCntPer; ++u) {
-            const int in = u * kWave + lane;
-            const int sc = wave * spw + in;
-            c_l[u] = (in < spw && sc < nsub) ? cnt[sc] : 0;
-        }
-        int before = 0, nz_before = 0;   // of the wave's earlier steps
-#pragma unroll
-        for (int u = 0; u < kCntPer; ++u) {
-            incl[u] = wave_incl_scan_i32(c_l[u]) + before;
-            nzm[u] = kRunsCopy ? __builtin_amdgcn_ballot_w64(c_l[u] > 0) : 0ull;
-            if constexpr (kCntPer > 1) before = __builtin_amdgcn_readlane(incl[u], kWave - 1);
-            nz_before += __popcll(nzm[u]);
-        }
+    int n_nz = 0;   // nonempty regions of the row
+    {
+        int incl = wave_incl_scan_i32(c);
+        const uint64_t nzm = kRunsCopy ? __builtin_amdgcn_ballot_w64(c > 0) : 0ull;
         if (lane == kWave - 1) {
-            ss.wave_tot[wave] = incl[kCntPer - 1];
-            ss.wave_aux[wave] = nz_before;
+            ss.wave_tot[wave] = incl;
+            ss.wave_aux[wave] = __popcll(nzm);
         }
         __syncthreads();
-        int wbase = 0, nzbase = 0;
+        constexpr int kCntWaves = kSelMaxRegions / kWave;   // the waves that hold counts
+        int nzbase = 0, wbase = 0;
 #pragma unroll
-        for (int i = 0; i < kNW; ++i) {
+        for (int i = 0; i < kCntWaves; ++i) {
             const int t = ss.wave_tot[i];
             const int z = ss.wave_aux[i];
             wbase += i < wave ? t : 0;
@@ -583,23 +547,17 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
             total += t;
             n_nz += z;
         }
-#pragma unroll
-        for (int u = 0; u < kCntPer; ++u) {
-            const int in = u * kWave + lane;
-            const int sc = wave * spw + in;
-            const int first = incl[u] + wbase - c_l[u];   // row-wide index of the sub-chunk's first candidate
-            if constexpr (kRunsCopy) {
-                // entries are kept while the indices fit beside the sub-chunk
-                // bits (rows of more candidates take the global-memory path)
-                if (c_l[u] > 0) subl[nzbase + lanes_below(nzm[u])] = (min(first, kCap) << kNzSubBits) | sc;
-                nzbase += __popcll(nzm[u]);
-            } else {
-                if (in < spw && sc < nsub) subl[sc] = first;
-            }
+        const int first = incl + wbase - c;   // row-wide index of the region's first candidate
+        if constexpr (kRunsCopy) {
+            // used while the indices fit beside the region bits (rows of more
+            // candidates take the global-memory path)
+            if (c > 0) regl[nzbase + lanes_below(nzm)] = (min(first, kCap) << kNzBits) | tid;
+        } else {
+            if (tid < nreg) regl[tid] = first;
         }
         __syncthreads();
     }
-    const bool fallback = force_fallback || !fits_sub || (n_r > 0 && total < (k > 0 ? k : 1));
+    const bool fallback = force_fallback || (n_r > 0 && total < (k > 0 ? k : 1));
     bx.rescan = fallback;
     float shift = neg_inf;
 
@@ -628,9 +586,10 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
         auto copy = [&](auto tier) {
             constexpr int N = decltype(tier)::value;
             if constexpr (kRunsCopy)
-                copy_candidates_runs<N, kCap>(cand, subl, n_nz, total, lds, words, kmin, kmax, fh, bkmin, bsh);
+                copy_candidates_runs<N, kCap>(cand, regl, n_nz, rshift, top, total, lds, kmin, kmax, fh, bkmin, bsh);
             else
-                copy_candidates_search<N, kOffCand>(cand, subl, nsub, total, lds, kmin, kmax, fh, bkmin, bsh);
+                copy_candidates_search<N, kCap>(cand, regl, nreg, rshift, top, total, lds, words, kmin, kmax, fh,
+                                                bkmin, bsh);
         };
         if (total > kMid * kSelThreads)
             copy(std::integral_constant<int, kCap / kSelThreads>{});
@@ -706,33 +665,23 @@ __device__ __forceinline__ void select_row(const Dims& D, const BatchArgs& ba, c
     } else {
         // ---- slow path: candidates in global memory (many, or the re-scan) ----
         if (!fallback) {
-            // the sub-chunks' first indices into the (unused) key area, then a
-            // batch of kSlowBatch candidates per thread and round trip
+            // a batch of kSlowBatch candidates per thread and round trip, found
+            // over the regions' first indices
             constexpr int kSlowBatch = 8;
-            int* pre = reinterpret_cast<int*>(lds);
             if constexpr (kRunsCopy) {
-                __syncthreads();   // the nonempty sub-chunks may sit there
-                int at = 0;
-                for (int i = 0; i < wave; ++i) at += ss.wave_tot[i];
-#pragma unroll
-                for (int u = 0; u < kCntPer; ++u) {
-                    const int in = u * kWave + lane;
-                    const int sc = wave * spw + in;
-                    const int c = (in < spw && sc < nsub) ? cnt[sc] : 0;
-                    const int inc = wave_incl_scan_i32(c) + at;
-                    if (in < spw && sc < nsub) pre[sc] = inc - c;
-                    at = __builtin_amdgcn_readlane(inc, kWave - 1);
-                }
+                // these are not the (clamped) entries of the nonempty regions
                 __syncthreads();
-            } else {
-                pre = subl;   // the offsets of the search copy
+                int first = wave_incl_scan_i32(c) - c;
+                for (int i = 0; i < wave; ++i) first += ss.wave_tot[i];
+                if (tid < nreg) regl[tid] = first;
+                __syncthreads();
             }
             const uint2* __restrict__ src = w.cand + rbase;
             uint32_t* __restrict__ okey = w.comp_key + rbase;
             int32_t* __restrict__ oword = w.comp_pos + rbase;
             for (int first = 0; first < total; first += kSlowBatch * kSelThreads) {
                 uint2 rec[kSlowBatch];
-                read_candidates_search<kSlowBatch, kMaxSub>(src, pre, nsub, first, total, rec);
+                read_candidates_search<kSlowBatch>(src, regl, nreg, rshift, top, first, total, rec);
 #pragma unroll
                 for (int u = 0; u < kSlowBatch; ++u) {
                     const int i = first + u * kSelThreads + tid;
@@ -819,22 +768,21 @@ static int expected_candidates(int n_r, int k) {
 }
 
 // The capacity of a call's select:
-//  * wide when a row has more sub-chunks or is likely to have more candidates
-//    than the plain one holds: such rows took the global-memory path (one
-//    sequence of 512K tokens, 1%: the call 253 -> 102 us, its select 189 ->
-//    about 40 us);
+//  * wide when a row is likely to have more candidates than the plain one
+//    holds: such rows took the global-memory path (one sequence of 512K tokens,
+//    1%: the select 189 -> 28 us);
 //  * small when the rows outnumber the CUs, two of its workgroups fit in one
 //    CU's LDS and the rows' candidates are likely to fit it.
-// Budgets that are device data are unknown here (the context's largest may be
-// far above the step's), so they pick nothing: a row whose candidates don't
-// fit takes the global-memory path.
+// Budgets that are device data are unknown here, and the context's largest may
+// be far above the step's: up to 1/64 of the tokens is provided for (rows of
+// more take the global-memory path).
 static int select_cap(const Dims& D, const BatchArgs& ba, bool dev_args) {
-    int n_max = 0, c_max = 0;
+    int c_max = 0;
     for (int b = 0; b < D.B; ++b) {
-        n_max = std::max(n_max, ba.n_r[b]);
-        if (!dev_args) c_max = std::max(c_max, expected_candidates(ba.n_r[b], ba.topk[b]));
+        const int k = dev_args ? std::min(D.max_topk, ba.n_r[b] / 64) : ba.topk[b];
+        c_max = std::max(c_max, expected_candidates(ba.n_r[b], k));
     }
-    if (n_max > kSelMaxSub * kSub || c_max > kSelCap) return kSelCapWide;
+    if (c_max > kSelCap) return kSelCapWide;
     const int n_cu = device_cu_count();
     constexpr size_t kStatic = sizeof(SelectScratch) + sizeof(BlockScratch);
     if (n_cu > 0 && D.B * D.Hq > n_cu && c_max <= kSelCapSmall &&
