@@ -620,7 +620,10 @@ __device__ __forceinline__ void dense_load(Raw8<T> (&kr)[R], Raw8<T> (&vr)[R], c
 // sequences of 50001 179 -> 155. Sequences of different lengths take twice the
 // splits where these are long, so that the short ones' share spreads (8 of
 // 15K-30K: 151 -> 144), and none is longer than kDenseRowsMax (16 of
-// 64K-128K: 1176 -> 1143; with nontemporal loads 1007).
+// 64K-128K: 1176 -> 1143; with nontemporal loads 1007). Groups of eight heads
+// are bound by their arithmetic, which spreads better over four splits per CU
+// (32 / 4 heads, 4 of 128K: 2048 rows always 253, two per CU about 260, four
+// 249; 2 of 30K-60K at 16 / 2 heads 108, 43, 39; one of 128K 109, 74, 76).
 static int dense_split_rows(const Dims& D, const BatchInts& lens, size_t partials) {
     int n_min = lens.v[0], n_max = lens.v[0];
     for (int b = 1; b < D.B; ++b) {
@@ -634,7 +637,7 @@ static int dense_split_rows(const Dims& D, const BatchInts& lens, size_t partial
         return rows < kDenseRowsMin ? kDenseRowsMin : rows > kDenseRowsMax ? kDenseRowsMax : rows;
     };
     const int n_cu = device_cu_count() > 0 ? device_cu_count() : 1;
-    int rows = rows_for(2 * n_cu);
+    int rows = rows_for((D.G >= 8 ? 4 : 2) * n_cu);
     if (n_min < n_max && rows > kDenseRowsMax / 4 && rows < kDenseRowsMax) rows = rows_for(4 * n_cu);
     // a buffer that holds no more keeps to the splits it was sized for
     if (static_cast<size_t>(units) * D.G * ((n_max + rows - 1) / rows) > partials) rows = kDenseRows;
