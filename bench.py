@@ -184,7 +184,7 @@ def main() -> int:
                          "(for rocprofv3)")
     ap.add_argument("--summarize-build", nargs=2, metavar=("STATS_CSV", "COMMAND"),
                     help="print the index build's kernel summary (time per kernel, the "
-                         "assignment passes' TFLOP/s against the fp32 peak) and exit")
+                         "searches' TFLOP/s against the bf16 peak) and exit")
     ap.add_argument("--summarize-trace", nargs=2, metavar=("STATS_CSV", "COMMAND"),
                     help="print a summary of a rocprofv3 kernel_stats.csv and exit")
     ap.add_argument("--summarize-pmc", nargs=4, metavar=("STAGE", "FETCH_CSV", "WRITE_CSV", "COMMANDS"),
@@ -665,57 +665,56 @@ def build_only(args, dev) -> int:
 
 
 def build_flops() -> dict:
-    """Distance arithmetic of one build of the bench workload: 3 flops per
-    dimension of a squared distance (a subtraction and a fused multiply-add).
-    Passes: the norm pass (subspace search against the zero model), each
-    coarse iteration and the final lists (coarse + subspace search), each
-    subspace iteration and the final codes (subspace search)."""
+    """Matrix-core arithmetic of one build of the bench workload: products of
+    bf16 parts, 2 flops per dimension of each. A bf16 key meets a coarse
+    center's three parts (3 products), a residual's and a codeword's parts
+    make 6. Passes: a coarse search per coarse iteration and one for the final
+    lists, a subspace search per subspace iteration and one for the final
+    codes."""
     from paper_2609_33746_amd import synth
     wl = synth.workload(WORKLOAD)
     n = wl.batch * wl.n_kv_heads * (wl.max_seq - wl.n_sink - wl.n_local)   # not ragged
     dsub = wl.head_dim // wl.pq_m
-    coarse = 3.0 * n * wl.n_list * wl.head_dim
-    sub = 3.0 * n * wl.pq_m * wl.pq_ksub * dsub
+    coarse = 3 * 2.0 * n * wl.n_list * wl.head_dim
+    sub = 6 * 2.0 * n * wl.pq_m * wl.pq_ksub * dsub
     n_coarse = BUILD_ITERS[0] + 1
-    n_sub = 1 + (BUILD_ITERS[0] + 1) + BUILD_ITERS[1] + 1
+    n_sub = BUILD_ITERS[1] + 1
     return {"tokens": n, "coarse_passes": n_coarse, "subspace_passes": n_sub,
             "flops": n_coarse * coarse + n_sub * sub}
 
 
-FP32_PEAK_TFLOPS = 157.3
+BF16_PEAK_TFLOPS = 2500.0   # dense
 
 
 def summarize_build(stats_csv: str, command: str) -> str:
     """Kernel summary of index builds (rocprofv3 --kernel-trace --stats), with
-    the assignment passes' arithmetic rate against the fp32 peak."""
+    the searches' arithmetic rate against the dense bf16 peak."""
     rows = [r for r in _csv_rows(stats_csv) if "pqhsa" in r["Name"]]
     fl = build_flops()
     out = [f"command: {command}",
            f"build: {BUILD_ITERS[0]} coarse and {BUILD_ITERS[1]} subspace iterations, "
            f"{fl['tokens']} tokens, {fl['coarse_passes']} coarse and {fl['subspace_passes']} "
-           f"subspace assignment passes per build, {fl['flops'] / 1e12:.3f} TFLOP of distances",
+           f"subspace searches per build, {fl['flops'] / 1e12:.3f} TFLOP of bf16 products",
            "kernel  calls  avg_us  min_us  max_us  total_us"]
-    enc_ns, enc_calls, tot_ns = 0.0, 0, 0.0
+    search_ns, sub_calls, tot_ns = 0.0, 0, 0.0
     for r in rows:
         name = r["Name"].split("(")[0]
         calls, tot = int(r["Calls"]), float(r["TotalDurationNs"])
         out.append(f"{name}  {calls}  {float(r['AverageNs']) / 1e3:.2f}  {float(r['MinNs']) / 1e3:.2f}  "
                    f"{float(r['MaxNs']) / 1e3:.2f}  {tot / 1e3:.1f}")
         tot_ns += tot
-        if "encode_kernel" in name or "assign_kernel" in name or "subspace_kernel" in name:
-            enc_ns += tot
-        if "encode_kernel" in name or "subspace_kernel" in name:
-            enc_calls += calls
-    # one subspace-search launch per subspace pass (the coarse searches are
-    # separate launches on the matrix cores)
-    builds = enc_calls / fl["subspace_passes"]
+        if any(k in name for k in ("assign_kernel", "nearest_kernel", "subspace_kernel")):
+            search_ns += tot
+        if "subspace_kernel" in name:
+            sub_calls += calls
+    builds = sub_calls / fl["subspace_passes"]   # one launch per subspace search
     if builds:
-        per_build_ms = enc_ns / builds / 1e6
-        tflops = fl["flops"] / (enc_ns / builds * 1e-9) / 1e12
+        per_build_ms = search_ns / builds / 1e6
+        tflops = fl["flops"] / (search_ns / builds * 1e-9) / 1e12
         out.append(f"builds profiled: {builds:g}; kernel time per build {tot_ns / builds / 1e6:.2f} ms, "
-                   f"of which assignment passes (coarse and subspace searches) {per_build_ms:.2f} ms")
-        out.append(f"assignment passes: {tflops:.1f} TFLOP/s = {tflops / FP32_PEAK_TFLOPS:.3f} of "
-                   f"the {FP32_PEAK_TFLOPS} TFLOP/s fp32 peak")
+                   f"of which searches (assign, nearest and subspace kernels) {per_build_ms:.2f} ms")
+        out.append(f"searches: {tflops:.1f} TFLOP/s of bf16 products = {tflops / BF16_PEAK_TFLOPS:.3f} of "
+                   f"the {BF16_PEAK_TFLOPS:.0f} TFLOP/s dense bf16 peak")
     return "\n".join(out) + "\n"
 
 
