@@ -161,9 +161,10 @@ pqhsa_status pqhsa_index_update(pqhsa_ctx* ctx, const int32_t* new_seq_lens,
  *               directions start the coarse centers (drawn by the caller)
  *   init_pq     DEVICE int32 [B, Hkv, M, K]: token ids in R_b whose residual
  *               slices start the codewords
- * Allocates and frees its own scratch (about 4 (M + 2) bytes per cache slot)
- * and synchronises `stream`. INVALID_ARGUMENT for a starting token outside
- * R_b or an iteration count outside [0, 64]. */
+ * Its scratch is the context's decode workspace where that holds it, else one
+ * allocation, freed before the call returns; synchronises `stream`.
+ * INVALID_ARGUMENT for a starting token outside R_b or an iteration count
+ * outside [0, 64]. */
 pqhsa_status pqhsa_index_build(pqhsa_ctx* ctx, const int32_t* seq_lens, const void* k_cache,
                                const void* v_cache, const int64_t* kv_strides,
                                const int32_t* init_coarse, const int32_t* init_pq,
@@ -288,8 +289,8 @@ pqhsa_status pqhsa_dense_decode(pqhsa_ctx* ctx, const void* q, const void* k_cac
  *   q, k_cache, v_cache, kv_strides, out  as in pqhsa_dense_decode
  *   seq_lens                      HOST int32 [batch], 1 <= N_b <= 2^20
  * Scratch: the split partials of every row, batch * n_q_heads *
- * ceil(max N_b / 2048) of 528 bytes each, live in one fixed 32 MiB device
- * array of the library (a copy on every GPU it runs on, held until the
+ * ceil(max N_b / 2048) of 528 bytes each (more where they fit), live in one
+ * fixed 32 MiB device array of the library (a copy on every GPU it runs on, held until the
  * process ends; its address is looked up on the first call on each device).
  * A call that needs more (for example batch * n_q_heads > 992 at
  * N_b = 131072) returns PQHSA_ERR_INVALID_ARGUMENT before any device work.
