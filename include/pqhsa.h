@@ -161,8 +161,9 @@ pqhsa_status pqhsa_index_update(pqhsa_ctx* ctx, const int32_t* new_seq_lens,
  *               directions start the coarse centers (drawn by the caller)
  *   init_pq     DEVICE int32 [B, Hkv, M, K]: token ids in R_b whose residual
  *               slices start the codewords
- * Its scratch is the context's decode workspace where that holds it, else one
- * allocation, freed before the call returns; synchronises `stream`.
+ * Its scratch is what the context leaves idle during a build, and one
+ * allocation for what does not fit there, freed before the call returns;
+ * synchronises `stream`.
  * INVALID_ARGUMENT for a starting token outside R_b or an iteration count
  * outside [0, 64]. */
 pqhsa_status pqhsa_index_build(pqhsa_ctx* ctx, const int32_t* seq_lens, const void* k_cache,
