@@ -1037,7 +1037,7 @@ __global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
             for (int it = 0; it < kLoads; ++it) {
                 const int idx = it * kNearThreads + tid;
                 const float4 v = next[it];
-                float ss = v.x * v.x + v.y * v.y + v.z * v.z + v.w * v.w;
+                float ss = fmaf(v.w, v.w, fmaf(v.z, v.z, fmaf(v.y, v.y, v.x * v.x)));   // this order, whatever the compiler contracts
 #pragma unroll
                 for (int off = 1; off < 32; off <<= 1) ss += __shfl_xor(ss, off);
                 if (idx % 32 == 0) cn[idx / 32] = ss;

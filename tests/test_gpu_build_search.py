@@ -65,3 +65,69 @@ def test_search_is_nearest(n_r, n_list, heads, bits, dtype):
                             compute_mode="donot_use_mm_for_euclid_dist") ** 2
             assert float((d.gather(1, z[:, None])[:, 0] - d.min(1).values).max()) <= TOL
             assert int(z[80 - 4]) == int(z[70 - 4])
+
+
+def _build(key, val, n_list, bits, dtype, ic, ip, it_coarse, it_pq):
+    m, ksub = (16, 256) if bits == 8 else (8, 16)
+    b, heads, n, _ = key.shape
+    ctx = pqhsa.PQHSA(b, heads, heads, n, n_list, 16, kv_dtype=dtype, pq_m=m, pq_ksub=ksub)
+    ctx.index_build([n] * b, key, val, ic.to(torch.int32).cuda(), ip.to(torch.int32).cuda(), it_coarse, it_pq)
+    return ctx.index_export_tokens()
+
+
+def _bits(x):
+    return x.contiguous().view(torch.int32) if x.dtype == torch.float32 else x
+
+
+def _fma(a, b, c):
+    """a b + c rounded once to 32 bits (the product is exact in float64)."""
+    return (a.double() * b.double() + c.double()).float()
+
+
+def _slices(ix, key, tokens, bits):
+    """u = k / ||k|| and the residual slices u - c_a of the tokens, in 32 bits on the CPU, under the
+    exported norms, lists and centroids: [tokens, 128] and [tokens, M, 128 / M]."""
+    k = key[0, 0, tokens].float().cpu()
+    r = ix["norms"][0, 0, tokens].cpu()
+    u = k / r[:, None]
+    res = u - ix["centroids"][0, 0].cpu()[ix["list_ids"][0, 0, tokens].cpu().long()]
+    return u, res.view(len(tokens), 16 if bits == 8 else 8, -1)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("n_r,n_list,pairs", [(3000, 64, 32), (2900, 129, 50), (4000, 40, 1)])
+def test_near_centers_are_the_choice_of_32_bit_sums(n_r, n_list, pairs, dtype):
+    """Centers in pairs of nearly one direction (the other ones ordinary; with one pair, all
+    the others coincide): the list is the smallest ||c||^2 - 2 u . c of 32-bit sums in the
+    order of the matrix instruction's steps, the first of equal ones. Every token is then a
+    near tie, over 1024 of them per KV head."""
+    say(f"[near centers] n_r={n_r} n_list={n_list} pairs={pairs} {dtype}")
+    n = n_r + 132
+    gen = torch.Generator().manual_seed(n_list)
+    key = torch.randn((1, 1, n, 128), generator=gen)
+    if dtype == "bf16":
+        key = key.to(torch.bfloat16)
+        key[:, :, 5:n:2] = 3 * key[:, :, 4:n - 1:2]
+    else:
+        key[:, :, 5:n:2] = 1.2345 * key[:, :, 4:n - 1:2]
+    pick = 4 + 2 * torch.randperm(n_r // 2, generator=gen)
+    near = torch.stack([pick[:pairs], pick[:pairs] + 1], -1).flatten()
+    rest = pick[pairs:pairs + n_list - 2 * pairs] if pairs > 1 else pick[1:2].expand(n_list - 2)
+    ic = torch.cat([near, rest])[None, None]
+    ip = pick[torch.arange(16 * 256) % 1000].view(1, 1, 16, 256)
+    ix = _build(key.cuda(), key.cuda(), n_list, 8, dtype, ic, ip, 0, 0)
+    t = torch.arange(4, 4 + n_r)
+    u, _ = _slices(ix, key, t, 8)
+    c = ix["centroids"][0, 0].cpu()
+    q4 = c.view(n_list, 32, 4)
+    sq = q4[:, :, 0] * q4[:, :, 0]
+    for e in (1, 2, 3):
+        sq = _fma(q4[:, :, e], q4[:, :, e], sq)
+    while sq.shape[1] > 1:
+        sq = sq[:, 0::2] + sq[:, 1::2]
+    dot = torch.zeros((n_r, n_list))
+    for x in [32 * q + j for j in range(32) for q in range(4)]:
+        dot = _fma(u[:, x:x + 1], c[:, x][None], dot)
+    want = _fma(torch.tensor(-2.0), dot, sq.T).numpy().argmin(1)
+    got = ix["list_ids"][0, 0, t].cpu().numpy()
+    assert (got == want).all(), int((got != want).sum())
