@@ -595,7 +595,7 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
                      {reinterpret_cast<void**>(&bb.dist_c), BG * rc * 4, false},
                      {reinterpret_cast<void**>(&bb.sums), BG * c->codebook_floats * sizeof(unsigned long long), false},
                      {reinterpret_cast<void**>(&bb.seg_hist), std::max<size_t>(1, nseg * BG * L) * 4, false},
-                     {reinterpret_cast<void**>(&bb.counts), BG * per_pq * sizeof(uint32_t), false},
+                     {reinterpret_cast<void**>(&bb.counts), 2 * BG * per_pq * sizeof(uint32_t), false},
                      {reinterpret_cast<void**>(&bb.offs), BG * (L + 1) * 4, false},
                      {reinterpret_cast<void**>(&bb.n_near), BG * sizeof(uint32_t), false}};
         auto round = [](size_t b) { return (b + 255) / 256 * 256; };
@@ -619,6 +619,7 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
                 *w.p = at;
                 at += round(w.bytes);
             }
+        bb.nans = bb.counts + BG * per_pq;
     }
     float* C = c->centroids;
     float* P = c->codebooks;

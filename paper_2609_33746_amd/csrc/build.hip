@@ -715,8 +715,8 @@ __device__ __forceinline__ void asg_fold(float& d, int& i, float od, int oi) {
 // + 7 of every block kb. Returns ||k|| (the sum in row_norm's order), in
 // `scale` what the row stands multiplied by (r for the raw key, 1 for the
 // direction), and in `unit2` ||u||^2. A zero row, or one whose norm
-// overflows, is the zero direction; a row with a NaN or an infinity is
-// nearest to nothing and takes center 0 at distance 0.
+// overflows, is the zero direction; a row with a NaN or an infinity has the
+// scale 0, so that all centers tie and nearest_kernel decides it.
 template <typename T>
 __device__ __forceinline__ float load_token(const T* p, bool present, int half,
                                             bf8_t (&v)[AsgTokens<T>::kParts][kDimBlocks], float& scale,
@@ -1105,9 +1105,10 @@ __global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
 // bf16 parts: the six of a residual's and a codeword's parts that matter,
 // v_mfma_f32_16x16x32_bf16 on 16 codewords x 16 tokens, started at the token's
 // ||r||^2 / 2. These are never below 0 but for rounding, so their bits are
-// compared as integers (a three-way minimum costs one instruction and needs no
-// quieting of NaNs, whose bits are the largest): the search is bound by the
-// VALU, 15 instructions per 8 codewords. Lane group q (lane / 16) owns DQ = DSUB / 4 consecutive
+// compared as integers (a three-way minimum costs one instruction): the search
+// is bound by the VALU, 15 instructions per 8 codewords. A codeword that holds a
+// NaN stands far away, and a residual that holds one (its values all do) takes
+// codeword 0 at distance 0, so no NaN's bits decide anything. Lane group q (lane / 16) owns DQ = DSUB / 4 consecutive
 // dimensions of the subspace in both operands and holds every product of parts
 // of these, so a lane computes, splits and later adds only its own slice of
 // the residual, and no operand crosses lanes. Its 8 kBlocks slots, in order:
@@ -1134,7 +1135,6 @@ constexpr int kSubTiles = 2;                        // token tiles of 16 per wav
 constexpr int kSubStep = kSubWaves * kSubTiles * 16;   // tokens per workgroup step
 constexpr float kSumHi = 1048576.0f;                // 2^20: the fixed point's upper part
 constexpr float kSumLo = 2199023255552.0f;          // 2^41
-constexpr uint32_t kSumNan = 0x80000000u;           // count bit: a member was not a number
 
 template <typename PQ>
 struct SubLayout {
@@ -1173,7 +1173,8 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
     Dims D, BatchInts lo, BatchInts hi, KV kv, const float* __restrict__ centroids,
     const float* __restrict__ codebooks, const int32_t* __restrict__ ids_tm,
     const float* __restrict__ norms_tm, int n_pair, int per, uint8_t* __restrict__ codes_tm,
-    float* __restrict__ dist_f, unsigned long long* __restrict__ sums, uint32_t* __restrict__ counts) {
+    float* __restrict__ dist_f, unsigned long long* __restrict__ sums, uint32_t* __restrict__ counts,
+    uint32_t* __restrict__ nans) {
     using L = SubLayout<PQ>;
     constexpr int M = PQ::M, K = PQ::K, DS = PQ::DSUB, DQ = L::DQ, NB = L::kBlocks, CT = L::kTiles;
     constexpr int kSubs = L::kSubs;
@@ -1208,15 +1209,16 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
         double p2 = 0.0;
 #pragma unroll
         for (int d = 0; d < DS; ++d) p2 += static_cast<double>(p[d]) * p[d];
+        const bool real = p2 < static_cast<double>(kFarCenter);   // not a NaN
 #pragma unroll
         for (int e = 0; e < DQ; ++e) {
             __bf16 x[3];
-            split_bf16(p[sq * DQ + e], x);
+            split_bf16(real ? p[sq * DQ + e] : 0.0f, x);
 #pragma unroll
             for (int u = 0; u < 3; ++u) part[u][e] = x[u];
         }
         __bf16 np[3];
-        split_bf16(static_cast<float>(0.5 * p2), np);
+        split_bf16(real ? static_cast<float>(0.5 * p2) : kFarCenter, np);
         __bf16 slot[8 * NB];
 #pragma unroll
         for (int u = 0; u < 8 * NB; ++u) slot[u] = static_cast<__bf16>(0.0f);
@@ -1273,17 +1275,16 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
                 float x[DQ], c[DQ];
                 load_slice<T, DQ>(kp, x);
                 load_slice<float, DQ>(cp, c);
-                // u = k / r to the last bit or so; the zero direction for a zero or
-                // overflowing norm, NaN where the row holds one or an infinity
+                // u = k / r to the last bit or so; the zero direction for a zero norm
+                // or one that is no number, 0 k for an infinite one
                 const bool live = r[tt] > 0.0f && r[tt] < __builtin_huge_valf();
                 const float inv = __builtin_amdgcn_rcpf(r[tt]);
-                const float dead = r[tt] != r[tt] ? r[tt] : 0.0f;
                 r2[tt] = 0.0f;
                 __bf16 part[3][DQ];
 #pragma unroll
                 for (int e = 0; e < DQ; ++e) {
                     const float qt = x[e] * inv;
-                    const float u = live ? fmaf(fmaf(-qt, r[tt], x[e]), inv, qt) : x[e] * dead;
+                    const float u = live ? fmaf(fmaf(-qt, r[tt], x[e]), inv, qt) : r[tt] > 0.0f ? x[e] * 0.0f : 0.0f;
                     res[tt][e] = u - c[e];
                     r2[tt] = fmaf(res[tt][e], res[tt][e], r2[tt]);
                     __bf16 y[3];
@@ -1372,19 +1373,20 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
                         best_z[tt] = oz;
                     }
                 }
+                if (!(r2[tt] < __builtin_huge_valf())) best[tt] = best_z[tt] = 0;   // a NaN
                 if (tk[tt] >= t1) continue;
                 if constexpr (kTrain) {
-                    bool nan = false;
 #pragma unroll
                     for (int e = 0; e < DQ; ++e) {
-                        nan = nan || !(fabsf(res[tt][e]) <= 4.0f);
+                        const bool nan = !(fabsf(res[tt][e]) < 1024.0f);
                         atomicAdd(&sum[(ss * DS + q * DQ + e) * L::kSumLd + best_z[tt]], to_fixed(nan ? 0.0f : res[tt][e]));
+                        if (nan)
+                            atomicOr(&nans[(static_cast<int64_t>(bg) * M + m) * K + best_z[tt]], 1u << (q * DQ + e));
                     }
                     if (q == 0) {
                         atomicAdd(&cnt[ss * K + best_z[tt]], 1u);
                         dist_f[(static_cast<int64_t>(bg) * M + m) * D.rcap + tk[tt]] = fmaxf(2.0f * __int_as_float(best[tt]), 0.0f);
                     }
-                    if (nan) atomicOr(&cnt[ss * K + best_z[tt]], kSumNan);
                 } else {
                     if (q == 0) codes_tm[(row + tk[tt]) * M + m] = static_cast<uint8_t>(best_z[tt]);
                 }
@@ -1398,11 +1400,8 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
             const unsigned long long v = sum[(i / (K * DS) * DS + i % DS) * L::kSumLd + i / DS % K];
             if (v) atomicAdd(&sums[pz * DS + i], v);
         }
-        for (int i = tid; i < kSubs * K; i += kSubThreads) {
-            const uint32_t n = cnt[i];
-            if (n & ~kSumNan) atomicAdd(&counts[pz + i], n & ~kSumNan);
-            if (n & kSumNan) atomicOr(&counts[pz + i], kSumNan);
-        }
+        for (int i = tid; i < kSubs * K; i += kSubThreads)
+            if (cnt[i]) atomicAdd(&counts[pz + i], cnt[i]);
     }
 }
 
@@ -1410,15 +1409,13 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
 // (an empty one keeps its value, the re-seeding replaces it).
 __global__ __launch_bounds__(256) void codewords_kernel(int64_t n, int dims, const unsigned long long* __restrict__ sums,
                                                         const uint32_t* __restrict__ counts,
-                                                        float* __restrict__ out) {
+                                                        const uint32_t* __restrict__ nans, float* __restrict__ out) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (i >= n) return;
     const uint32_t c = counts[i / dims];
-    if (c & kSumNan) {
-        out[i] = __builtin_nanf("");
-    } else if (c) {
+    if (c) {
         const double s = static_cast<double>(static_cast<long long>(sums[i])) / static_cast<double>(kSumLo);
-        out[i] = static_cast<float>(s / c);
+        out[i] = nans[i / dims] >> (i % dims) & 1u ? __builtin_nanf("") : static_cast<float>(s / c);
     }
 }
 
@@ -1440,19 +1437,19 @@ static hipError_t launch_subspace_t(const Dims& D, const BatchInts& lo, const Ba
     const dim3 grid((n_pair + 7) / 8 * 8 * L::kGroups);
     if (!train) {
         hipLaunchKernelGGL((subspace_kernel<T, PQ, false>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv,
-                           centroids, codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, nullptr, nullptr, nullptr);
+                           centroids, codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, nullptr, nullptr, nullptr, nullptr);
         return hipGetLastError();
     }
     const int64_t n = static_cast<int64_t>(bgs) * PQ::M * PQ::K;
     hipError_t e = hipMemsetAsync(bb.sums, 0, n * PQ::DSUB * sizeof(unsigned long long), s);
-    if (e == hipSuccess) e = hipMemsetAsync(bb.counts, 0, n * sizeof(uint32_t), s);
+    if (e == hipSuccess) e = hipMemsetAsync(bb.counts, 0, 2 * n * sizeof(uint32_t), s);   // and the marks behind them
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((subspace_kernel<T, PQ, true>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv, centroids,
-                       codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, bb.dist_f, bb.sums, bb.counts);
+                       codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, bb.dist_f, bb.sums, bb.counts, bb.nans);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(codewords_kernel, dim3(static_cast<unsigned>((n * PQ::DSUB + 255) / 256)), dim3(256), 0, s,
-                       n * PQ::DSUB, PQ::DSUB, bb.sums, bb.counts, codebooks);
+                       n * PQ::DSUB, PQ::DSUB, bb.sums, bb.counts, bb.nans, codebooks);
     return hipGetLastError();
 }
 

@@ -301,6 +301,7 @@ struct BuildBufs {
     float* dist_f;       // [B, Hkv, M, rcap]
     unsigned long long* sums;   // [B, Hkv, M, K, d / M] residual sums of a training pass (fixed point)
     uint32_t* counts;           // [B, Hkv, M, K] members of a codeword
+    uint32_t* nans;             // [B, Hkv, M, K], behind counts; bit x: a member's dimension x is no number
     int32_t* seg_hist;   // [B, Hkv, segments of 4096 tokens, n_list] counts, then first positions
                          //   (at most 1024 lists)
     void* split;         // split_center_bytes: the centers as matrix-core operands

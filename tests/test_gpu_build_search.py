@@ -131,3 +131,78 @@ def test_near_centers_are_the_choice_of_32_bit_sums(n_r, n_list, pairs, dtype):
     want = _fma(torch.tensor(-2.0), dot, sq.T).numpy().argmin(1)
     got = ix["list_ids"][0, 0, t].cpu().numpy()
     assert (got == want).all(), int((got != want).sum())
+
+
+NAN_CASES = [(8, "bf16"), (4, "f32"), (8, "f32"), (4, "bf16")]
+
+
+@pytest.mark.parametrize("bits,dtype", NAN_CASES)
+def test_a_key_with_a_nan_is_the_zero_direction(bits, dtype):
+    """Rows that hold a NaN, of either sign, in one dimension or in all, have the
+    norm NaN and otherwise count as zero keys: the index is bit for bit the one
+    of the same keys with zeros in their place."""
+    say(f"[nan] bits={bits} {dtype}")
+    m, ksub = (16, 256) if bits == 8 else (8, 16)
+    n_r, n_list, heads = 700, 20, 2
+    n = n_r + 132
+    gen = torch.Generator().manual_seed(bits)
+    key = torch.randn((1, heads, n, 128), generator=gen)
+    key = key.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    val = torch.randn((1, heads, n, 128), generator=gen).to(key.dtype).cuda()
+    ic = torch.stack([4 + torch.randperm(n_r, generator=gen)[:n_list] for _ in range(heads)])[None]
+    ip = 4 + torch.randint(n_r, (1, heads, m, ksub), generator=gen)
+    rows = [50, 51, 333]
+    ip[0, :, :, 3] = rows[0]      # one of them also starts a codeword
+    zero = key.clone()
+    zero[:, :, rows] = 0.0
+    nan = key.clone()
+    nan[:, :, rows[0], 77] = float("nan")
+    nan[:, :, rows[1], 5] = -torch.tensor(float("nan"), dtype=key.dtype)
+    nan[:, :, rows[2]] = -torch.tensor(float("nan"), dtype=key.dtype)
+    want = _build(zero.cuda(), val, n_list, bits, dtype, ic, ip, 1, 2)
+    got = _build(nan.cuda(), val, n_list, bits, dtype, ic, ip, 1, 2)
+    assert torch.isnan(got["norms"][:, :, rows]).all()
+    got["norms"][:, :, rows] = want["norms"][:, :, rows]
+    for name in ("list_means", "centroids", "codebooks"):
+        assert torch.isfinite(got[name]).all(), name
+        assert torch.equal(_bits(got[name]), _bits(want[name])), name
+    for name in ("list_ids", "codes", "norms"):
+        assert torch.equal(_bits(got[name][:, :, 4:4 + n_r]), _bits(want[name][:, :, 4:4 + n_r])), name
+
+
+@pytest.mark.parametrize("bits,dtype", NAN_CASES)
+def test_a_key_with_an_infinity(bits, dtype):
+    """u = k / r of a row with an infinity is NaN there and 0 elsewhere: the row is
+    in list 0, takes codeword 0 in the subspace of the infinity and makes that one
+    dimension of that one codeword NaN, which no other token then chooses."""
+    say(f"[inf] bits={bits} {dtype}")
+    m, ksub = (16, 256) if bits == 8 else (8, 16)
+    ds = 128 // m
+    n_r, n_list, x, row = 700, 20, 77, 91
+    n = n_r + 132
+    gen = torch.Generator().manual_seed(10 + bits)
+    key = torch.randn((1, 1, n, 128), generator=gen)
+    key = key.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    val = torch.randn((1, 1, n, 128), generator=gen).to(key.dtype).cuda()
+    free = [t for t in range(4, 4 + n_r) if t != row]
+    pick = torch.tensor(free)[torch.randperm(n_r - 1, generator=gen)]
+    ic = pick[:n_list][None, None]
+    ip = pick[torch.randint(n_r - 1, (1, 1, m, ksub), generator=gen)]
+    key[:, :, row, x] = float("-inf")
+    ix = _build(key.cuda(), val, n_list, bits, dtype, ic, ip, 0, 1)
+    c = ix["centroids"][0, 0].double()
+    cb = ix["codebooks"][0, 0].double()
+    assert torch.isfinite(c).all()
+    bad = torch.nonzero(torch.isnan(cb)).tolist()
+    assert bad == [[x // ds, 0, x % ds]], bad
+    assert int(ix["list_ids"][0, 0, row]) == 0 and int(ix["codes"][0, 0, row, x // ds]) == 0
+    t = torch.tensor(free, device="cuda")
+    k = key.cuda()[0, 0, t].double()
+    u = k / torch.linalg.vector_norm(k, dim=1, keepdim=True)
+    a = ix["list_ids"][0, 0, t].long()
+    res = (u - c[a]).view(-1, m, ds)
+    for s in range(m):
+        z = ix["codes"][0, 0, t, s].long()
+        d = torch.cdist(res[:, s].contiguous(), cb[s], compute_mode="donot_use_mm_for_euclid_dist") ** 2
+        d = torch.nan_to_num(d, nan=float("inf"))
+        assert float((d.gather(1, z[:, None])[:, 0] - d.min(1).values).max()) <= TOL
