@@ -585,17 +585,17 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
     size_t extra_bytes = 0;
     {
         const size_t nseg = (static_cast<size_t>(std::max(max_n, 0)) + kBuildSegTok - 1) / kBuildSegTok;
+        void* sums = nullptr;
         struct Want {
             void** p;
             size_t bytes;
             bool placed;
         } wants[] = {{reinterpret_cast<void**>(&bb.dist_f), BG * rc * M * 4, false},
                      {&bb.split, split_center_bytes(D), false},
+                     {&sums, sub_sums_bytes(BG * per_pq, kHeadDim / M), false},
                      {reinterpret_cast<void**>(&bb.order), BG * rc * 4, false},
                      {reinterpret_cast<void**>(&bb.dist_c), BG * rc * 4, false},
-                     {reinterpret_cast<void**>(&bb.sums), BG * c->codebook_floats * sizeof(unsigned long long), false},
                      {reinterpret_cast<void**>(&bb.seg_hist), std::max<size_t>(1, nseg * BG * L) * 4, false},
-                     {reinterpret_cast<void**>(&bb.counts), 2 * BG * per_pq * sizeof(uint32_t), false},
                      {reinterpret_cast<void**>(&bb.offs), BG * (L + 1) * 4, false},
                      {reinterpret_cast<void**>(&bb.n_near), BG * sizeof(uint32_t), false}};
         auto round = [](size_t b) { return (b + 255) / 256 * 256; };
@@ -619,7 +619,7 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
                 *w.p = at;
                 at += round(w.bytes);
             }
-        bb.nans = bb.counts + BG * per_pq;
+        bb.sums = sub_sums_at(sums, BG * per_pq, kHeadDim / M);
     }
     float* C = c->centroids;
     float* P = c->codebooks;

@@ -528,10 +528,10 @@ hipError_t launch_reseed(const Dims& D, const BatchInts& lo, const BatchInts& hi
     const dim3 grid(n_problems(D, kind));
     if (kv.bf16)
         hipLaunchKernelGGL(reseed_kernel<bf16_t>, grid, dim3(kGroupThreads), 0, s, D, lo, hi, kind,
-                           kv, ids_tm, norms_tm, centroids, bb.offs, bb.counts, bb.dist_c, bb.dist_f, out);
+                           kv, ids_tm, norms_tm, centroids, bb.offs, bb.sums.counts, bb.dist_c, bb.dist_f, out);
     else
         hipLaunchKernelGGL(reseed_kernel<float>, grid, dim3(kGroupThreads), 0, s, D, lo, hi, kind,
-                           kv, ids_tm, norms_tm, centroids, bb.offs, bb.counts, bb.dist_c, bb.dist_f, out);
+                           kv, ids_tm, norms_tm, centroids, bb.offs, bb.sums.counts, bb.dist_c, bb.dist_f, out);
     return hipGetLastError();
 }
 
@@ -1119,11 +1119,13 @@ __global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
 // A workgroup holds the operands of kSubs subspaces in LDS for all its tokens
 // (one of Pq8's, all eight of Pq4's: 32 KB) and
 // walks a slice of one KV head's tokens, 8 waves of kSubTiles x 16. In a
-// training pass it also adds every residual to its codeword's sum, in 64-bit
-// fixed point (2^-41; the slices are below 2 in size and at most 2^20 of them
-// meet in a sum), so the sums are exact to 2^-42 a member and don't depend on
-// the order: LDS first, then one global addition per workgroup. That replaces
-// the grouping of every subspace's tokens and the gathers of their means.
+// training pass it also adds every residual to its codeword's sum, in LDS
+// first, then with one global addition per workgroup. The sums are fixed
+// point, so they don't depend on the order: 64 bits of 2^-41 (the slices are
+// below 2 in size and at most 2^20 of them meet in a sum) and, for the
+// remainder of the few residuals below 2^-17 that leave one, 64 bits of 2^-84.
+// That replaces the grouping of every subspace's tokens and the gathers of
+// their means.
 // 128K tokens x 8 KV heads, Pq8: a training pass 0.82 ms, the final one 0.74 ms
 // (1.9 ms with v_mfma_f32_16x16x4f32 and a two-key compare per pair; the
 // grouping and gathers took another 1.3 ms a training pass). Two prompts of
@@ -1135,6 +1137,7 @@ constexpr int kSubTiles = 2;                        // token tiles of 16 per wav
 constexpr int kSubStep = kSubWaves * kSubTiles * 16;   // tokens per workgroup step
 constexpr float kSumHi = 1048576.0f;                // 2^20: the fixed point's upper part
 constexpr float kSumLo = 2199023255552.0f;          // 2^41
+constexpr float kRestLo = 19342813113834066795298816.0f;   // 2^84: the remainders' fixed point
 
 template <typename PQ>
 struct SubLayout {
@@ -1158,14 +1161,19 @@ __device__ __forceinline__ uint32_t pack_bf16(__bf16 lo, __bf16 hi) {
            (static_cast<uint32_t>(__builtin_bit_cast(uint16_t, hi)) << 16);
 }
 
-// x in 2^-41 fixed point, to nearest: the multiple of 2^-20 and, exactly, the
-// rest (|x| < 2^10).
-__device__ __forceinline__ unsigned long long to_fixed(float x) {
+// x (|x| < 2^10) in 2^-41 fixed point, to nearest, and in `rest` what that
+// leaves of it, exactly.
+__device__ __forceinline__ unsigned long long to_fixed(float x, float& rest) {
     const float hi = rintf(x * kSumHi);
-    const float lo = rintf(fmaf(hi, -1.0f / kSumHi, x) * kSumLo);
+    const float low = fmaf(hi, -1.0f / kSumHi, x);
+    const float lo = rintf(low * kSumLo);
+    rest = fmaf(lo, -1.0f / kSumLo, low);
     const long long v = static_cast<long long>(static_cast<int>(hi)) * static_cast<long long>(kSumLo / kSumHi) +
                         static_cast<int>(lo);
     return static_cast<unsigned long long>(v);
+}
+__device__ __forceinline__ unsigned long long rest_fixed(float rest) {
+    return static_cast<unsigned long long>(static_cast<long long>(rest * kRestLo));
 }
 
 template <typename T, typename PQ, bool kTrain>
@@ -1173,13 +1181,13 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
     Dims D, BatchInts lo, BatchInts hi, KV kv, const float* __restrict__ centroids,
     const float* __restrict__ codebooks, const int32_t* __restrict__ ids_tm,
     const float* __restrict__ norms_tm, int n_pair, int per, uint8_t* __restrict__ codes_tm,
-    float* __restrict__ dist_f, unsigned long long* __restrict__ sums, uint32_t* __restrict__ counts,
-    uint32_t* __restrict__ nans) {
+    float* __restrict__ dist_f, SubSums out) {
     using L = SubLayout<PQ>;
     constexpr int M = PQ::M, K = PQ::K, DS = PQ::DSUB, DQ = L::DQ, NB = L::kBlocks, CT = L::kTiles;
     constexpr int kSubs = L::kSubs;
     __shared__ uint4 op[kSubs * CT * NB * kWave];                  // codeword operands, in operand order
     __shared__ unsigned long long sum[kTrain ? kSubs * DS * L::kSumLd : 1];
+    __shared__ unsigned long long rests[kTrain ? kSubs * DS * L::kSumLd : 1];
     __shared__ uint32_t cnt[kTrain ? kSubs * K : 1];
     // the kGroups workgroups of a slice have ids congruent mod 8: one XCD,
     // whose L2 then serves the slice's keys and lists to all of them
@@ -1242,7 +1250,7 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
         }
     }
     if constexpr (kTrain) {
-        for (int i = tid; i < kSubs * DS * L::kSumLd; i += kSubThreads) sum[i] = 0ull;
+        for (int i = tid; i < kSubs * DS * L::kSumLd; i += kSubThreads) sum[i] = rests[i] = 0ull;
         for (int i = tid; i < kSubs * K; i += kSubThreads) cnt[i] = 0u;
     }
     __syncthreads();
@@ -1379,9 +1387,12 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
 #pragma unroll
                     for (int e = 0; e < DQ; ++e) {
                         const bool nan = !(fabsf(res[tt][e]) < 1024.0f);
-                        atomicAdd(&sum[(ss * DS + q * DQ + e) * L::kSumLd + best_z[tt]], to_fixed(nan ? 0.0f : res[tt][e]));
+                        const int at = (ss * DS + q * DQ + e) * L::kSumLd + best_z[tt];
+                        float rest;
+                        atomicAdd(&sum[at], to_fixed(nan ? 0.0f : res[tt][e], rest));
+                        if (rest != 0.0f) atomicAdd(&rests[at], rest_fixed(rest));
                         if (nan)
-                            atomicOr(&nans[(static_cast<int64_t>(bg) * M + m) * K + best_z[tt]], 1u << (q * DQ + e));
+                            atomicOr(&out.nans[(static_cast<int64_t>(bg) * M + m) * K + best_z[tt]], 1u << (q * DQ + e));
                     }
                     if (q == 0) {
                         atomicAdd(&cnt[ss * K + best_z[tt]], 1u);
@@ -1397,26 +1408,25 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
         __syncthreads();
         const int64_t pz = (static_cast<int64_t>(bg) * M + m0) * K;
         for (int i = tid; i < kSubs * K * DS; i += kSubThreads) {
-            const unsigned long long v = sum[(i / (K * DS) * DS + i % DS) * L::kSumLd + i / DS % K];
-            if (v) atomicAdd(&sums[pz * DS + i], v);
+            const int at = (i / (K * DS) * DS + i % DS) * L::kSumLd + i / DS % K;
+            if (sum[at]) atomicAdd(&out.sums[pz * DS + i], sum[at]);
+            if (rests[at]) atomicAdd(&out.rests[pz * DS + i], rests[at]);
         }
         for (int i = tid; i < kSubs * K; i += kSubThreads)
-            if (cnt[i]) atomicAdd(&counts[pz + i], cnt[i]);
+            if (cnt[i]) atomicAdd(&out.counts[pz + i], cnt[i]);
     }
 }
 
 // The codewords from a training pass's sums: the mean of each one's members
 // (an empty one keeps its value, the re-seeding replaces it).
-__global__ __launch_bounds__(256) void codewords_kernel(int64_t n, int dims, const unsigned long long* __restrict__ sums,
-                                                        const uint32_t* __restrict__ counts,
-                                                        const uint32_t* __restrict__ nans, float* __restrict__ out) {
+__global__ __launch_bounds__(256) void codewords_kernel(int64_t n, int dims, SubSums in, float* __restrict__ out) {
     const int64_t i = static_cast<int64_t>(blockIdx.x) * 256 + threadIdx.x;
     if (i >= n) return;
-    const uint32_t c = counts[i / dims];
-    if (c) {
-        const double s = static_cast<double>(static_cast<long long>(sums[i])) / static_cast<double>(kSumLo);
-        out[i] = nans[i / dims] >> (i % dims) & 1u ? __builtin_nanf("") : static_cast<float>(s / c);
-    }
+    const uint32_t c = in.counts[i / dims];
+    if (!c) return;
+    const double s = static_cast<double>(static_cast<long long>(in.sums[i])) / static_cast<double>(kSumLo) +
+                     static_cast<double>(static_cast<long long>(in.rests[i])) / static_cast<double>(kRestLo);
+    out[i] = in.nans[i / dims] >> (i % dims) & 1u ? __builtin_nanf("") : static_cast<float>(s / c);
 }
 
 template <typename T, typename PQ>
@@ -1437,19 +1447,18 @@ static hipError_t launch_subspace_t(const Dims& D, const BatchInts& lo, const Ba
     const dim3 grid((n_pair + 7) / 8 * 8 * L::kGroups);
     if (!train) {
         hipLaunchKernelGGL((subspace_kernel<T, PQ, false>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv,
-                           centroids, codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, nullptr, nullptr, nullptr, nullptr);
+                           centroids, codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, nullptr, SubSums{});
         return hipGetLastError();
     }
     const int64_t n = static_cast<int64_t>(bgs) * PQ::M * PQ::K;
-    hipError_t e = hipMemsetAsync(bb.sums, 0, n * PQ::DSUB * sizeof(unsigned long long), s);
-    if (e == hipSuccess) e = hipMemsetAsync(bb.counts, 0, 2 * n * sizeof(uint32_t), s);   // and the marks behind them
+    hipError_t e = hipMemsetAsync(bb.sums.sums, 0, sub_sums_bytes(n, PQ::DSUB), s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((subspace_kernel<T, PQ, true>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv, centroids,
-                       codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, bb.dist_f, bb.sums, bb.counts, bb.nans);
+                       codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, bb.dist_f, bb.sums);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(codewords_kernel, dim3(static_cast<unsigned>((n * PQ::DSUB + 255) / 256)), dim3(256), 0, s,
-                       n * PQ::DSUB, PQ::DSUB, bb.sums, bb.counts, bb.nans, codebooks);
+                       n * PQ::DSUB, PQ::DSUB, bb.sums, codebooks);
     return hipGetLastError();
 }
 

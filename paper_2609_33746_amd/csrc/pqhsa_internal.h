@@ -294,14 +294,28 @@ hipError_t launch_encode_update(const Dims& D, const BatchInts& lo, const BatchI
                                 float* norms_tm, float* part_d, int32_t* part_i, int64_t part_ints,
                                 hipStream_t s);
 // index build steps (k-means over the tokens [lo[b], hi[b]) of each (b, kv head))
+// The sums of a training pass of the codewords, one piece of memory (see
+// sub_sums_bytes and sub_sums_at).
+struct SubSums {
+    unsigned long long* sums;    // [B, Hkv, M, K, d / M] residual sums (fixed point)
+    unsigned long long* rests;   // the same, what the sums' step leaves of the residuals
+    uint32_t* counts;            // [B, Hkv, M, K] members of a codeword
+    uint32_t* nans;              // [B, Hkv, M, K] bit x: a member's dimension x is no number
+};
+inline size_t sub_sums_bytes(int64_t codewords, int dims) {
+    return static_cast<size_t>(codewords) * (dims * 2 * sizeof(unsigned long long) + 2 * sizeof(uint32_t));
+}
+inline SubSums sub_sums_at(void* at, int64_t codewords, int dims) {
+    unsigned long long* sums = static_cast<unsigned long long*>(at);
+    uint32_t* counts = reinterpret_cast<uint32_t*>(sums + 2 * codewords * dims);
+    return SubSums{sums, sums + codewords * dims, counts, counts + codewords};
+}
 struct BuildBufs {
     int32_t* order;      // [B, Hkv, rcap] tokens grouped by list, in id order within a list
     int32_t* offs;       // [B, Hkv, n_list + 1]
     float* dist_c;       // [B, Hkv, rcap]
     float* dist_f;       // [B, Hkv, M, rcap]
-    unsigned long long* sums;   // [B, Hkv, M, K, d / M] residual sums of a training pass (fixed point)
-    uint32_t* counts;           // [B, Hkv, M, K] members of a codeword
-    uint32_t* nans;             // [B, Hkv, M, K], behind counts; bit x: a member's dimension x is no number
+    SubSums sums;
     int32_t* seg_hist;   // [B, Hkv, segments of 4096 tokens, n_list] counts, then first positions
                          //   (at most 1024 lists)
     void* split;         // split_center_bytes: the centers as matrix-core operands

@@ -206,3 +206,24 @@ def test_a_key_with_an_infinity(bits, dtype):
         d = torch.cdist(res[:, s].contiguous(), cb[s], compute_mode="donot_use_mm_for_euclid_dist") ** 2
         d = torch.nan_to_num(d, nan=float("inf"))
         assert float((d.gather(1, z[:, None])[:, 0] - d.min(1).values).max()) <= TOL
+
+
+@pytest.mark.parametrize("bits,dtype,size", [(8, "f32", 1e-6), (4, "f32", 1e-6)])
+def test_a_codeword_of_one_token_is_its_residual(bits, dtype, size):
+    """As many tokens as codewords, each the start of one: after a training pass every
+    codeword is the mean of one residual, which is that residual bit for bit (the
+    direction by an exactly rounded division, the sum without a step of its own)."""
+    say(f"[one] bits={bits} {dtype} size={size}")
+    m, ksub = (16, 256) if bits == 8 else (8, 16)
+    n = ksub + 132
+    gen = torch.Generator().manual_seed(3 * bits)
+    key = size * torch.randn((1, 1, n, 128), generator=gen)
+    if size < 1.0:   # directions of one large dimension: the residuals of the others are as small as they are
+        key[..., 0] = 1.0
+    key = key.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    ic = torch.full((1, 1, 1), 4)
+    ip = (4 + torch.arange(ksub)).expand(1, 1, m, ksub)
+    ix = _build(key.cuda(), key.cuda(), 1, bits, dtype, ic, ip, 0, 1)
+    _, res = _slices(ix, key, torch.arange(4, 4 + ksub), bits)
+    for s in range(0 if size >= 1.0 else 1, m):
+        assert torch.equal(_bits(ix["codebooks"][0, 0, s].cpu()), _bits(res[:, s].contiguous())), s
