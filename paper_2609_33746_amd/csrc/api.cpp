@@ -596,6 +596,7 @@ pqhsa_status pqhsa_index_build(pqhsa_ctx* c, const int32_t* seq_lens, const void
                      {reinterpret_cast<void**>(&bb.order), BG * rc * 4, false},
                      {reinterpret_cast<void**>(&bb.dist_c), BG * rc * 4, false},
                      {reinterpret_cast<void**>(&bb.seg_hist), std::max<size_t>(1, nseg * BG * L) * 4, false},
+                     {reinterpret_cast<void**>(&bb.ties), BG * M * tie_words(D) * sizeof(uint32_t), false},
                      {reinterpret_cast<void**>(&bb.offs), BG * (L + 1) * 4, false},
                      {reinterpret_cast<void**>(&bb.n_near), BG * sizeof(uint32_t), false}};
         auto round = [](size_t b) { return (b + 255) / 256 * 256; };

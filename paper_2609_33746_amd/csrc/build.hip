@@ -5,8 +5,9 @@
 // Lloyd iteration is:
 //
 //  * assign_kernel (coarse) or subspace_kernel: the nearest center of every
-//    token, on the matrix cores. subspace_kernel also adds the residuals to
-//    their codewords' sums.
+//    token, on the bf16 matrix cores; the near ties they leave go to
+//    nearest_kernel or ties_kernel, on the 32-bit ones. The subspace kernels also
+//    add the residuals to their codewords' sums.
 //  * coarse: group_count / scan / place_kernel (group_kernel above 1024
 //    lists), a stable counting sort of a KV head's tokens by list, so that
 //    every mean adds its members in a fixed order, and centers_kernel, the
@@ -23,6 +24,7 @@
 
 #include "device_common.h"
 #include "pqhsa_internal.h"
+#include "radix_select.h"
 
 namespace pqhsa {
 
@@ -1106,9 +1108,12 @@ __global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
 // v_mfma_f32_16x16x32_bf16 on 16 codewords x 16 tokens, started at the token's
 // ||r||^2 / 2. These are never below 0 but for rounding, so their bits are
 // compared as integers (a three-way minimum costs one instruction): the search
-// is bound by the VALU, 15 instructions per 8 codewords. A codeword that holds a
-// NaN stands far away, and a residual that holds one (its values all do) takes
-// codeword 0 at distance 0, so no NaN's bits decide anything. Lane group q (lane / 16) owns DQ = DSUB / 4 consecutive
+// is bound by the VALU, 16 instructions per 8 codewords, one of them for the
+// second smallest value. A token whose two smallest are closer than the
+// arithmetic tells apart (kTieGap below) is only marked, one bit per token and
+// subspace, and ties_kernel decides it; so is one whose residual holds a NaN
+// (all its values then do), and a codeword that holds one stands far away.
+// Lane group q (lane / 16) owns DQ = DSUB / 4 consecutive
 // dimensions of the subspace in both operands and holds every product of parts
 // of these, so a lane computes, splits and later adds only its own slice of
 // the residual, and no operand crosses lanes. Its 8 kBlocks slots, in order:
@@ -1126,10 +1131,9 @@ __global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
 // remainder of the few residuals below 2^-17 that leave one, 64 bits of 2^-84.
 // That replaces the grouping of every subspace's tokens and the gathers of
 // their means.
-// 128K tokens x 8 KV heads, Pq8: a training pass 0.82 ms, the final one 0.74 ms
-// (1.9 ms with v_mfma_f32_16x16x4f32 and a two-key compare per pair; the
-// grouping and gathers took another 1.3 ms a training pass). Two prompts of
-// 40K, Pq4: 0.14 and 0.09 ms (0.20 ms, and 0.4 ms).
+// 128K tokens x 8 KV heads, Pq8: a training pass 0.85 ms, the final one 0.77 ms (1.9 ms with v_mfma_f32_16x16x4f32
+// and a two-key compare per pair; the grouping and gathers took another 1.3 ms
+// a training pass). Two prompts of 40K, Pq4: 0.15 and 0.10 ms (0.20 ms, and 0.4 ms).
 // ---------------------------------------------------------------------------
 constexpr int kSubThreads = 512;
 constexpr int kSubWaves = kSubThreads / kWave;
@@ -1149,6 +1153,14 @@ struct SubLayout {
     static constexpr int kNormSlot = 5 * DQ;
     static constexpr int kLastSlot = 8 * kBlocks - DQ;
     static constexpr int kPerCu = 2;                         // workgroups a CU's registers hold
+    // Half squared distances closer than kTieGap (||r||^2 + D), D the smaller
+    // squared distance, are a tie. With u = 2^-24, either sum's roundings and
+    // ||p||^2 <= 2 (||r||^2 + D): one of the 32-bit matrix cores' is off by at
+    // most (DSUB + 1) u (||r||^2 + 2 ||p||^2), one of the parts' by its 8 DSUB
+    // slots' u (||r||^2 + ||p||^2), both for two codewords: below 54 DSUB u
+    // (||r||^2 + D) in all. One (token, subspace) in some 2000 at 128K tokens
+    // with Pq8, in 1200 at 40K with Pq4.
+    static constexpr float kTieGap = 64.0f * PQ::DSUB / 16777216.0f;
     // the LDS sums, [subspace][dimension][codeword]: a row stride that puts
     // the four lane groups' dimensions 16 banks apart
     static constexpr int kSumLd = PQ::K + (PQ::K >= 256 ? 4 : 2);
@@ -1176,12 +1188,15 @@ __device__ __forceinline__ unsigned long long rest_fixed(float rest) {
     return static_cast<unsigned long long>(static_cast<long long>(rest * kRestLo));
 }
 
+// The middle one of three.
+__device__ __forceinline__ int med3(int a, int b, int c) { return max(min(a, b), min(max(a, b), c)); }
+
 template <typename T, typename PQ, bool kTrain>
 __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
     Dims D, BatchInts lo, BatchInts hi, KV kv, const float* __restrict__ centroids,
     const float* __restrict__ codebooks, const int32_t* __restrict__ ids_tm,
     const float* __restrict__ norms_tm, int n_pair, int per, uint8_t* __restrict__ codes_tm,
-    float* __restrict__ dist_f, SubSums out) {
+    float* __restrict__ dist_f, SubSums out, uint32_t* __restrict__ ties, int tie_words) {
     using L = SubLayout<PQ>;
     constexpr int M = PQ::M, K = PQ::K, DS = PQ::DSUB, DQ = L::DQ, NB = L::kBlocks, CT = L::kTiles;
     constexpr int kSubs = L::kSubs;
@@ -1262,13 +1277,23 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
     const __bf16 one = static_cast<__bf16>(1.0f), zero = static_cast<__bf16>(0.0f);
     for (int s0 = t0; s0 < t1; s0 += kSubStep) {
         int tk[kSubTiles], a[kSubTiles];
-        float r[kSubTiles];
+        float r[kSubTiles], inv[kSubTiles];
+        bool none[kSubTiles];
 #pragma unroll
         for (int tt = 0; tt < kSubTiles; ++tt) {
             tk[tt] = s0 + (wave * kSubTiles + tt) * 16 + col;
             const int t = min(tk[tt], t1 - 1);   // tokens past the slice repeat its last, unused
             a[tt] = min(max(ids_tm[row + t], 0), D.n_list - 1);
-            r[tt] = norms_tm[row + t];
+            // u = k / r: by the rounded reciprocal and one correction, which is the
+            // rounded quotient (Markstein; above 2^-100, where no remainder
+            // underflows); the zero direction for a zero norm or one that is no
+            // number, 0 k for an infinite one
+            const float n = norms_tm[row + t];
+            none[tt] = !(n > 0.0f);
+            const bool live = n > 0.0f && n < __builtin_huge_valf();
+            const float y = __builtin_amdgcn_rcpf(n);
+            r[tt] = live ? n : 0.0f;
+            inv[tt] = live ? fmaf(fmaf(-n, y, 1.0f), y, y) : 0.0f;
         }
 #pragma unroll 1
         for (int ss = 0; ss < kSubs; ++ss) {
@@ -1283,17 +1308,13 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
                 float x[DQ], c[DQ];
                 load_slice<T, DQ>(kp, x);
                 load_slice<float, DQ>(cp, c);
-                // u = k / r to the last bit or so; the zero direction for a zero norm
-                // or one that is no number, 0 k for an infinite one
-                const bool live = r[tt] > 0.0f && r[tt] < __builtin_huge_valf();
-                const float inv = __builtin_amdgcn_rcpf(r[tt]);
                 r2[tt] = 0.0f;
                 __bf16 part[3][DQ];
 #pragma unroll
                 for (int e = 0; e < DQ; ++e) {
-                    const float qt = x[e] * inv;
-                    const float u = live ? fmaf(fmaf(-qt, r[tt], x[e]), inv, qt) : r[tt] > 0.0f ? x[e] * 0.0f : 0.0f;
-                    res[tt][e] = u - c[e];
+                    const float xe = none[tt] ? 0.0f : x[e];
+                    const float qt = xe * inv[tt];
+                    res[tt][e] = fmaf(fmaf(-qt, r[tt], xe), inv[tt], qt) - c[e];
                     r2[tt] = fmaf(res[tt][e], res[tt][e], r2[tt]);
                     __bf16 y[3];
                     split_bf16(-res[tt][e], y);
@@ -1324,7 +1345,8 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
             f4_t half_r2[kSubTiles];
             constexpr int kAtOnce = CT < 2 ? CT : 2;   // codeword tiles per comparison
             constexpr int kOuts = 4 * kAtOnce;
-            int best[kSubTiles], best_z[kSubTiles], keep[kSubTiles][kOuts];   // keep: the best group's values
+            // keep: the best group's values; second: the second smallest of the groups' smallest
+            int best[kSubTiles], second[kSubTiles], best_z[kSubTiles], keep[kSubTiles][kOuts];
 #pragma unroll
             for (int tt = 0; tt < kSubTiles; ++tt) {
                 r2[tt] += __shfl_xor(r2[tt], 16);
@@ -1355,6 +1377,7 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
                     m1 = min(m1, v[kOuts - 1]);
                     // strictly below: the first of equal groups stays
                     const bool down = first || m1 < best[tt];
+                    second[tt] = first ? 0x7fffffff : med3(best[tt], m1, second[tt]);
                     best[tt] = first ? m1 : min(best[tt], m1);
                     best_z[tt] = down ? ct0 : best_z[tt];
 #pragma unroll
@@ -1366,42 +1389,55 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
             // in registers across the steps
 #pragma unroll 1
             for (int ct0 = kAtOnce; ct0 < CT; ct0 += kAtOnce) group(ct0, false);
+            uint64_t tied[kSubTiles];
+            static_assert(kSubTiles == 2, "a word of ties per wave and step");
 #pragma unroll
             for (int tt = 0; tt < kSubTiles; ++tt) {
                 int e = 0;   // the first of the group's values that is the smallest
 #pragma unroll
                 for (int u = kOuts - 1; u >= 0; --u) e = keep[tt][u] == best[tt] ? u : e;
+                int low = keep[tt][0], next = 0x7fffffff;   // and the second smallest
+#pragma unroll
+                for (int u = 1; u < kOuts; ++u) {
+                    next = med3(low, keep[tt][u], next);
+                    low = min(low, keep[tt][u]);
+                }
+                second[tt] = min(second[tt], next);
                 best_z[tt] = (best_z[tt] + e / 4) * 16 + 4 * q + e % 4;
 #pragma unroll
                 for (int off = 16; off < kWave; off <<= 1) {
                     const int od = __shfl_xor(best[tt], off);
                     const int oz = __shfl_xor(best_z[tt], off);
+                    second[tt] = min(max(best[tt], od), min(second[tt], __shfl_xor(second[tt], off)));
                     if (od < best[tt] || (od == best[tt] && oz < best_z[tt])) {
                         best[tt] = od;
                         best_z[tt] = oz;
                     }
                 }
-                if (!(r2[tt] < __builtin_huge_valf())) best[tt] = best_z[tt] = 0;   // a NaN
-                if (tk[tt] >= t1) continue;
+                const float h = __int_as_float(best[tt]);
+                const bool tie = !(__int_as_float(second[tt]) - h > L::kTieGap * fmaf(2.0f, h, r2[tt]));   // also with a NaN
+                tied[tt] = __ballot(tie && tk[tt] < t1);
+                if (tie || tk[tt] >= t1) continue;
                 if constexpr (kTrain) {
 #pragma unroll
-                    for (int e = 0; e < DQ; ++e) {
-                        const bool nan = !(fabsf(res[tt][e]) < 1024.0f);
-                        const int at = (ss * DS + q * DQ + e) * L::kSumLd + best_z[tt];
+                    for (int e2 = 0; e2 < DQ; ++e2) {
+                        const int at = (ss * DS + q * DQ + e2) * L::kSumLd + best_z[tt];
                         float rest;
-                        atomicAdd(&sum[at], to_fixed(nan ? 0.0f : res[tt][e], rest));
+                        atomicAdd(&sum[at], to_fixed(res[tt][e2], rest));
                         if (rest != 0.0f) atomicAdd(&rests[at], rest_fixed(rest));
-                        if (nan)
-                            atomicOr(&out.nans[(static_cast<int64_t>(bg) * M + m) * K + best_z[tt]], 1u << (q * DQ + e));
                     }
                     if (q == 0) {
                         atomicAdd(&cnt[ss * K + best_z[tt]], 1u);
-                        dist_f[(static_cast<int64_t>(bg) * M + m) * D.rcap + tk[tt]] = fmaxf(2.0f * __int_as_float(best[tt]), 0.0f);
+                        dist_f[(static_cast<int64_t>(bg) * M + m) * D.rcap + tk[tt]] = fmaxf(2.0f * h, 0.0f);
                     }
                 } else {
                     if (q == 0) codes_tm[(row + tk[tt]) * M + m] = static_cast<uint8_t>(best_z[tt]);
                 }
             }
+            // the step's 32 tokens of the wave, a bit each (s0 - lo is a multiple of kSubStep)
+            if (lane == 0)
+                ties[(static_cast<int64_t>(bg) * M + m) * tie_words + (s0 - lo.v[b]) / 32 + wave] =
+                    static_cast<uint32_t>(tied[0] & 0xffffu) | static_cast<uint32_t>(tied[1] & 0xffffu) << 16;
         }
     }
     if constexpr (kTrain) {
@@ -1414,6 +1450,123 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
         }
         for (int i = tid; i < kSubs * K; i += kSubThreads)
             if (cnt[i]) atomicAdd(&out.counts[pz + i], cnt[i]);
+    }
+}
+
+// ---------------------------------------------------------------------------
+// ties_kernel: the codewords of the tokens that subspace_kernel marked, by the
+// distance the 32-bit matrix cores give (v_mfma_f32_16x16x4f32, lane group q with
+// dimensions q DSUB / 4 + s in step s; ties to the smaller codeword), so the
+// choice is the one that those alone would make. A residual that holds a NaN takes
+// codeword 0 at distance 0. In training it also adds them to the sums; a
+// residual that is a NaN marks its codeword's dimension in `nans`.
+//
+// One workgroup per problem and kTieWords words of marks, which it lists first;
+// most find a few tokens or none, so each wave takes 16 of them against all the
+// codewords: 22 us a pass at
+// 128K tokens x 8 KV heads with Pq8 (2.2 ms where all codewords coincide). With it
+// and the second smallest value subspace_kernel takes 0.85 and 0.77 ms there,
+// 0.75 and 0.69 without.
+// ---------------------------------------------------------------------------
+constexpr int kTieThreads = 256;
+constexpr int kTieWords = kTieThreads;
+
+template <typename T, typename PQ, bool kTrain>
+__global__ __launch_bounds__(kTieThreads) void ties_kernel(
+    Dims D, BatchInts lo, BatchInts hi, KV kv, const float* __restrict__ centroids,
+    const float* __restrict__ codebooks, const int32_t* __restrict__ ids_tm, const float* __restrict__ norms_tm,
+    const uint32_t* __restrict__ ties, int tie_words, uint8_t* __restrict__ codes_tm, float* __restrict__ dist_f,
+    SubSums out) {
+    constexpr int M = PQ::M, K = PQ::K, DS = PQ::DSUB, S = DS / 4, LD = DS + 1;   // odd row stride: distinct banks
+    __shared__ float rows[K * LD];
+    __shared__ float pn[K];                        // ||p||^2
+    __shared__ uint16_t list[kTieWords * 32];      // the marked tokens, from the first word's first
+    __shared__ SelectScratch scan;
+    static_assert(kTieWords * 32 <= 65536, "16-bit token offsets");
+    const int p = blockIdx.x;
+    const int bg = p / M, m = p % M;
+    const int b = bg / D.Hkv, g = bg % D.Hkv;
+    const int first = lo.v[b] + static_cast<int>(blockIdx.y) * kTieWords * 32;
+    if (first >= hi.v[b]) return;
+    const int tid = threadIdx.x;
+    const int wave = tid / kWave;
+    const int lane = lane_id();
+    const int col = lane % 16;
+    const int q = lane / 16;
+    uint32_t bits = first + tid * 32 < hi.v[b]
+                        ? ties[static_cast<int64_t>(p) * tie_words + blockIdx.y * kTieWords + tid] : 0u;
+    int total = 0;
+    int at = block_excl_scan<kTieThreads>(__popc(bits), total, scan);
+    if (total == 0) return;
+    for (; bits; bits &= bits - 1) list[at++] = static_cast<uint16_t>(tid * 32 + __ffs(bits) - 1);
+    const float* cb = codebooks + static_cast<int64_t>(p) * K * DS;
+    for (int i = tid; i < K * DS; i += kTieThreads) rows[i / DS * LD + i % DS] = cb[i];
+    __syncthreads();
+    for (int z = tid; z < K; z += kTieThreads) {
+        float ss = 0.0f;
+#pragma unroll
+        for (int x = 0; x < DS; ++x) ss = fmaf(rows[z * LD + x], rows[z * LD + x], ss);
+        pn[z] = ss;
+    }
+    __syncthreads();
+    const int64_t row = static_cast<int64_t>(bg) * D.rcap;
+    for (int i0 = wave * 16; i0 < total; i0 += kTieThreads / kWave * 16) {
+        const bool present = i0 + col < total;
+        const int t = first + list[min(i0 + col, total - 1)];
+        const int a = min(max(ids_tm[row + t], 0), D.n_list - 1);
+        const float r = norms_tm[row + t];
+        const int d0 = m * DS + q * S;
+        float x[S], c[S], res[S];
+        load_slice<T, S>(static_cast<const T*>(kv.k) + b * kv.sb + g * kv.sh + static_cast<int64_t>(t) * kv.sn + d0, x);
+        load_slice<float, S>(centroids + (static_cast<int64_t>(bg) * D.n_list + a) * kHeadDim + d0, c);
+        float r2 = 0.0f;
+#pragma unroll
+        for (int s2 = 0; s2 < S; ++s2) {
+            res[s2] = (r > 0.0f ? x[s2] / r : 0.0f) - c[s2];
+            r2 = fmaf(res[s2], res[s2], r2);
+        }
+        float best_d = __builtin_huge_valf();
+        int best_z = 0;   // a valid codeword even if every distance is NaN
+#pragma unroll 2
+        for (int ct = 0; ct < K / 16; ++ct) {
+            f4_t acc = f4_t{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+            for (int s2 = 0; s2 < S; ++s2)
+                acc = __builtin_amdgcn_mfma_f32_16x16x4f32(rows[(ct * 16 + col) * LD + q * S + s2], res[s2], acc, 0, 0, 0);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const int z = ct * 16 + 4 * q + i;
+                near_fold(best_d, best_z, fmaf(-2.0f, acc[i], pn[z]), z);
+            }
+        }
+#pragma unroll
+        for (int off = 16; off < kWave; off <<= 1) {
+            r2 += __shfl_xor(r2, off);
+            const float od = __shfl_xor(best_d, off);
+            const int oz = __shfl_xor(best_z, off);
+            near_fold(best_d, best_z, od, oz);
+        }
+        if (!present) continue;
+        if constexpr (kTrain) {
+            const int64_t pz = static_cast<int64_t>(p) * K + best_z;
+#pragma unroll
+            for (int s2 = 0; s2 < S; ++s2) {
+                const int d = q * S + s2;
+                if (!(fabsf(res[s2]) < 1024.0f)) {   // a NaN
+                    atomicOr(&out.nans[pz], 1u << d);
+                    continue;
+                }
+                float rest;
+                atomicAdd(&out.sums[pz * DS + d], to_fixed(res[s2], rest));
+                if (rest != 0.0f) atomicAdd(&out.rests[pz * DS + d], rest_fixed(rest));
+            }
+            if (q == 0) {
+                atomicAdd(&out.counts[pz], 1u);
+                dist_f[static_cast<int64_t>(p) * D.rcap + t] = fmaxf(best_d + r2, 0.0f);
+            }
+        } else if (q == 0) {
+            codes_tm[(row + t) * M + m] = static_cast<uint8_t>(best_z);
+        }
     }
 }
 
@@ -1445,16 +1598,27 @@ static hipError_t launch_subspace_t(const Dims& D, const BatchInts& lo, const Ba
     const int per = ((max_n + slices - 1) / slices + kSubStep - 1) / kSubStep * kSubStep;
     const int n_pair = bgs * ((max_n + per - 1) / per);
     const dim3 grid((n_pair + 7) / 8 * 8 * L::kGroups);
+    const int words = tie_words(D);
+    const dim3 tie_grid(bgs * PQ::M, (max_n + kTieWords * 32 - 1) / (kTieWords * 32));
+    const SubSums none{};
     if (!train) {
-        hipLaunchKernelGGL((subspace_kernel<T, PQ, false>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv,
-                           centroids, codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, nullptr, SubSums{});
+        hipLaunchKernelGGL((subspace_kernel<T, PQ, false>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv, centroids,
+                           codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, nullptr, none, bb.ties, words);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((ties_kernel<T, PQ, false>), tie_grid, dim3(kTieThreads), 0, s, D, lo, hi, kv, centroids,
+                           codebooks, ids_tm, norms_tm, bb.ties, words, codes_tm, nullptr, none);
         return hipGetLastError();
     }
     const int64_t n = static_cast<int64_t>(bgs) * PQ::M * PQ::K;
     hipError_t e = hipMemsetAsync(bb.sums.sums, 0, sub_sums_bytes(n, PQ::DSUB), s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((subspace_kernel<T, PQ, true>), grid, dim3(kSubThreads), 0, s, D, lo, hi, kv, centroids,
-                       codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, bb.dist_f, bb.sums);
+                       codebooks, ids_tm, norms_tm, n_pair, per, codes_tm, bb.dist_f, bb.sums, bb.ties, words);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((ties_kernel<T, PQ, true>), tie_grid, dim3(kTieThreads), 0, s, D, lo, hi, kv, centroids,
+                       codebooks, ids_tm, norms_tm, bb.ties, words, codes_tm, bb.dist_f, bb.sums);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(codewords_kernel, dim3(static_cast<unsigned>((n * PQ::DSUB + 255) / 256)), dim3(256), 0, s,

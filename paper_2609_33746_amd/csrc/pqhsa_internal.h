@@ -310,12 +310,16 @@ inline SubSums sub_sums_at(void* at, int64_t codewords, int dims) {
     uint32_t* counts = reinterpret_cast<uint32_t*>(sums + 2 * codewords * dims);
     return SubSums{sums, sums + codewords * dims, counts, counts + codewords};
 }
+// words of the tie marks per (b, kv head, subspace): a bit per token of R_b, in
+// whole steps of 256 tokens
+inline int tie_words(const Dims& D) { return (D.rcap + 255) / 256 * 8; }
 struct BuildBufs {
     int32_t* order;      // [B, Hkv, rcap] tokens grouped by list, in id order within a list
     int32_t* offs;       // [B, Hkv, n_list + 1]
     float* dist_c;       // [B, Hkv, rcap]
     float* dist_f;       // [B, Hkv, M, rcap]
     SubSums sums;
+    uint32_t* ties;      // [B, Hkv, M, tie_words] tokens whose codeword subspace_kernel leaves open
     int32_t* seg_hist;   // [B, Hkv, segments of 4096 tokens, n_list] counts, then first positions
                          //   (at most 1024 lists)
     void* split;         // split_center_bytes: the centers as matrix-core operands

@@ -208,7 +208,28 @@ def test_a_key_with_an_infinity(bits, dtype):
         assert float((d.gather(1, z[:, None])[:, 0] - d.min(1).values).max()) <= TOL
 
 
-@pytest.mark.parametrize("bits,dtype,size", [(8, "f32", 1e-6), (4, "f32", 1e-6)])
+def _norms(k):
+    """||k|| in 32 bits, 16 sums of 8 dimensions added in pairs."""
+    x = k.float().view(-1, 16, 8)
+    ss = torch.zeros(x.shape[:2])
+    for e in range(8):
+        ss = _fma(x[:, :, e], x[:, :, e], ss)
+    while ss.shape[1] > 1:
+        ss = ss[:, 0::2] + ss[:, 1::2]
+    return torch.sqrt(ss[:, 0])
+
+
+def _hard_rows(count, gen, dtype):
+    """The rows of some 2^17 whose k / ||k|| lies closest to the middle of two 32-bit values."""
+    k = torch.randn((1 << 17, 128), generator=gen).to(dtype)
+    q = k.double() / _norms(k).double()[:, None]
+    steps = q.abs() * torch.exp2(23.0 - torch.floor(torch.log2(q.abs().clamp(min=1e-30))))
+    off = ((steps - torch.floor(steps)) - 0.5).abs().min(1).values
+    return k[torch.argsort(off)[:count]]
+
+
+@pytest.mark.parametrize("bits,dtype,size", [(8, "f32", 1.0), (4, "f32", 1.0), (8, "bf16", 1.0), (4, "bf16", 1.0),
+                                             (8, "f32", 1e-6), (4, "f32", 1e-6)])
 def test_a_codeword_of_one_token_is_its_residual(bits, dtype, size):
     """As many tokens as codewords, each the start of one: after a training pass every
     codeword is the mean of one residual, which is that residual bit for bit (the
@@ -221,9 +242,48 @@ def test_a_codeword_of_one_token_is_its_residual(bits, dtype, size):
     if size < 1.0:   # directions of one large dimension: the residuals of the others are as small as they are
         key[..., 0] = 1.0
     key = key.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    if size == 1.0:
+        key[0, 0, 4:4 + ksub] = _hard_rows(ksub, gen, key.dtype)
     ic = torch.full((1, 1, 1), 4)
     ip = (4 + torch.arange(ksub)).expand(1, 1, m, ksub)
     ix = _build(key.cuda(), key.cuda(), 1, bits, dtype, ic, ip, 0, 1)
     _, res = _slices(ix, key, torch.arange(4, 4 + ksub), bits)
     for s in range(0 if size >= 1.0 else 1, m):
         assert torch.equal(_bits(ix["codebooks"][0, 0, s].cpu()), _bits(res[:, s].contiguous())), s
+
+
+@pytest.mark.parametrize("bits,dtype", NAN_CASES)
+def test_near_codewords_are_the_choice_of_32_bit_sums(bits, dtype):
+    """Codewords in pairs that differ by the rounding of a direction, so that every token
+    has two to choose from: the code is the smallest ||p||^2 - 2 r . p of a chain of
+    32-bit fused multiply-adds over the dimensions (in the order of the matrix
+    instruction's steps), the first of equal ones."""
+    say(f"[near codewords] bits={bits} {dtype}")
+    m, ksub = (16, 256) if bits == 8 else (8, 16)
+    ds = 128 // m
+    n_r, n_list = 3000, 12
+    n = n_r + 132
+    gen = torch.Generator().manual_seed(bits)
+    key = torch.randn((1, 1, n, 128), generator=gen)
+    key = key.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    key[:, :, 5:n:2] = 1.2345 * key[:, :, 4:n - 1:2].float()   # pairs of tokens of nearly one direction
+    if dtype == "bf16":
+        key[:, :, 5:n:2] = 3 * key[:, :, 4:n - 1:2]            # a multiple that few bits of a key hold
+    ic = 4 + 2 * torch.randperm(n_r // 2, generator=gen)[:n_list][None, None]
+    first = 4 + 2 * torch.stack([torch.randperm(n_r // 2, generator=gen)[:ksub // 2] for _ in range(m)])
+    ip = torch.stack([first, first + 1], -1).reshape(1, 1, m, ksub)
+    ix = _build(key.cuda(), key.cuda(), n_list, bits, dtype, ic, ip, 0, 0)
+    t = torch.arange(4, 4 + n_r)
+    _, res = _slices(ix, key, t, bits)
+    cb = ix["codebooks"][0, 0].cpu()
+    order = [q * (ds // 4) + s for s in range(ds // 4) for q in range(4)]
+    for s in range(m):
+        p2 = torch.zeros(ksub)
+        for x in range(ds):
+            p2 = _fma(cb[s, :, x], cb[s, :, x], p2)
+        dot = torch.zeros((n_r, ksub))
+        for x in order:
+            dot = _fma(res[:, s, x:x + 1], cb[s, :, x][None], dot)
+        want = _fma(torch.tensor(-2.0), dot, p2[None]).numpy().argmin(1)
+        got = ix["codes"][0, 0, t, s].cpu().numpy()
+        assert (got == want).all(), (s, int((got != want).sum()))
