@@ -19,6 +19,7 @@
 // candidate loads are issued in batches, and every workgroup-wide step is one
 // scan or reduction, so the dependency chain stays short.
 #include <algorithm>
+#include <cmath>
 #include <type_traits>
 
 #include "device_common.h"
@@ -754,33 +755,38 @@ __global__ __launch_bounds__(kSelThreads) void select_wide_kernel(Dims D, BatchA
     select_row<kDev, kSelCapWide, kBx>(D, ba, ix, w, force_fallback);
 }
 
-// Candidates the sampled threshold is likely to leave for a row of n_r tokens
-// and budget k: its rank among the samples (see the prologue) in tokens, and
-// 30% for the sample's spread (over the rows of the 128K workload the counts
-// range over -20% to +15%).
+// Candidates the sampled threshold is likely to leave, at most, for a row of
+// n_r tokens and budget k: its rank c among the samples (see the prologue) in
+// tokens, and 2.2 / sqrt(c) more for the spread of a sample's c-th largest. In
+// units of that spread, the capacity that the rows of a call still fit lies
+// between 1.9 and 2.3 above the rank: 32 to 288 rows of 64K to 512K tokens take
+// fewer us with a capacity 2.3 above it (two workgroups per CU, 288 rows of
+// 128K, 2%: 203 against 213 with one; one plain row set of 128K, 3.75%: 66 against
+// 70 with the wide one) and more with one 1.9 above it (288 rows of 200K, 1.25%:
+// 205 against 192; 32 rows of 512K, 0.7%: 81 against 76), where a row or two
+// takes the global-memory path.
 static int expected_candidates(int n_r, int k) {
     if (n_r <= 0) return 0;
     const SampleRuns sr = sample_runs(n_r);
     const double ns = static_cast<double>(sr.nrun) * sr.run_len;
     const double c = 2.0 * k * ns / n_r + 8.0;
     if (c > ns) return n_r;   // no threshold: every token
-    return static_cast<int>(std::min<double>(n_r, 1.3 * c * n_r / ns));
+    return static_cast<int>(std::min<double>(n_r, (1.0 + 2.2 / std::sqrt(c)) * c * n_r / ns));
 }
 
-// The capacity of a call's select:
-//  * wide when a row is likely to have more candidates than the plain one
-//    holds: such rows took the global-memory path (one sequence of 512K tokens,
-//    1%: the select 189 -> 28 us);
+// The capacity of a call's select, by the row likely to have the most candidates:
+//  * wide when that is more than the plain one holds: such rows took the
+//    global-memory path (one sequence of 512K tokens, 1%: the select 189 -> 28 us);
 //  * small when the rows outnumber the CUs, two of its workgroups fit in one
-//    CU's LDS and the rows' candidates are likely to fit it.
+//    CU's LDS and that many candidates fit it.
 // Budgets that are device data are unknown here, and the context's largest may
 // be far above the step's: up to 1/64 of the tokens is provided for (rows of
 // more take the global-memory path).
-static int select_cap(const Dims& D, const BatchArgs& ba, bool dev_args) {
+static int select_cap(const Dims& D, const int32_t* n_r, const int32_t* topk, bool dev_args) {
     int c_max = 0;
     for (int b = 0; b < D.B; ++b) {
-        const int k = dev_args ? std::min(D.max_topk, ba.n_r[b] / 64) : ba.topk[b];
-        c_max = std::max(c_max, expected_candidates(ba.n_r[b], k));
+        const int k = dev_args ? std::min(D.max_topk, n_r[b] / 64) : topk[b];
+        c_max = std::max(c_max, expected_candidates(n_r[b], k));
     }
     if (c_max > kSelCap) return kSelCapWide;
     const int n_cu = device_cu_count();
@@ -791,11 +797,22 @@ static int select_cap(const Dims& D, const BatchArgs& ba, bool dev_args) {
     return kSelCap;
 }
 
+// The tests' view of that rule: the capacity a call would take.
+extern "C" int pqhsa_select_capacity(int batch, int n_q_heads, int n_list, int max_topk, const int32_t* n_r,
+                                     const int32_t* topk, int dev_args) {
+    Dims D{};
+    D.B = batch;
+    D.Hq = n_q_heads;
+    D.n_list = n_list;
+    D.max_topk = max_topk;
+    return select_cap(D, n_r, topk, dev_args != 0);
+}
+
 template <bool kDev, bool kBx>
 static void launch_select_d(const Dims& D, const BatchArgs& ba, const Index& ix, const Work& w,
                             int force_fallback, hipStream_t s, const KTiming& tm) {
     const dim3 grid(D.B * D.Hq), block(kSelThreads);
-    switch (select_cap(D, ba, kDev)) {
+    switch (select_cap(D, ba.n_r, ba.topk, kDev)) {
         case kSelCapSmall:
             hipExtLaunchKernelGGL((select_small_kernel<kDev, kBx>), grid, block,
                                   SelLayout<kSelCapSmall>::bytes(D.n_list), s, tm.start, tm.stop, 0, D, ba,
