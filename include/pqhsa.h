@@ -79,7 +79,8 @@ typedef struct pqhsa_ctx pqhsa_ctx;
 
 /* Create a context: validates the shape and allocates, on the current HIP
  * device, the prepared-index storage and the whole decode workspace, so that
- * decode calls allocate nothing. *out receives the context (NULL on error).
+ * decode calls allocate nothing (the dense decode's split partials alone take
+ * 4.3 MB in the smallest context). *out receives the context (NULL on error).
  * Shape errors are reported before any HIP call is made. */
 pqhsa_status pqhsa_create(const pqhsa_shape* shape, pqhsa_ctx** out);
 

@@ -293,7 +293,9 @@ pqhsa_status pqhsa_create(const pqhsa_shape* shape, pqhsa_ctx** out) {
     c->nsplit_max = (D.n_sink + D.n_local + kTailGrowth + shape->max_topk + D.attn_rows - 1) / D.attn_rows;
     if (c->nsplit_max < 1) c->nsplit_max = 1;
     const int n_bgc = (D.n_list + kBgLists - 1) / kBgLists;
-    c->dense_partials = std::max<size_t>(BQ * ((D.rcap + kDenseRows - 1) / kDenseRows), kDensePartials);
+    // the splits of kDenseRows rows, and up to one workgroup per CU more
+    const size_t n_cu = device_cu_count() > 0 ? device_cu_count() : 256;
+    c->dense_partials = std::max<size_t>(BQ * ((D.rcap + kDenseRows - 1) / kDenseRows) + G * n_cu, kDensePartials);
 
     Work& w = c->w;
     hipError_t ea = hipSuccess;

@@ -19,6 +19,8 @@
 //    then Z_B += M_j and N_B += M_j * v_bar_j (Eq. 4), reading each list mean
 //    once for the whole group.
 //  * merge_kernel: log-sum-exp of all partials of a row, y = N / Z (Eq. 5).
+#include <algorithm>
+
 #include "device_common.h"
 #include "pqhsa.h"
 #include "pqhsa_internal.h"
@@ -388,9 +390,8 @@ static_assert(kMergeBatch <= kMergeThreads, "one (m, Z) per thread");
 // kGroups groups of kMergeThreads threads: group gi folds batches gi,
 // gi + kGroups, ... of the row's partials, then the groups' results fold in
 // LDS. One group serves rows of up to kMergeBatch (40) partials and two
-// groups rows of up to 80, each in one round trip (the PQ-HSA rows and the
-// dense decode up to 128K rows); longer dense rows (more than 80 splits of
-// 2048 rows) take 8. (40 partials per group: a 128K row of 64-row splits has
+// groups rows of up to 80, each in one round trip; rows of more, which only the
+// dense decode has, take 8, and more than one round trip beyond 320. (40 partials per group: a 128K row of 64-row splits has
 // 39; the merge took 4.3 us against 4.8 us with two groups of 32.)
 template <int kGroups>
 __global__ __launch_bounds__(kMergeThreads * kGroups) void merge_kernel(
@@ -612,36 +613,58 @@ __device__ __forceinline__ void dense_load(Raw8<T> (&kr)[R], Raw8<T> (&vr)[R], c
     }
 }
 
-// Cache rows per dense split. The kernel is bound by memory once about two
-// workgroups per CU stream (fewer leave loads out of flight, more pay for their
-// partials): as many splits as make that many workgroups, the same for every
-// KV head. Measured with 2048 rows always -> this, us per call (32 / 8 heads,
-// bf16): 4K tokens 62 -> 14, 16K 62 -> 21, 32K 61 -> 35, 128K 100 -> 100, four
-// sequences of 50001 179 -> 155. Sequences of different lengths take twice the
-// splits where these are long, so that the short ones' share spreads (8 of
-// 15K-30K: 151 -> 144), and none is longer than kDenseRowsMax (16 of
-// 64K-128K: 1176 -> 1143; with nontemporal loads 1007). Groups of eight heads
-// are bound by their arithmetic, which spreads better over four splits per CU
-// (32 / 4 heads, 4 of 128K: 2048 rows always 253, two per CU about 260, four
-// 249; 2 of 30K-60K at 16 / 2 heads 108, 43, 39; one of 128K 109, 74, 76).
-static int dense_split_rows(const Dims& D, const BatchInts& lens, size_t partials) {
+// Cache rows per dense split: 128 to 2048 (kDenseRows, the longest serial sum
+// that a stream takes), the same for every KV head. The kernel is bound by memory
+// once about two workgroups a CU stream bf16 rows, or one fp32 rows, which hold
+// twice the bytes in flight; from there on a whole number of workgroups per CU
+// is what counts, and more splits only pay for their partials. Measured against
+// 2048 rows always, us per call at 8 query and 8 KV heads / 32 and 8:
+//   bf16, one sequence of 16384 tokens        29.3 -> 17.6 / 61.2 -> 21.0
+//   bf16, four of 50001 (3.1 -> 4.0 a CU)      138 -> 125 / 158 -> 132
+//   fp32, one of 8192                         28.8 -> 16.7 / 50.5 -> 19.8
+//   fp32, eight of 150000, 2 KV heads (4.6 -> 5.0 a CU)  406 -> 402 / 424 -> 414
+// and the same splits for one sequence of 131072 bf16 or 65536 fp32. Groups of
+// eight heads in bf16 are bound by their arithmetic and take four workgroups a
+// CU where that leaves more than 256 rows (one of 65536: two a CU 75.6, four
+// 71.4; one of 16384 30.0 and 33.4). Sequences of different lengths of few
+// splits each take twice as many, so that the short ones' share spreads (eight
+// of 15001-30000, bf16 125 -> 122 / 138 -> 126; with more splits 1-2% slower). A
+// row has at most 256 partials unless it needs more splits: its merge reads
+// them in turn (one KV head, 131072 tokens, bf16: 512 partials 26.3, 256 21.0).
+static int dense_split_rows(const Dims& D, bool bf16, const BatchInts& lens, size_t partials) {
     int n_min = lens.v[0], n_max = lens.v[0];
     for (int b = 1; b < D.B; ++b) {
         n_min = lens.v[b] < n_min ? lens.v[b] : n_min;
         n_max = lens.v[b] > n_max ? lens.v[b] : n_max;
     }
-    const int units = D.B * D.Hkv;
-    auto rows_for = [&](int wgs) {
-        const int nsplit = wgs / units > 1 ? wgs / units : 1;
-        const int rows = ((n_max + nsplit - 1) / nsplit + kDenseStep - 1) / kDenseStep * kDenseStep;
-        return rows < kDenseRowsMin ? kDenseRowsMin : rows > kDenseRowsMax ? kDenseRowsMax : rows;
-    };
+    const int64_t units = static_cast<int64_t>(D.B) * D.Hkv;
     const int n_cu = device_cu_count() > 0 ? device_cu_count() : 1;
-    int rows = rows_for((D.G >= 8 ? 4 : 2) * n_cu);
-    if (n_min < n_max && rows > kDenseRowsMax / 4 && rows < kDenseRowsMax) rows = rows_for(4 * n_cu);
-    // a buffer that holds no more keeps to the splits it was sized for
-    if (static_cast<size_t>(units) * D.G * ((n_max + rows - 1) / rows) > partials) rows = kDenseRows;
-    return rows;
+    // splits of the longest sequence that make this many workgroups a CU, and their rows
+    auto splits_for = [&](int64_t per_cu) { return static_cast<int>(std::max<int64_t>(1, per_cu * n_cu / units)); };
+    auto rows_for = [&](int nsplit) { return ((n_max + nsplit - 1) / nsplit + kDenseStep - 1) / kDenseStep * kDenseStep; };
+    const int need = (n_max + kDenseRows - 1) / kDenseRows;
+    int64_t per_cu = std::max<int64_t>(bf16 ? 2 : 1, (units * need + n_cu - 1) / n_cu);
+    if (bf16 && D.G >= 8 && per_cu < 4 && rows_for(splits_for(per_cu)) > 512) per_cu = 4;
+    auto fits = [&](int rows) { return static_cast<size_t>(units) * D.G * ((n_max + rows - 1) / rows) <= partials; };
+    int nsplit = splits_for(per_cu);
+    if (n_min < n_max && nsplit <= 16 && rows_for(nsplit) > kDenseRows / 2 && fits(rows_for(splits_for(2 * per_cu))))
+        nsplit = splits_for(2 * per_cu);
+    int rows = rows_for(std::min(nsplit, std::max(256, need)));
+    rows = rows < kDenseRowsMin ? kDenseRowsMin : rows > kDenseRows ? kDenseRows : rows;
+    return fits(rows) ? rows : kDenseRows;   // the rows that any buffer is sized for
+}
+
+// The tests' view of that rule, for a buffer of that many partials.
+extern "C" int pqhsa_dense_split_rows(int batch, int n_q_heads, int n_kv_heads, int bf16, const int32_t* seq_lens,
+                                      int64_t partials) {
+    Dims D{};
+    D.B = batch;
+    D.Hq = n_q_heads;
+    D.Hkv = n_kv_heads;
+    D.G = n_q_heads / n_kv_heads;
+    BatchInts lens{};
+    std::copy(seq_lens, seq_lens + batch, lens.v);
+    return dense_split_rows(D, bf16 != 0, lens, static_cast<size_t>(partials));
 }
 
 // Fold R rows into o with a lazily moved shift: o.m changes only when a row's
@@ -761,7 +784,7 @@ hipError_t launch_dense(const Dims& D, const KV& kv, const BatchInts& lens, floa
                         size_t partials, float* out, hipStream_t s) {
     int n_max = 1;
     for (int b = 0; b < D.B; ++b) n_max = lens.v[b] > n_max ? lens.v[b] : n_max;
-    const int rows = dense_split_rows(D, lens, partials);
+    const int rows = dense_split_rows(D, kv.bf16, lens, partials);
     const int nsplit = (n_max + rows - 1) / rows;
     const hipError_t e = kv.bf16 ? launch_dense_g<bf16_t>(D, kv, lens, partial, nsplit, rows, s)
                                  : launch_dense_g<float>(D, kv, lens, partial, nsplit, rows, s);

@@ -46,9 +46,8 @@ constexpr int kMaxSeq = 1 << kPosBits;
 constexpr int kAttnRows = 128;     // exact-set rows per split, the larger of the two sizes
 constexpr int kAttnRowsSmall = 64; // the split of small exact sets (see attn_rows_for)
 constexpr int kBgLists = 64;       // lists per background workgroup
-constexpr int kDenseRows = 2048;     // cache rows per dense split that sizes the partial buffers
-constexpr int kDenseRowsMin = 128;   // rows per split of a call (see dense_split_rows)
-constexpr int kDenseRowsMax = 4096;
+constexpr int kDenseRows = 2048;     // cache rows per dense split, at most; sizes the partial buffers
+constexpr int kDenseRowsMin = 128;   // and at least (see dense_split_rows)
 constexpr int kDenseStep = 32;       // multiples of
 constexpr int kDensePartials = 8192; // partials a context's dense buffer holds at least
 constexpr int kPartStride = 132;   // floats per partial: m, Z, pad, pad, N[128]
