@@ -913,9 +913,9 @@ __global__ __launch_bounds__(kAsgThreads) void assign_kernel(Dims D, BatchInts l
 // close to a second center (near, n_near per KV head), by the distance the
 // 32-bit matrix cores give (v_mfma_f32_16x16x4f32): which of two such centers is
 // called the nearest is then the same as with those alone. One token in some
-// thousands comes here; where many centers coincide it can be all of them, and
-// then costs what that search costs for every token (3.2 ms at 128K tokens x 8
-// KV heads x 1024 lists).
+// thousands comes here (55 us at 128K tokens x 8 KV heads x 1024 lists); where
+// centers coincide it can be all of them, which takes 5.3 ms there (6.9 with 32
+// workgroups per KV head; the search with these instructions alone took 3.2).
 //
 // ||u - c||^2 = ||u||^2 + ||c||^2 - 2 u . c: 32 tokens per workgroup step (2
 // tiles of 16), centers in chunks of 64 through LDS, the next chunk's loads
@@ -931,7 +931,8 @@ constexpr int kNearThreads = 256;
 constexpr int kNearTok = 32;                   // tokens per workgroup step
 constexpr int kNearCen = 64;                   // centers per chunk, a tile per wave
 constexpr int kNearLd = kHeadDim + 4;          // LDS row stride (floats)
-constexpr int kNearWgs = 32;                   // workgroups per KV head
+constexpr int kNearWgs = 32;                   // workgroups per KV head, at least
+constexpr int kNearPerCu = 3;                  // workgroups whose LDS a CU holds (51 KB each)
 static_assert(kNearCen == kNearThreads / kWave * 16, "one center tile per wave");
 
 __device__ __forceinline__ void near_fold(float& d, int& i, float od, int oi) {
@@ -956,9 +957,10 @@ __global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
     __shared__ int wi[kNearThreads / kWave][kNearTok];
     float* tok = reinterpret_cast<float*>(tok4);
     float* rows = reinterpret_cast<float*>(cen4);
-    const int b = blockIdx.z;
-    const int g = blockIdx.y;
-    const int bg = b * D.Hkv + g;
+    // the KV heads along the grid's first dimension: the few workgroups that usually
+    // have tokens come first, each on a CU of its own
+    const int bg = blockIdx.x;
+    const int b = bg / D.Hkv, g = bg % D.Hkv;
     const int n = static_cast<int>(n_near[bg]);
     const int32_t* list = near + static_cast<int64_t>(bg) * D.rcap;
     const int tid = threadIdx.x;
@@ -969,8 +971,8 @@ __global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
     const T* kb = static_cast<const T*>(kv.k) + b * kv.sb + g * kv.sh;
     const float* cen = centroids + static_cast<int64_t>(bg) * D.n_list * kHeadDim;
 
-    for (int base = static_cast<int>(blockIdx.x) * kNearTok; base < n;
-         base += static_cast<int>(gridDim.x) * kNearTok) {
+    for (int base = static_cast<int>(blockIdx.y) * kNearTok; base < n;
+         base += static_cast<int>(gridDim.y) * kNearTok) {
         const int nt = min(kNearTok, n - base);
         // the chunks' loads: 32 float4 per center row, zeros past the last center
         constexpr int kLoads = kNearCen * kHeadDim / 4 / kNearThreads;
@@ -1652,7 +1654,9 @@ hipError_t launch_assign(const Dims& D, const BatchInts& lo, const BatchInts& hi
     if (e != hipSuccess) return e;
     const int tok = kAsgWaves * 32 * (kv.bf16 ? AsgTokens<bf16_t>::kTiles : AsgTokens<float>::kTiles);
     const dim3 grid((max_n + tok - 1) / tok, D.Hkv, D.B);
-    const dim3 near_grid(std::min(kNearWgs, (max_n + kNearTok - 1) / kNearTok), D.Hkv, D.B);
+    const int n_cu = device_cu_count() > 0 ? device_cu_count() : 1;
+    const int near_wgs = std::max(kNearWgs, kNearPerCu * n_cu / (D.B * D.Hkv));
+    const dim3 near_grid(D.B * D.Hkv, std::min(near_wgs, (max_n + kNearTok - 1) / kNearTok));
 #define PQHSA_ASSIGN(TT)                                                                                    \
     do {                                                                                                    \
         hipLaunchKernelGGL(assign_kernel<TT>, grid, dim3(kAsgThreads), 0, s, D, lo, hi, kv, parts, n_tile,  \

@@ -95,12 +95,12 @@ def _slices(ix, key, tokens, bits):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("n_r,n_list,pairs", [(3000, 64, 32), (2900, 129, 50), (4000, 40, 1)])
+@pytest.mark.parametrize("n_r,n_list,pairs", [(3000, 64, 32), (2900, 129, 50), (25000, 40, 1)])
 def test_near_centers_are_the_choice_of_32_bit_sums(n_r, n_list, pairs, dtype):
     """Centers in pairs of nearly one direction (the other ones ordinary; with one pair, all
     the others coincide): the list is the smallest ||c||^2 - 2 u . c of 32-bit sums in the
     order of the matrix instruction's steps, the first of equal ones. Every token is then a
-    near tie, over 1024 of them per KV head."""
+    near tie, in the last case more of them than one round of its workgroups takes."""
     say(f"[near centers] n_r={n_r} n_list={n_list} pairs={pairs} {dtype}")
     n = n_r + 132
     gen = torch.Generator().manual_seed(n_list)
