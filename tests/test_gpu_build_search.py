@@ -95,21 +95,31 @@ def _slices(ix, key, tokens, bits):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("n_r,n_list,pairs", [(3000, 64, 32), (2900, 129, 50), (25000, 40, 1)])
-def test_near_centers_are_the_choice_of_32_bit_sums(n_r, n_list, pairs, dtype):
+@pytest.mark.parametrize("n_r,n_list,pairs,apart", [(3000, 64, 32, False), (2900, 129, 50, False),
+                                                    (25000, 40, 1, False), (25000, 64, 32, True)])
+def test_near_centers_are_the_choice_of_32_bit_sums(n_r, n_list, pairs, apart, dtype):
     """Centers in pairs of nearly one direction (the other ones ordinary; with one pair, all
     the others coincide): the list is the smallest ||c||^2 - 2 u . c of 32-bit sums in the
     order of the matrix instruction's steps, the first of equal ones. Every token is then a
-    near tie, in the last case more of them than one round of its workgroups takes."""
-    say(f"[near centers] n_r={n_r} n_list={n_list} pairs={pairs} {dtype}")
+    near tie, in the third case more of them than one round of its workgroups takes. With the
+    pairs apart (by one bit of one element, or 1e-4 of each) the squared distances differ by
+    about 1e-5: some tokens are near ties, and the others are up to the bf16 products alone
+    (a CPU model of these without the product of the first center and second key part differs
+    for 28 tokens in 32 bits, without the second and first for thousands in either type)."""
+    say(f"[near centers] n_r={n_r} n_list={n_list} pairs={pairs} apart={apart} {dtype}")
     n = n_r + 132
     gen = torch.Generator().manual_seed(n_list)
     key = torch.randn((1, 1, n, 128), generator=gen)
-    if dtype == "bf16":
-        key = key.to(torch.bfloat16)
-        key[:, :, 5:n:2] = 3 * key[:, :, 4:n - 1:2]
+    key = key.to(torch.bfloat16 if dtype == "bf16" else torch.float32)
+    even = key[:, :, 4:n - 1:2]
+    if not apart:
+        key[:, :, 5:n:2] = (3 if dtype == "bf16" else 1.2345) * even
+    elif dtype == "bf16":
+        bits = even.clone().view(torch.int16)
+        x = torch.randint(128, (*bits.shape[:3], 1), generator=gen)
+        key[:, :, 5:n:2] = bits.scatter(3, x, bits.gather(3, x) + 1).view(torch.bfloat16)
     else:
-        key[:, :, 5:n:2] = 1.2345 * key[:, :, 4:n - 1:2]
+        key[:, :, 5:n:2] = even + 1e-4 * torch.randn(even.shape, generator=gen)
     pick = 4 + 2 * torch.randperm(n_r // 2, generator=gen)
     near = torch.stack([pick[:pairs], pick[:pairs] + 1], -1).flatten()
     rest = pick[pairs:pairs + n_list - 2 * pairs] if pairs > 1 else pick[1:2].expand(n_list - 2)
