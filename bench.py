@@ -703,7 +703,7 @@ def summarize_build(stats_csv: str, command: str) -> str:
         out.append(f"{name}  {calls}  {float(r['AverageNs']) / 1e3:.2f}  {float(r['MinNs']) / 1e3:.2f}  "
                    f"{float(r['MaxNs']) / 1e3:.2f}  {tot / 1e3:.1f}")
         tot_ns += tot
-        if any(k in name for k in ("assign_kernel", "nearest_kernel", "subspace_kernel")):
+        if any(k in name for k in ("assign_kernel", "nearest_kernel", "subspace_kernel", "ties_kernel")):
             search_ns += tot
         if "subspace_kernel" in name:
             sub_calls += calls
@@ -712,7 +712,7 @@ def summarize_build(stats_csv: str, command: str) -> str:
         per_build_ms = search_ns / builds / 1e6
         tflops = fl["flops"] / (search_ns / builds * 1e-9) / 1e12
         out.append(f"builds profiled: {builds:g}; kernel time per build {tot_ns / builds / 1e6:.2f} ms, "
-                   f"of which searches (assign, nearest and subspace kernels) {per_build_ms:.2f} ms")
+                   f"of which searches (assign, nearest, subspace and ties kernels) {per_build_ms:.2f} ms")
         out.append(f"searches: {tflops:.1f} TFLOP/s of bf16 products = {tflops / BF16_PEAK_TFLOPS:.3f} of "
                    f"the {BF16_PEAK_TFLOPS:.0f} TFLOP/s dense bf16 peak")
     return "\n".join(out) + "\n"
