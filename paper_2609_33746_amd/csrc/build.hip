@@ -683,7 +683,7 @@ __device__ __forceinline__ bf8_t norm_slots(float r, int half) {
 // 32 (25 KB) at a time, the next tile's loads under the current one's
 // products. v_mfma_f32_32x32x16_bf16: element i of lane l is center
 // 8 (i / 4) + 4 (l / 32) + i mod 4 against token l mod 32. 128K tokens x 8 KV
-// heads against 1024 lists: 0.71 ms (1.2 PFLOP/s of bf16 products, about what
+// heads against 1024 lists: 0.71-0.76 ms (1.1-1.2 PFLOP/s of bf16 products, about what
 // a large library product reaches here) in place of 3.19 ms with
 // v_mfma_f32_16x16x4f32 and a distance and a two-key compare per pair.
 // ---------------------------------------------------------------------------
@@ -1133,9 +1133,9 @@ __global__ __launch_bounds__(kNearThreads) void nearest_kernel(Dims D, KV kv,
 // remainder of the few residuals below 2^-17 that leave one, 64 bits of 2^-84.
 // That replaces the grouping of every subspace's tokens and the gathers of
 // their means.
-// 128K tokens x 8 KV heads, Pq8: a training pass 0.85 ms, the final one 0.77 ms (1.9 ms with v_mfma_f32_16x16x4f32
-// and a two-key compare per pair; the grouping and gathers took another 1.3 ms
-// a training pass). Two prompts of 40K, Pq4: 0.15 and 0.10 ms (0.20 ms, and 0.4 ms).
+// 128K tokens x 8 KV heads, Pq8: a training pass 0.85-0.90 ms, the final one
+// 0.77-0.82 ms (1.9 ms with v_mfma_f32_16x16x4f32 and a two-key compare per pair;
+// the grouping and gathers took another 1.3 ms a training pass). Two prompts of 40K, Pq4: 0.15 and 0.10 ms (0.20 ms, and 0.4 ms).
 // ---------------------------------------------------------------------------
 constexpr int kSubThreads = 512;
 constexpr int kSubWaves = kSubThreads / kWave;
@@ -1465,10 +1465,9 @@ __global__ __launch_bounds__(kSubThreads) void subspace_kernel(
 //
 // One workgroup per problem and kTieWords words of marks, which it lists first;
 // most find a few tokens or none, so each wave takes 16 of them against all the
-// codewords: 22 us a pass at
-// 128K tokens x 8 KV heads with Pq8 (2.2 ms where all codewords coincide). With it
-// and the second smallest value subspace_kernel takes 0.85 and 0.77 ms there,
-// 0.75 and 0.69 without.
+// codewords: 22 us a pass at 128K tokens x 8 KV heads with Pq8 (2.2 ms where all
+// codewords coincide). With it and the second smallest value subspace_kernel
+// takes 0.85 and 0.77 ms there, 0.75 and 0.69 without.
 // ---------------------------------------------------------------------------
 constexpr int kTieThreads = 256;
 constexpr int kTieWords = kTieThreads;
